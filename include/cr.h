@@ -325,8 +325,8 @@ cr_status cr_replay_partition(const uint32_t* keys, const uint16_t* suffix, cons
  * segments replays the segment before the run (without counting it) and then the run, in
  * order. Each request is thus replayed at most twice and scanned at most nine times,
  * whatever the key mix; the results do not depend on which launch counts them.
- * The launches of the first pass (one per list size, ceil(W/64) registers, and one per
- * grouped form) are independent of each other. When there are two or more and `stream`
+ * The launches of the first pass (one per class of list sizes and one per grouped form)
+ * are independent of each other. When there are two or more and `stream`
  * is not capturing, they run on two side streams of the device, forked from `stream`
  * by an event and joined back to it before the second launch: the side streams and
  * their three events are created by the first such call on a device (hipStreamCreate,

@@ -15,7 +15,7 @@ __device__ __forceinline__ uint32_t lane_id()
     return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
 
-__device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 // Raises the calling wavefront's instruction-issue priority on its SIMD (s_setprio 3). The
 // placement, routing and partition kernels are chains of dependent latency-bound steps; when

@@ -8,7 +8,7 @@
 //        arrival order; each record packs (key, suffix, interval) into 8 bytes;
 //        k_seg_items also splits every (candidate, destination) stream into segments of
 //        S records;
-//   k_replay<SL>
+//   k_replay, k_replay_hash
 //        one wavefront per segment. The LRU state before a segment is exactly the most
 //        recent W distinct keys seen at that destination (carried state appended), so a
 //        wavefront rebuilds it by scanning backwards, then replays its segment. This
@@ -17,18 +17,11 @@
 //   k_replay_grp<G>
 //        lists of at most 16 slots in calls with one interval: G = 4 or 8 segments per
 //        wavefront, one per lane group (below).
-// The LRU lives in registers. Up to 64 slots it is a move-to-front list across the lanes:
-// lane i holds the i-th most recent key. A lookup is one compare and a ballot; the first
-// set bit p is the hit depth, and the update shifts lanes 0..p (all lanes on a miss) up
-// by one and writes the key into lane 0, a single select between a lane and its left
-// neighbour under a scalar mask. Above 64 slots the list takes SL = ceil(W / 64)
-// registers. Up to 128 slots it is interleaved over them (position SL * lane + s in
-// register s), so that moving a position back by one is a copy from register s-1 in the
-// same lane, and only the last register wraps into register 0 of the next lane through a
-// one-lane DPP shift; an access is SL compares and SL selects under scalar masks, without
-// branches. Above 128 slots it is two-level: the 64 most recent keys in a front register
-// that every access updates like the one-register list, the rest interleaved behind it and
-// touched only when the front misses. No form needs a per-request search or reduction.
+// Below 64 slots the LRU is a move-to-front list across the lanes of one register: lane i
+// holds the i-th most recent key. A lookup is one compare and a ballot; the first set bit p is
+// the hit depth, and the update shifts lanes 0..p (all lanes on a miss) up by one and writes
+// the key into lane 0, a single select between a lane and its left neighbour under a scalar
+// mask. From 64 slots it is a hash table in LDS that takes 64 records per step (below).
 #include "cr_common.h"
 
 #include <mutex>
@@ -44,7 +37,7 @@ struct WArg {
     uint32_t seg_min;  // shortest segment for this call's record count
 };
 
-// The candidates one k_replay launch serves and the first wavefront of each: wavefront v
+// The candidates one k_replay or k_replay_hash launch serves and the first wavefront of each: wavefront v
 // takes work item v - wv0[i] of candidate cand[i] for wv0[i] <= v < wv0[i + 1]. Each
 // candidate gets as many wavefronts as it can have work items (one per stream plus one per
 // full segment), so a launch runs no wavefront for another list size's candidates. n = 0
@@ -101,18 +94,23 @@ __host__ __device__ __forceinline__ uint32_t grp_of(uint32_t W, uint32_t J)
     return W <= 8u ? 8u : 4u;
 }
 
-// Registers per lane of a W-slot list: ceil(W / 64), 1 .. 8. An access costs about one
-// compare and one select per register, so each W gets the fewest that hold it.
-__host__ __device__ __forceinline__ uint32_t slot_class(uint32_t W)
-{
-    const uint32_t sl = (W + 63u) / 64u;
-    return sl < 1u ? 1u : (sl > 8u ? 8u : sl);
-}
+// How a list of W slots is replayed one per wavefront: class 0 the list in a register
+// (k_replay), 1 .. 4 the hash table (k_replay_hash) for up to kHashW[class] slots. The hash
+// form needs W >= 64. Table sizes by measurement, 4e7 requests x 8 candidates over 1,024
+// streams: W = 86 2.67 / 2.69 / 2.83 ms with 384 / 512 / 640 slots, W = 156 3.12 / 2.95 / 2.78
+// with 512 / 640 / 768, W = 283 3.21 / 3.10 / 3.49 with 768 / 1,024 / 1,280, W = 512 3.93 /
+// 3.60 / 3.51 / 3.96 with 1,024 / 1,280 / 1,536 / 2,048: a small table is refreshed more often
+// and probes further, a large one leaves fewer wavefronts per CU.
+constexpr uint32_t kHashFrom = 64;
+constexpr uint32_t kClasses = 5;
+constexpr int kHashW[kClasses] = {0, 96, 192, 384, 512};
+constexpr int kHashSlots[kClasses] = {0, 384, 768, 1024, 1536};
 
-// Lists of 3 registers and more are two-level (a 64-key front and the rest behind it). On
-// the 1e8-request sweep: W = 156 19.8 ms two-level against 21.6 interleaved, W = 283 26.6
-// against 32.7; at W = 86 (two registers) interleaved was faster, 16.1 against 16.5 ms.
-constexpr uint32_t kTwoLevelFrom = 3;
+__host__ __device__ __forceinline__ uint32_t rep_class(uint32_t W)
+{
+    if (W < kHashFrom) return 0u;
+    return W <= (uint32_t)kHashW[1] ? 1u : (W <= (uint32_t)kHashW[2] ? 2u : (W <= (uint32_t)kHashW[3] ? 3u : 4u));
+}
 
 struct PartGeom {
     uint64_t tile;
@@ -712,43 +710,6 @@ __global__ __launch_bounds__(1024) void k_seg_items(const uint32_t* __restrict__
     if (c == 0) gwave_off[P] = wtot;
 }
 
-template <int SL>
-__device__ __forceinline__ bool lru_contains(const uint32_t (&skey)[SL], uint32_t kk)
-{
-    uint64_t m = 0;
-#pragma unroll
-    for (int s = 0; s < SL; ++s) m |= ballot(skey[s] == kk);
-    return m != 0;
-}
-
-// List positions in registers. Interleaved (kTwo false): position SL lane + s in register s.
-// Two-level (kTwo, SL >= 2): register 0 is the front, position lane (the 64 most recent
-// keys), and registers 1..SL-1 the back, position 64 + (SL-1) lane + (s-1) in register s.
-template <int SL, bool kTwo>
-__device__ __forceinline__ uint32_t list_pos(uint32_t s, uint32_t lane)
-{
-    if (kTwo) return s == 0 ? lane : 64u + (uint32_t)(SL - 1) * lane + (s - 1u);
-    return (uint32_t)SL * lane + s;
-}
-
-template <int SL, bool kTwo>
-__device__ __forceinline__ void lru_put_slot(uint32_t (&skey)[SL], uint32_t q, uint32_t kk, uint32_t lane)
-{
-    (void)lane;
-    uint32_t rs, rl;  // register and lane of position q
-    if (kTwo) {
-        const uint32_t b = q - 64u;
-        rs = q < 64u ? 0u : 1u + b % (uint32_t)(SL - 1);
-        rl = q < 64u ? q : b / (uint32_t)(SL - 1);
-    } else {
-        rs = q % (uint32_t)SL;
-        rl = q / (uint32_t)SL;
-    }
-#pragma unroll
-    for (int s = 0; s < SL; ++s)
-        if ((uint32_t)s == rs) skey[s] = wrlane(skey[s], kk, rl);
-}
-
 // Move-to-front update after a lookup whose hit mask is m: p = first set bit of m
 // (0xFFFFFFFF when none); lanes 1..p (every lane on a miss) take their left neighbour's
 // key and deeper lanes keep theirs, by one v_cndmask with a wave_shr:1 DPP source under
@@ -770,22 +731,6 @@ __device__ __forceinline__ uint32_t mtf_core(uint32_t& sk, uint64_t m)
     return p;
 }
 
-// mtf_core with the lane mask made by the vector unit (VCC = lanes above p, one compare of
-// the lane id with p) instead of s_lshl: for lists whose scalar unit is the busier one. A
-// miss (p = 0xFFFFFFFF) leaves VCC empty, so every lane shifts, as in mtf_core.
-__device__ __forceinline__ uint32_t mtf_core_v(uint32_t& sk, uint64_t m, uint32_t lane)
-{
-    uint32_t p, out;
-    asm("s_ff1_i32_b64 %1, %3\n\t"
-        "v_cmp_lt_u32 vcc, %1, %4\n\t"
-        "v_cndmask_b32_dpp %0, %2, %2, vcc wave_shr:1 row_mask:0xf bank_mask:0xf"
-        : "=v"(out), "=&s"(p)
-        : "v"(sk), "s"(m), "v"(lane)
-        : "vcc");
-    sk = out;
-    return p;
-}
-
 // Move-to-front access of key kk (lane i = i-th most recent key; lanes outside `wmask`
 // are ignored). Returns the hit depth, or 0xFFFFFFFF on a miss. On a miss the shift runs
 // over every lane, which drops the least recent key of a full list.
@@ -796,15 +741,15 @@ __device__ __forceinline__ uint32_t mtf_step(uint32_t& sk, uint32_t kk, uint64_t
     return p;
 }
 
-// Rebuild step over one full batch of 64 valid records (lane t = record t), newest first:
-// every key not yet collected is appended at position q (SL lane + s in register s). Each
-// record is branch-free: the put is a select on lane position == target, with target = q
-// for a new key and no position otherwise. q is compared with W once per 8 records, so up
-// to 7 keys may land past W; positions >= W are ignored everywhere (and positions past
-// the registers are never written). Returns the new q.
-template <int SL, bool kTwo>
-__device__ __forceinline__ uint32_t rebuild_batch(uint32_t (&sk)[SL], const uint64_t* __restrict__ rb, uint32_t q,
-                                                  uint32_t W, uint32_t lane)
+// Rebuild step over one full batch of 64 valid records, newest first: every key not yet
+// collected is appended at lane q. Positions q and up are free while the list is rebuilt, so
+// every key is written into lane q and q advances only past a new one; a repeated key left in
+// lane q duplicates an entry at a smaller position, which every later lookup finds first, and
+// the next new key overwrites it. Lanes past the final q are cleared once the rebuild ends. q
+// is compared with W once per 8 records; near W, where 8 keys might not fit the wave, a key
+// is put by a select on lane == q. Returns the new q.
+__device__ __forceinline__ uint32_t rebuild_batch(uint32_t& sk, const uint64_t* __restrict__ rb, uint32_t q, uint32_t W,
+                                                  uint32_t lane)
 {
     // keys by scalar loads from the batch's records (rb is uniform), 8 per load
     for (int g = 7; g >= 0 && q < W; --g) {
@@ -814,173 +759,24 @@ __device__ __forceinline__ uint32_t rebuild_batch(uint32_t (&sk)[SL], const uint
         uint32_t key[8];
 #pragma unroll
         for (uint32_t t = 0; t < 8; ++t) key[t] = (uint32_t)rk[7u - t];  // newest first
-        if (SL == 1 && q + 8u <= W) {
-            // Positions q and up are free while the list is rebuilt, so every key is written
-            // into lane q and q advances only past a new one; a repeated key left in lane q
-            // duplicates an entry at a smaller position, which every later lookup finds
-            // first, and the next new key overwrites it. Lanes past the final q are cleared
-            // once the rebuild ends. q + 8 <= W <= 64 keeps every write inside the wave.
+        if (q + 8u <= W) {
 #pragma unroll
             for (uint32_t t = 0; t < 8; ++t) {
-                const uint64_t m = ballot(sk[0] == key[t]);
-                sk[0] = wrlane(sk[0], key[t], q);
+                const uint64_t m = ballot(sk == key[t]);
+                sk = wrlane(sk, key[t], q);
                 asm("s_cmp_eq_u64 %1, 0\n\ts_addc_u32 %0, %0, 0" : "+s"(q) : "s"(m) : "scc");  // q += (m == 0)
             }
             continue;
         }
 #pragma unroll
         for (uint32_t t = 0; t < 8; ++t) {
-            uint64_t m = 0;
-#pragma unroll
-            for (int s = 0; s < SL; ++s) m |= ballot(sk[s] == key[t]);
-            const bool fresh = m == 0;
+            const bool fresh = ballot(sk == key[t]) == 0;
             const uint32_t target = fresh ? q : 0xFFFFFFFFu;
-#pragma unroll
-            for (int s = 0; s < SL; ++s) sk[s] = list_pos<SL, kTwo>((uint32_t)s, lane) == target ? key[t] : sk[s];
+            sk = lane == target ? key[t] : sk;
             q += fresh ? 1u : 0u;
         }
     }
     return q;
-}
-
-// Register 0 of the interleaved list after an access whose combined hit mask is m: with
-// l = first set bit of m (0xFFFFFFFF when none, which shifts by 63 and keeps no lane),
-// keep = ~1 << l and lanes outside keep take the last register's key from the lane before
-// (one v_cndmask with a wave_shr:1 DPP source); lane 0 is left for the caller. The scalar
-// steps precede the select in the same block, which gives the DPP read of `last` the two
-// wait states it needs after that register's last VALU write.
-__device__ __forceinline__ uint32_t il_core(uint32_t first, uint32_t last, uint64_t m, uint64_t& keep, uint32_t& l)
-{
-    asm("s_ff1_i32_b64 %1, %4\n\t"
-        "s_lshl_b64 %2, -2, %1\n\t"
-        "s_mov_b64 vcc, %2\n\t"
-        "v_cndmask_b32_dpp %0, %3, %0, vcc wave_shr:1 row_mask:0xf bank_mask:0xf"
-        : "+v"(first), "=&s"(l), "=&s"(keep)
-        : "v"(last), "s"(m)
-        : "vcc", "scc");  // s_lshl_b64 sets SCC
-    return first;
-}
-
-// Move-to-front access of key kk over the interleaved list (position SL lane + s in
-// register s; with kMasked, vm[s] masks the positions < W). Returns the hit position's
-// lane, or 0xFFFFFFFF on a miss. With the hit in lane l of register h, positions up to the
-// hit move back by one: register s > 0 takes register s-1 in lanes <= l (lanes < l when
-// s > h), register 0 takes the last register of the lane before in lanes 1..l, and lane 0
-// of register 0 takes the key. A miss moves every position, dropping the least recent key
-// of a full list.
-template <int SL, bool kMasked>
-__device__ __forceinline__ uint32_t mtf_step_il(uint32_t (&sk)[SL], uint32_t kk, const uint64_t (&vm)[SL])
-{
-    uint64_t mh[SL];
-    uint64_t m = 0;
-#pragma unroll
-    for (int s = 0; s < SL; ++s) {
-        mh[s] = ballot(sk[s] == kk);
-        if (kMasked) mh[s] &= vm[s];
-        m |= mh[s];
-    }
-    uint64_t keep;
-    uint32_t l;
-    const uint32_t r0 = il_core(sk[0], sk[SL - 1], m, keep, l);
-    uint64_t before[SL];  // hit bits of registers before s
-    before[0] = 0;
-#pragma unroll
-    for (int s = 1; s < SL; ++s) before[s] = before[s - 1] | mh[s - 1];
-#pragma unroll
-    for (int s = SL - 1; s >= 1; --s) sk[s] = __builtin_amdgcn_inverse_ballot_w64(keep | before[s]) ? sk[s] : sk[s - 1];
-    sk[0] = wrlane(r0, kk, 0u);
-    return l;
-}
-
-// 64 records (lane t of kl = key of record t, all valid) through the interleaved list;
-// returns lane t = hit lane of record t (0xFFFFFFFF on a miss). Keys are read 16 at a
-// time ahead of use.
-template <int SL, bool kMasked>
-__device__ __forceinline__ uint32_t mtf_batch_il(uint32_t (&sk)[SL], const uint64_t* __restrict__ rb,
-                                                 const uint64_t (&vm)[SL])
-{
-    uint32_t depth = 0xFFFFFFFFu;  // keys by scalar loads, 8 records per load (rb is uniform)
-#pragma unroll
-    for (uint32_t g = 0; g < 8; ++g) {
-        uint64_t rk[8];
-#pragma unroll
-        for (uint32_t t = 0; t < 8; ++t) rk[t] = rb[8u * g + t];
-#pragma unroll
-        for (uint32_t t = 0; t < 8; ++t)
-            depth = wrlane(depth, mtf_step_il<SL, kMasked>(sk, (uint32_t)rk[t], vm), 8u * g + t);
-    }
-    return depth;
-}
-
-// Two-level list, back operation for an access that missed the front: kk is the accessed
-// key and ins the key the front pushed out (its old position 63). If kk is in the back, the
-// back positions before it move back by one; otherwise every back position does, dropping
-// the least recent key of a full list. ins takes back position 0. The interleaved move-to-
-// front of mtf_step_il over registers 1..SL-1, inserting ins instead of kk. Returns the hit
-// mask of kk over the back (0 when kk was not there).
-template <int SL, bool kMasked>
-__device__ __forceinline__ uint64_t back_step(uint32_t (&sk)[SL], uint32_t kk, uint32_t ins, const uint64_t (&vm)[SL])
-{
-    uint64_t mh[SL];
-    uint64_t m = 0;
-#pragma unroll
-    for (int s = 1; s < SL; ++s) {
-        mh[s] = ballot(sk[s] == kk);
-        if (kMasked) mh[s] &= vm[s];
-        m |= mh[s];
-    }
-    if constexpr (SL == 2) {
-        mtf_core(sk[1], m);
-        sk[1] = wrlane(sk[1], ins, 0u);
-    } else {
-        uint64_t keep;
-        uint32_t l;
-        const uint32_t r1 = il_core(sk[1], sk[SL - 1], m, keep, l);
-        uint64_t before[SL];  // hit bits of back registers before s
-        before[1] = 0;
-#pragma unroll
-        for (int s = 2; s < SL; ++s) before[s] = before[s - 1] | mh[s - 1];
-#pragma unroll
-        for (int s = SL - 1; s >= 2; --s)
-            sk[s] = __builtin_amdgcn_inverse_ballot_w64(keep | before[s]) ? sk[s] : sk[s - 1];
-        sk[1] = wrlane(r1, ins, 0u);
-    }
-    return m;
-}
-
-// Two-level list, 64 records (all valid). Every access changes the front alone until it
-// misses there, and the back changes only on those misses (its operation takes the key and
-// the key the front pushed out of position 63). Each record's front access is branch-free;
-// a front miss runs its back operation first, behind a branch the whole wavefront takes
-// together, so nothing is logged per record. The keys come by scalar loads, 8 records
-// per load, and the 8 records of a load are unrolled with one copy of the back operation
-// each. Each front miss writes its lane of a vector register with whether the back held the
-// key (one writelane). Returns lane t = 1 if record t hit (front or back).
-template <int SL, bool kMasked>
-__device__ __forceinline__ uint32_t mtf_batch_two(uint32_t (&sk)[SL], const uint64_t* __restrict__ rb,
-                                                  const uint64_t (&vm)[SL], uint32_t lane)
-{
-    uint32_t missed = 0;  // lane t: 1 if record t was in neither part of the list
-#pragma unroll 1
-    for (uint32_t g = 0; g < 8; ++g) {
-        uint64_t rk[8];
-#pragma unroll
-        for (uint32_t t = 0; t < 8; ++t) rk[t] = rb[8u * g + t];
-#pragma unroll
-        for (uint32_t t = 0; t < 8; ++t) {
-            const uint32_t key = (uint32_t)rk[t];
-            const uint64_t m = ballot(sk[0] == key);
-            if (m == 0) {  // the back operation first, while front position 63 still holds the key it pushes out
-                const uint64_t mb = back_step<SL, kMasked>(sk, key, rdlane(sk[0], 63u), vm);
-                uint32_t miss;  // 1 when the back did not hold the key either, chosen by the scalar unit
-                asm("s_cmp_eq_u64 %1, 0\n\ts_cselect_b32 %0, 1, 0" : "=s"(miss) : "s"(mb) : "scc");
-                missed = wrlane(missed, miss, 8u * g + t);
-            }
-            mtf_core_v(sk[0], m, lane);  // with m = 0 every front position moves
-            sk[0] = wrlane(sk[0], key, 0u);
-        }
-    }
-    return missed ^ 1u;
 }
 
 // 64 records (lane t of kl = key of record t, all valid) through the move-to-front list;
@@ -1012,10 +808,59 @@ __device__ __forceinline__ uint32_t mtf_batch(uint32_t& sk, const uint64_t* __re
 
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
 {
+    if (ballot((v >> 26) != 0ull) == 0ull) return rdlane(wave_incl_scan_u32((uint32_t)v), 63u);  // the sum fits 32 bits
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += (uint64_t)__shfl_xor((unsigned long long)v, o, 64);
     return v;
 }
+
+// Statistics of one stream: per-lane sums for the current interval, flushed (one atomic per
+// statistic) when the interval changes and at the end of a range.
+struct StreamStats {
+    uint64_t* __restrict__ stats;
+    uint32_t P, R, J, c, d, lane;
+    uint32_t cur = 0xFFFFFFFFu;
+    uint32_t n_req = 0, n_hit = 0;  // uniform: a wavefront replays fewer than 2^32 records
+    uint64_t a_pre = 0, a_hp = 0;
+
+    __device__ __forceinline__ void flush()
+    {
+        if (cur >= J) return;
+        const uint64_t r2 = wave_sum_u64(a_pre), r3 = wave_sum_u64(a_hp);
+        if (lane == 0) {
+            unsigned long long* st = (unsigned long long*)(stats + (((uint64_t)cur * P + c) * R + d) * 4u);
+            atomicAdd(st + 0, (unsigned long long)n_req);
+            if (n_hit) atomicAdd(st + 1, (unsigned long long)n_hit);
+            atomicAdd(st + 2, (unsigned long long)r2);
+            if (r3) atomicAdd(st + 3, (unsigned long long)r3);
+        }
+        n_req = n_hit = 0;
+        a_pre = a_hp = 0;
+    }
+
+    // The records of the lanes of vm: record word, the lanes that hit, the keys' prefix lengths.
+    __device__ __forceinline__ void add(uint64_t rv, uint64_t vm, uint64_t hm, uint32_t pl)
+    {
+        const uint32_t sfx = (uint32_t)(rv >> 32) & 0xFFFFu;
+        const uint32_t ivl = (uint32_t)(rv >> 48);
+        const bool hl = __builtin_amdgcn_inverse_ballot_w64(hm);
+        while (vm) {
+            const uint32_t iv = rdlane(ivl, first_lane(vm));
+            if (iv != cur) {
+                flush();
+                cur = iv;
+            }
+            const uint64_t sel = vm & ballot(ivl == iv);
+            n_req += (uint32_t)__popcll(sel);
+            n_hit += (uint32_t)__popcll(sel & hm);
+            if (__builtin_amdgcn_inverse_ballot_w64(sel)) {
+                a_pre += (uint64_t)sfx + (hl ? 0u : pl);
+                a_hp += hl ? pl : 0u;
+            }
+            vm &= ~sel;
+        }
+    }
+};
 
 // One work item per segment (kSeq false), or per run of consecutive segments whose
 // rebuild ran out of budget (kSeq true).
@@ -1047,10 +892,8 @@ __device__ __forceinline__ bool item_marked(const uint32_t* __restrict__ aborted
     return (aborted[it >> 5] >> (it & 31u)) & 1u;
 }
 
-// At most 96 scalar registers, so that eight wavefronts fit on a SIMD (the W = 512 list took
-// 104 and seven); the one- and two-register lists spill three of theirs to vector-register
-// lanes. The sweep's replay measured 117.6 -> 116.2 ms alone with the cap.
-template <int SL, bool kTwo, bool kSeq>
+// At most 96 scalar registers, so that eight wavefronts fit on a SIMD.
+template <bool kSeq>
 __global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))) void k_replay(
     const uint64_t* __restrict__ rec, uint64_t n, const uint32_t* __restrict__ grp_off,
     const uint32_t* __restrict__ item_off, uint32_t P, uint32_t R, uint32_t K, uint32_t J,
@@ -1095,7 +938,7 @@ __global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))
     if (kSeq && (item == item_off[lo] || item_marked(aborted, item - 1))) return;
     const uint32_t d = lo - c * R;
     const uint32_t W = wa.W[c];
-    if (slot_class(W) != (uint32_t)SL) return;
+    if (W >= kHashFrom) return;
     if (!kSeq && wa.grp[c] > 1u) return;  // k_replay_grp's segments (its marked ones come here in kSeq)
     const uint32_t* go = grp_off + (uint64_t)c * (R + 1u);
     const uint32_t gs = go[d], cnt = go[d + 1] - gs;
@@ -1115,18 +958,8 @@ __global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))
 
     // Slot q of the rebuilt state is the q-th most recent key, which is already the
     // move-to-front order.
-    uint32_t skey[SL];
-    uint64_t vm[SL];  // lanes of register s whose position is < W
-#pragma unroll
-    for (int s = 0; s < SL; ++s) {
-        skey[s] = CR_EMPTY_SLOT;
-        uint32_t nl;  // lanes l with list_pos(s, l) < W
-        if (kTwo && s == 0) nl = W < 64u ? W : 64u;
-        else if (kTwo) nl = W > 63u + (uint32_t)s ? (W - 63u - (uint32_t)s + SL - 2u) / (uint32_t)(SL - 1) : 0u;
-        else nl = W > (uint32_t)s ? (W - (uint32_t)s + SL - 1u) / (uint32_t)SL : 0u;
-        vm[s] = nl >= 64u ? ~0ull : (1ull << nl) - 1ull;
-    }
-    const uint64_t wmask = vm[0];
+    uint32_t skey = CR_EMPTY_SLOT;
+    const uint64_t wmask = W >= 64u ? ~0ull : (1ull << W) - 1ull;  // lanes whose position is < W
     uint32_t q = 0;
     {
         // State before record s0: the most recent W distinct keys, newest first. Records
@@ -1148,14 +981,14 @@ __global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))
             nb = pos < 64u ? pos : 64u;
             kl_next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
             if (cnb == 64u && ballot(kl < K) == ~0ull) {
-                q = rebuild_batch<SL, kTwo>(skey, rl + pos, q, W, lane);
+                q = rebuild_batch(skey, rl + pos, q, W, lane);
                 continue;
             }
             for (int t = (int)cnb - 1; t >= 0 && q < W; --t) {
                 const uint32_t kk = rdlane(kl, (uint32_t)t);
                 if (kk >= K) continue;
-                if (!lru_contains<SL>(skey, kk)) {
-                    lru_put_slot<SL, kTwo>(skey, q, kk, lane);
+                if (ballot(skey == kk) == 0) {
+                    skey = wrlane(skey, kk, q);
                     ++q;
                 }
             }
@@ -1174,36 +1007,18 @@ __global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))
                     break;
                 }
                 if (kk >= K) continue;
-                if (!lru_contains<SL>(skey, kk)) {
-                    lru_put_slot<SL, kTwo>(skey, q, kk, lane);
+                if (ballot(skey == kk) == 0) {
+                    skey = wrlane(skey, kk, q);
                     ++q;
                 }
             }
         }
     }
 
-    if constexpr (SL == 1) {
-        if (q < W) skey[0] = lane >= q ? CR_EMPTY_SLOT : skey[0];  // drop what the rebuild left past q
-    }
+    if (q < W) skey = lane >= q ? CR_EMPTY_SLOT : skey;  // drop what the rebuild left past q
 
-    // Per-lane sums for the current interval; flushed (one atomic per statistic) when the
-    // interval changes and at the end of a range.
-    uint64_t a_req = 0, a_hit = 0, a_pre = 0, a_hp = 0;
-    uint32_t cur = 0xFFFFFFFFu;
+    StreamStats st{stats, P, R, J, c, d, lane};
     bool bad = false;
-    auto flush = [&]() {
-        if (cur >= J) return;
-        const uint64_t r0 = wave_sum_u64(a_req), r1 = wave_sum_u64(a_hit), r2 = wave_sum_u64(a_pre),
-                       r3 = wave_sum_u64(a_hp);
-        if (lane == 0) {
-            unsigned long long* st = (unsigned long long*)(stats + (((uint64_t)cur * P + c) * R + d) * 4u);
-            atomicAdd(st + 0, (unsigned long long)r0);
-            if (r1) atomicAdd(st + 1, (unsigned long long)r1);
-            atomicAdd(st + 2, (unsigned long long)r2);
-            if (r3) atomicAdd(st + 3, (unsigned long long)r3);
-        }
-        a_req = a_hit = a_pre = a_hp = 0;
-    };
     // Forward replay of records [r0, r1); the next batch of records is in flight while one
     // is replayed. With `on` false the list advances but nothing is counted.
     auto run = [&](uint32_t r0, uint32_t r1, bool on) {
@@ -1216,82 +1031,421 @@ __global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))
             const bool vl = lane < nb && kl < K;
             bad |= lane < nb && kl >= K;
             const uint32_t pl = vl && on ? prefix_len[kl] : 0u;  // consumed after the batch
-            bool hl;
-            if constexpr (SL == 1) {
-                uint32_t depth = 0xFFFFFFFFu;  // lane t: hit depth of record t
-                if (ballot(vl) == ~0ull) {
-                    depth = W == 64u ? mtf_batch<false>(skey[0], rl + b0, wmask)
-                                     : mtf_batch<true>(skey[0], rl + b0, wmask);
-                } else {
-                    for (uint32_t t = 0; t < nb; ++t) {
-                        const uint32_t kk = rdlane(kl, t);
-                        if (kk < K) depth = wrlane(depth, mtf_step(skey[0], kk, wmask), t);
-                    }
-                }
-                hl = depth != 0xFFFFFFFFu;
-            } else if constexpr (kTwo) {
-                uint32_t hit = 0;  // lane t: 1 if record t hit
-                if (ballot(vl) == ~0ull) {
-                    hit = W == 64u * SL ? mtf_batch_two<SL, false>(skey, rl + b0, vm, lane)
-                                        : mtf_batch_two<SL, true>(skey, rl + b0, vm, lane);
-                } else {
-                    for (uint32_t t = 0; t < nb; ++t) {
-                        const uint32_t kk = rdlane(kl, t);
-                        if (kk >= K) continue;
-                        const uint64_t m = ballot(skey[0] == kk);
-                        const uint32_t ev = rdlane(skey[0], 63u);
-                        mtf_core(skey[0], m);
-                        skey[0] = wrlane(skey[0], kk, 0u);
-                        if (m || back_step<SL, true>(skey, kk, ev, vm) != 0) hit = wrlane(hit, 1u, t);
-                    }
-                }
-                hl = hit != 0u;
+            uint32_t depth = 0xFFFFFFFFu;  // lane t: hit depth of record t
+            if (ballot(vl) == ~0ull) {
+                depth = W == 64u ? mtf_batch<false>(skey, rl + b0, wmask) : mtf_batch<true>(skey, rl + b0, wmask);
             } else {
-                uint32_t depth = 0xFFFFFFFFu;  // lane t: hit lane of record t
-                if (ballot(vl) == ~0ull) {
-                    depth = W == 64u * SL ? mtf_batch_il<SL, false>(skey, rl + b0, vm)
-                                          : mtf_batch_il<SL, true>(skey, rl + b0, vm);
-                } else {
-                    for (uint32_t t = 0; t < nb; ++t) {
-                        const uint32_t kk = rdlane(kl, t);
-                        if (kk < K) depth = wrlane(depth, mtf_step_il<SL, true>(skey, kk, vm), t);
-                    }
+                for (uint32_t t = 0; t < nb; ++t) {
+                    const uint32_t kk = rdlane(kl, t);
+                    if (kk < K) depth = wrlane(depth, mtf_step(skey, kk, wmask), t);
                 }
-                hl = depth != 0xFFFFFFFFu;
             }
-            if (!on) continue;
-            const uint32_t sfx = (uint32_t)(rv >> 32) & 0xFFFFu;
-            const uint32_t ivl = (uint32_t)(rv >> 48);
-            uint64_t rem = ballot(vl);
-            while (rem) {
-                const uint32_t iv = rdlane(ivl, first_lane(rem));
-                if (iv != cur) {
-                    flush();
-                    cur = iv;
-                }
-                const uint64_t sel = rem & ballot(ivl == iv);
-                if ((sel >> lane) & 1ull) {
-                    a_req += 1;
-                    a_hit += hl ? 1u : 0u;
-                    a_pre += sfx + (hl ? 0u : pl);
-                    a_hp += hl ? pl : 0u;
-                }
-                rem &= ~sel;
-            }
+            if (on) st.add(rv, ballot(vl), ballot(depth != 0xFFFFFFFFu), pl);
         }
-        flush();
+        st.flush();
     };
     if (sc > s0) run(s0, sc < s1 ? sc : s1, false);
     run(sc, s1, true);
     if (ballot(bad) && lane == 0) atomicOr(err, CR_ERR_KEY_RANGE);
     if (s1 == cnt) {
         uint32_t* __restrict__ lo_ = lru_out + ((uint64_t)c * R + d) * max_W;
-#pragma unroll
-        for (int s = 0; s < SL; ++s) {
-            const uint32_t idx = list_pos<SL, kTwo>((uint32_t)s, lane);
-            if (idx < W) lo_[idx] = skey[s];
-        }
+        if (lane < W) lo_[lane] = skey;
         for (uint32_t idx = W + lane; idx < max_W; idx += 64) lo_[idx] = CR_EMPTY_SLOT;
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// Lists of 64 slots and more: 64 records per step instead of one. A wavefront keeps the
+// segment's cache as a hash table in LDS, {key, position of its last access}, where newer
+// accesses have smaller positions, and a bitmap over the positions that marks the last access
+// of every cached key. The cache is the table's entries at positions up to T, T being the
+// position of the W-th most recent key; a key's depth in the list is the number of bits below
+// its position. A step takes 64 records, one per lane:
+//   - every lane finds its key in the table or claims a slot for it;
+//   - with W >= 64, a key seen earlier in the step is always a hit (at most 62 other keys lie
+//     between). A key seen here first is a hit iff it was cached and was not pushed out earlier
+//     in the step: at depth d it is still there after c other keys iff d + c < W, where only
+//     the keys that were behind it (deeper or not cached) count, each once. Only lanes with
+//     d + 63 >= W can fail that; those that the counts of all such keys before them do not
+//     decide are counted exactly, one ballot each;
+//   - the step's last access of every key becomes its position, the old position's bit is
+//     cleared, and T moves to the W-th bit.
+// The cost of a step hardly depends on W, where a list in registers paid a compare and a move
+// per 64 slots for every record. Measured (the cr_replay_lru call, 4e7 requests x 8 candidates
+// over 1,024 streams; list in registers before): W = 64 3.83 -> 2.46 ms, 86 6.64 -> 2.48,
+// 156 7.64 -> 2.72, 283 10.5 -> 3.10, 512 14.3 -> 3.86. Bound by instruction issue up to W of
+// about 200, and by the latency of the dependent LDS round trips where the tables leave few
+// wavefronts per CU.
+// Entries past T stay in the table (their keys may come back to the same slot); when the
+// table or the 64 bitmap words run full, the live entries are re-inserted into an empty table
+// at positions that leave the words before them free (refresh).
+template <int NS, int kMaxW>
+struct HashLds {
+    uint4 tab[NS / 2];            // buckets of two {key, position}
+    unsigned long long bm[64];    // word b: positions 64 b .. 64 b + 63
+    uint32_t list[kMaxW];         // keys or entries by depth, for refresh and rebuild
+};
+
+constexpr uint32_t kNoPos = 4096u;     // position of an entry that is not cached
+constexpr uint32_t kMarkPos = 8192u;   // above it: marks of the lanes of one step
+
+// Compiler-level ordering of one wavefront's LDS accesses (the hardware keeps them in order).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ uint32_t bperm(uint32_t src_lane, uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src_lane << 2), (int)v);
+}
+
+__device__ __forceinline__ uint32_t mbcnt64(uint64_t m)  // set bits of m below this lane
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+__device__ __forceinline__ void clear_bit(uint64_t& m, uint32_t t) { asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(t)); }
+
+// One wavefront's cache. Masks of lanes and all members but w, pex and inc are uniform.
+template <int NS, int kMaxW>
+struct HashCache {
+    static_assert(NS % 128 == 0 && kMaxW + 128 <= NS * 7 / 8, "whole LDS rounds; room for two steps of claims past a full cache");
+    HashLds<NS, kMaxW>& lds;
+    uint32_t W, lane;
+    uint32_t used = 0;        // claimed slots
+    uint32_t live = 0;        // cached keys
+    int32_t beta = 63;        // bitmap word of the next step (below every word in use)
+    uint32_t T = kNoPos - 1;  // entries at positions past T are not cached
+    uint64_t w = 0;           // lane b: bitmap word b
+    uint32_t pex = 0;         // lane b: live positions in the words before b
+    uint32_t inc = 0;         // lane b: the same with word b
+
+    __device__ __forceinline__ HashCache(HashLds<NS, kMaxW>& l, uint32_t W_, uint32_t lane_) : lds(l), W(W_), lane(lane_) {}
+
+    // The 32-bit word at byte address a of the table (an entry's key; its position is at a + 4).
+    __device__ __forceinline__ uint32_t* at(uint32_t a)
+    {
+        return reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lds.tab) + a);
+    }
+
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll 4
+        for (uint32_t i = 0; i < NS / 2u; i += 64u) lds.tab[i + lane] = make_uint4(CR_EMPTY_SLOT, kNoPos, CR_EMPTY_SLOT, kNoPos);
+        used = 0;
+        wave_lds_fence();
+    }
+
+    // Byte address of the entry of every lane's key (lanes of am), claimed if the table does
+    // not hold it; `pos` = the entry's position (kNoPos when claimed here). Entries are
+    // claimed in probe order, so a lookup ends at the key or at a bucket with its second slot
+    // empty. The lanes of one key take the same path, so a key never gets two entries; the
+    // table always has an empty slot, so every probe ends.
+    __device__ __forceinline__ uint32_t find(uint32_t key, uint64_t am, uint32_t& pos)
+    {
+        uint32_t a = __umulhi(key * 0x9E3779B1u, NS / 2u) * 16u;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        uint64_t todo = am;
+        while (todo) {  // a lane's v and a stay as they are once it is done
+            if (lane_in(todo)) v = *reinterpret_cast<const uint4*>(at(a));
+            todo = ballot(v.x != key) & ballot(v.z != key) & ballot(v.z != CR_EMPTY_SLOT) & am;
+            const uint32_t next = a + 16u;
+            a = lane_in(todo) ? (next < NS * 8u ? next : 0u) : a;
+        }
+        const bool h0 = v.x == key, h1 = v.z == key;
+        pos = h0 ? v.y : (h1 ? v.w : kNoPos);
+        a += h0 || (!h1 && v.x == CR_EMPTY_SLOT) ? 0u : 8u;
+        todo = am & ~(ballot(h0) | ballot(h1));
+        uint32_t claimed = 0, prev = 0;
+        while (todo) {
+            if (lane_in(todo)) prev = atomicCAS(at(a), CR_EMPTY_SLOT, key);
+            const uint64_t won = ballot(prev == CR_EMPTY_SLOT) & todo;
+            claimed += (uint32_t)__popcll(won);
+            todo = todo & ~won & ballot(prev != key);  // another key took it: the next slot
+            const uint32_t next = a + 8u;
+            a = lane_in(todo) ? (next < NS * 8u ? next : 0u) : a;
+        }
+        used += claimed;
+        wave_lds_fence();
+        return a;
+    }
+
+    // Depth in the list of a cached key at position `p`.
+    __device__ __forceinline__ uint32_t depth_of(uint32_t p) const
+    {
+        const uint32_t wd = (p >> 6) & 63u;
+        const uint32_t lo = bperm(wd, (uint32_t)w), hi = bperm(wd, (uint32_t)(w >> 32));
+        return bperm(wd, pex) + (uint32_t)__popcll((((uint64_t)hi << 32) | lo) & ~(~0ull << (p & 63u)));
+    }
+
+    // Visits every cached key as f(key, depth).
+    template <typename F>
+    __device__ __forceinline__ void each_live(F f)
+    {
+        for (uint32_t i = 0; i < (uint32_t)NS; i += 64u) {
+            const uint2 e = *reinterpret_cast<const uint2*>(at(8u * (i + lane)));
+            const uint32_t d = depth_of(e.y);
+            if (e.y <= T) f(e.x, d);
+        }
+    }
+
+    // The cache made of the n entries whose byte addresses lds.list holds, list[i] at depth i.
+    __device__ __forceinline__ void place(uint32_t n)
+    {
+        const uint32_t w0 = 64u - ((n + 63u) >> 6);  // first bitmap word in use
+        for (uint32_t i = lane; i < n; i += 64u) at(lds.list[i])[1] = 64u * w0 + i;
+        live = n;
+        T = kNoPos - 1u;
+        beta = (int32_t)w0 - 1;
+        const uint32_t b = lane >= w0 ? 64u * (lane - w0) : n;  // positions before this lane's word
+        const uint32_t c = n - b < 64u ? n - b : 64u;
+        w = lane < w0 || c == 0u ? 0ull : (c == 64u ? ~0ull : (1ull << c) - 1ull);
+        pex = lane >= w0 ? b : 0u;
+        inc = lane >= w0 ? b + c : 0u;
+        lds.bm[lane] = w;
+        wave_lds_fence();
+    }
+
+    __device__ __forceinline__ void refresh()
+    {
+        each_live([&](uint32_t key, uint32_t d) { lds.list[d] = key; });
+        wave_lds_fence();
+        clear();
+        for (uint32_t i0 = 0; i0 < live; i0 += 64u) {
+            const uint32_t i = i0 + lane;
+            const bool in = i < live;
+            uint32_t pos;
+            const uint32_t a = find(in ? lds.list[i] : 0u, ballot(in), pos);
+            if (in) lds.list[i] = a;
+            wave_lds_fence();
+        }
+        place(live);
+    }
+
+    // One step: 64 records in lane order, key kk on the lanes of am. Returns the lanes that hit.
+    __device__ __forceinline__ uint64_t step(uint32_t kk, uint64_t am)
+    {
+        if (beta < 0 || used + 64u > (uint32_t)NS * 7u / 8u) refresh();
+        uint32_t old;
+        uint32_t* __restrict__ e = at(find(kk, am, old)) + 1;
+        const bool act = lane_in(am);
+        // the step's first and last record of every key
+        const uint32_t c0 = kMarkPos + 63u - lane, c1 = 64u * (uint32_t)beta + 63u - lane;
+        if (act) atomicMax(e, c0);
+        wave_lds_fence();
+        const uint64_t fm = ballot(*e == c0) & am;
+        wave_lds_fence();
+        uint64_t lm = fm;
+        if (fm == am) {  // no key twice
+            if (act) *e = c1;
+        } else {
+            if (act) atomicMin(e, c1);
+            wave_lds_fence();
+            lm = ballot(*e == c1) & am;
+        }
+        wave_lds_fence();
+        // hits; the lanes that may have been pushed out in this step are counted
+        const uint64_t pm = ballot(old <= T) & am;  // cached before the step
+        uint64_t hits = am & ~(fm & ~pm);
+        const uint32_t nw = (uint32_t)__popcll(ballot(inc + 63u <= W));  // words wholly at depths below W - 63
+        const uint64_t near = fm & ballot(old >= 64u * nw) & pm;
+        if (near) {
+            const uint64_t absent = fm & ~pm;
+            const uint32_t d = depth_of(old);
+            const uint64_t out = ballot(d + mbcnt64(absent) >= W) & near;
+            uint64_t open = ballot(d + mbcnt64(absent | near) >= W) & near & ~out;
+            hits &= ~out;
+            const uint32_t key = lane_in(pm) ? old : kNoPos;  // absent keys are behind every cached one
+            while (open) {
+                const uint32_t t = first_lane(open);
+                const uint64_t ahead = ballot(key > rdlane(old, t)) & fm & ~(~0ull << t);
+                if (rdlane(d, t) + (uint32_t)__popcll(ahead) >= W) clear_bit(hits, t);
+                clear_bit(open, t);
+            }
+        }
+        // positions: the old ones out, the step's own in
+        if (lane_in(lm & pm)) atomicXor(reinterpret_cast<uint32_t*>(lds.bm) + (old >> 5), 1u << (old & 31u));
+        wave_lds_fence();
+        w = lds.bm[lane];
+        const uint64_t own = __builtin_bitreverse64(lm);
+        w = (uint64_t)wrlane((uint32_t)w, (uint32_t)own, (uint32_t)beta) |
+            ((uint64_t)wrlane((uint32_t)(w >> 32), (uint32_t)(own >> 32), (uint32_t)beta) << 32);
+        const uint32_t c = (uint32_t)__popcll(w);
+        inc = wave_incl_scan_u32(c);
+        pex = inc - c;
+        live = rdlane(inc, 63);
+        --beta;
+        if (live > W) {  // push out what is past the W-th
+            const uint32_t wl = (uint32_t)__popcll(ballot(inc < W));  // word of the W-th
+            const uint64_t ww = rdlane64(w, wl);
+            const uint32_t b = first_lane(ww & ballot(mbcnt64(ww) + rdlane(pex, wl) == W - 1u));
+            T = 64u * wl + b;
+            const uint64_t keep = ~(~0ull << b << 1);
+            w = lane > wl ? 0ull : (lane == wl ? w & keep : w);
+            inc = inc < W ? inc : W;
+            live = W;
+        }
+        lds.bm[lane] = w;
+        wave_lds_fence();
+        return hits;
+    }
+
+    // Rebuild: the next older records (the lanes' order is the stream's). The entries of keys
+    // not met yet are appended to lds.list, newest first; q counts them (those past W, which
+    // only the last rebuild step can meet, stay in the table as not cached).
+    __device__ __forceinline__ uint32_t rebuild_step(uint32_t kk, uint64_t am, uint32_t q)
+    {
+        uint32_t pos;
+        const uint32_t a = find(kk, am, pos);
+        uint32_t* __restrict__ e = at(a) + 1;
+        const uint64_t fresh = ballot(pos == kNoPos) & am;
+        if (lane_in(fresh)) atomicMax(e, kMarkPos + lane);
+        wave_lds_fence();
+        const uint64_t rep = ballot(*e == kMarkPos + lane) & fresh;  // its newest record here
+        wave_lds_fence();
+        const uint32_t total = (uint32_t)__popcll(rep);
+        const uint32_t i = q + total - 1u - mbcnt64(rep);
+        if (lane_in(rep)) {
+            *e = i < W ? 0u : kNoPos;
+            if (i < W) lds.list[i] = a;
+        }
+        wave_lds_fence();
+        return q + total;
+    }
+};
+
+template <int NS, int kMaxW, bool kSeq>
+__global__ __launch_bounds__(64) void k_replay_hash(
+    const uint64_t* __restrict__ rec, uint64_t n, const uint32_t* __restrict__ grp_off,
+    const uint32_t* __restrict__ item_off, uint32_t P, uint32_t R, uint32_t K, uint32_t J,
+    const uint32_t* __restrict__ prefix_len, WArg wa, CandMap cm, uint32_t max_W,
+    const uint32_t* __restrict__ lru_in, uint32_t* __restrict__ lru_out, uint64_t* __restrict__ stats,
+    uint32_t* __restrict__ aborted, uint32_t* __restrict__ err)
+{
+    __shared__ HashLds<NS, kMaxW> lds;
+    const uint32_t lane = lane_id();
+    const uint32_t v = blockIdx.x;
+    uint64_t item;
+    uint32_t lo, hi;  // the item's stream is searched for in [lo, hi)
+    if (cm.n == 0) {  // every candidate of the call: wavefront v takes work item v
+        item = v;
+        if (item >= item_off[P * R]) return;
+        lo = 0;
+        hi = P * R;
+    } else {
+        if (v >= cm.wv0[cm.n]) return;
+        uint32_t ci = 0;  // the last i with wv0[i] <= v
+        {
+            uint32_t h = cm.n;
+            while (h - ci > 1) {
+                const uint32_t mid = (ci + h) >> 1;
+                if (cm.wv0[mid] <= v) ci = mid;
+                else h = mid;
+            }
+        }
+        const uint32_t cc = cm.cand[ci];
+        item = (uint64_t)item_off[cc * R] + (v - cm.wv0[ci]);
+        if (item >= item_off[(cc + 1) * R]) return;
+        lo = cc * R;
+        hi = (cc + 1) * R;
+    }
+    if (kSeq && !item_marked(aborted, item)) return;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (item_off[mid] <= item) lo = mid;
+        else hi = mid;
+    }
+    const uint32_t c = lo / R;
+    // kSeq: only the first marked segment of a run, which is never a stream's first item
+    if (kSeq && (item == item_off[lo] || item_marked(aborted, item - 1))) return;
+    const uint32_t d = lo - c * R;
+    const uint32_t W = wa.W[c];
+    if (W < kHashFrom || W > (uint32_t)kMaxW) return;
+    static_assert(kHashFrom >= 64u, "a key repeated within 64 records is always a hit");
+    const uint32_t* go = grp_off + (uint64_t)c * (R + 1u);
+    const uint32_t gs = go[d], cnt = go[d + 1] - gs;
+    const uint32_t S = seg_len(W, wa.seg_min, 1u);
+    const uint32_t nseg = item_off[lo + 1] - item_off[lo];
+    // [s0, s1): the records this wavefront replays; [s0, sc) of them are replayed only to
+    // reach the state at sc (the run's predecessor in the kSeq pass)
+    uint64_t i0 = item, i1 = item + 1;
+    if (kSeq) {
+        i0 = item - 1;
+        while (i1 < item_off[lo + 1] && item_marked(aborted, i1)) ++i1;
+    }
+    const uint32_t s0 = seg_start((uint32_t)(i0 - item_off[lo]), nseg, cnt);
+    const uint32_t sc = kSeq ? seg_start((uint32_t)(item - item_off[lo]), nseg, cnt) : s0;
+    const uint32_t s1 = seg_start((uint32_t)(i1 - item_off[lo]), nseg, cnt);
+    const uint64_t* __restrict__ rl = rec + (uint64_t)c * n + gs;
+
+    HashCache<NS, kMaxW> cache(lds, W, lane);
+    cache.clear();
+    uint32_t q = 0;
+    {
+        // State before record s0: the most recent W distinct keys. Records are read backwards
+        // 64 at a time, the next (older) batch in flight while one is scanned.
+        uint32_t pos = s0, scanned = 0;
+        const uint32_t budget = kRebuildBudget * S;
+        uint32_t nb = pos < 64u ? pos : 64u;
+        uint32_t kl_next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
+        while (q < W && pos > 0) {
+            if (!kSeq && scanned >= budget) {  // too few distinct keys: left to the kSeq pass
+                if (lane == 0) atomicOr(&aborted[item >> 5], 1u << (item & 31u));
+                return;
+            }
+            const uint32_t kl = kl_next;
+            pos -= nb;
+            scanned += nb;
+            nb = pos < 64u ? pos : 64u;
+            kl_next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
+            q = cache.rebuild_step(kl, ballot(kl < K), q);
+        }
+    }
+    if (q < W && lru_in) {
+        // the carried state, newest first: lane 63 takes the newest of 64 entries
+        const uint32_t* __restrict__ li = lru_in + ((uint64_t)c * R + d) * max_W;
+        for (uint32_t s = 0; s < W && q < W; s += 64) {
+            const uint32_t i = s + 63u - lane;
+            const uint32_t kk = i < W ? li[i] : CR_EMPTY_SLOT;
+            const uint64_t empty = ballot(kk == CR_EMPTY_SLOT);  // entries end at the first empty one
+            const uint64_t valid = empty ? ~0ull << (63u - (uint32_t)__builtin_clzll(empty)) : ~0ull;
+            q = cache.rebuild_step(kk, ballot(kk < K) & valid, q);
+            if (empty) break;
+        }
+    }
+    cache.place(q < W ? q : W);
+
+    StreamStats st{stats, P, R, J, c, d, lane};
+    bool bad = false;
+    // Replay of records [r0, r1); the next batch of records is in flight while one is
+    // replayed. With `on` false the cache advances but nothing is counted.
+    auto run = [&](uint32_t r0, uint32_t r1, bool on) {
+        uint64_t rv_next = r0 + lane < r1 ? rl[r0 + lane] : 0ull;
+        for (uint32_t b0 = r0; b0 < r1; b0 += 64) {
+            const uint32_t nb = r1 - b0 < 64u ? r1 - b0 : 64u;
+            const uint64_t rv = rv_next;
+            rv_next = b0 + 64u + lane < r1 ? rl[b0 + 64u + lane] : 0ull;
+            const uint32_t kl = lane < nb ? (uint32_t)rv : CR_EMPTY_SLOT;
+            const bool vl = lane < nb && kl < K;
+            bad |= lane < nb && kl >= K;
+            const uint32_t pl = vl && on ? prefix_len[kl] : 0u;  // consumed after the step
+            const uint64_t vm = ballot(vl);
+            const uint64_t hm = cache.step(kl, vm);
+            if (on) st.add(rv, vm, hm, pl);
+        }
+        st.flush();
+    };
+    if (sc > s0) run(s0, sc < s1 ? sc : s1, false);
+    run(sc, s1, true);
+    if (ballot(bad) && lane == 0) atomicOr(err, CR_ERR_KEY_RANGE);
+    if (s1 == cnt) {
+        uint32_t* __restrict__ lo_ = lru_out + ((uint64_t)c * R + d) * max_W;
+        cache.each_live([&](uint32_t key, uint32_t depth) { lo_[depth] = key; });
+        for (uint32_t idx = cache.live + lane; idx < max_W; idx += 64) lo_[idx] = CR_EMPTY_SLOT;
     }
 }
 
@@ -1315,7 +1469,7 @@ __global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))
 // the window holds W distinct keys the list is exactly the W most recent ones, so it is full
 // when it is right; otherwise D grows, up to kGrpRebuildBudget S rounded up to whole
 // 64-record batches. A segment whose window still holds fewer than W distinct keys there is
-// marked in `aborted`, and the kSeq pass of k_replay<1> replays it from its predecessor.
+// marked in `aborted`, and the kSeq pass of k_replay replays it from its predecessor.
 //
 // Statistics: a step's hit is the bit of the lane that held its key; each lane shifts its
 // bits into a register, and after a round of 64 steps the group's registers, OR-ed, give the
@@ -1600,7 +1754,7 @@ inline ReplayWs replay_layout(void* base, uint64_t n, uint32_t P, uint32_t R)
 
 struct ReplayArgs {
     WArg wa;
-    uint32_t classes;    // bit SL - 1: some candidate's list has SL registers
+    uint32_t classes;    // bit rep_class: some candidate's list is of that class
     uint32_t wclasses;   // the same, candidates replayed one list per wavefront only
     uint32_t groups;     // bit G: some candidate is replayed by k_replay_grp<G>
     uint64_t grp_waves;  // bound on k_replay_grp wavefronts
@@ -1631,8 +1785,8 @@ inline cr_status replay_args(uint64_t n, uint32_t J, uint32_t P, uint32_t R, con
         ra->wa.W[c] = (uint16_t)W[c];
         const uint32_t G = grouped ? grp_of(W[c], J) : 1u;
         ra->wa.grp[c] = (uint8_t)G;
-        ra->classes |= 1u << (slot_class(W[c]) - 1u);
-        if (G == 1u) ra->wclasses |= 1u << (slot_class(W[c]) - 1u);
+        ra->classes |= 1u << rep_class(W[c]);
+        if (G == 1u) ra->wclasses |= 1u << rep_class(W[c]);
         const uint32_t S = seg_len(W[c], ra->wa.seg_min, G);
         if (G > 1u) {  // at most R + n / S work items, G per wavefront
             ra->groups |= 1u << G;
@@ -1805,15 +1959,14 @@ extern "C" cr_status cr_replay_lru(const uint32_t* prefix_len, uint32_t num_keys
     const hipStream_t st = as_stream(stream);
     const uint64_t gblocks = (ra.grp_waves + (kReplayThreads / 64) - 1) / (kReplayThreads / 64);
     if (gblocks > 0x7FFFFFFFull) return CR_EINVAL;
-    // One k_replay launch per list size, with wavefronts for its own candidates only: a
-    // stream of cnt records has max(1, ceil(cnt / S)) work items, so a candidate has at most
-    // R + n / S of them.
+    // One launch per list class, with wavefronts for its own candidates only: a stream of cnt
+    // records has max(1, ceil(cnt / S)) work items, so a candidate has at most R + n / S of them.
     CandMap cm;
-    auto cand_map = [&](uint32_t SL, bool seq) -> uint64_t {
+    auto cand_map = [&](uint32_t cls, bool seq) -> uint64_t {
         uint64_t wv = 0;
         cm.n = 0;
         for (uint32_t c = 0; c < P; ++c) {
-            if (slot_class(W[c]) != SL || (!seq && ra.wa.grp[c] > 1u)) continue;
+            if (rep_class(W[c]) != cls || (!seq && ra.wa.grp[c] > 1u)) continue;
             cm.cand[cm.n] = (uint16_t)c;
             cm.wv0[cm.n++] = (uint32_t)wv;
             wv += (uint64_t)R + n / seg_len(W[c], ra.wa.seg_min, ra.wa.grp[c]) + 1u;
@@ -1822,20 +1975,31 @@ extern "C" cr_status cr_replay_lru(const uint32_t* prefix_len, uint32_t num_keys
         if (cm.n == P) cm.n = 0;  // every candidate, in order: work item v is wavefront v
         return wv;
     };
-    for (uint32_t SL = 1; SL <= 8; ++SL)
-        if (cand_map(SL, true) > 0x7FFFFFFFull) return CR_EINVAL;
+    for (uint32_t cls = 0; cls < kClasses; ++cls)
+        if (cand_map(cls, true) > 0x7FFFFFFFull) return CR_EINVAL;
     (void)hipGetLastError();
     hipLaunchKernelGGL(k_zero_u32, dim3(256), dim3(256), 0, st, w.aborted, w.flag_words);
-#define CR_REPLAY(SL, TWO, SEQ, NB)                                                                                 \
-    hipLaunchKernelGGL((k_replay<SL, TWO, SEQ>), dim3((uint32_t)(NB)), dim3(kReplayThreads), 0, st, w.rec, n,        \
-                       w.grp_off, w.item_off, P, R, num_keys, J, prefix_len, ra.wa, cm, max_W, lru_in, lru_out,       \
-                       stats, w.aborted, err)
-#define CR_CLASS(SL, SEQ)                                                                                           \
-    if ((SEQ ? ra.classes : ra.wclasses) & (1u << ((SL) - 1))) {                                                   \
-        const uint64_t nw = cand_map(SL, SEQ);                                                                      \
-        if (nw) CR_REPLAY(SL, (SL) >= kTwoLevelFrom, SEQ, (nw + (kReplayThreads / 64) - 1) / (kReplayThreads / 64)); \
+    auto launch_class = [&](uint32_t cls, bool seq, hipStream_t on) {
+        const uint64_t nw = cand_map(cls, seq);
+        if (!nw) return;
+        const dim3 b4((uint32_t)((nw + (kReplayThreads / 64) - 1) / (kReplayThreads / 64))), b1((uint32_t)nw);
+#define CR_REPLAY(KERNEL, BLOCKS, THREADS)                                                                          \
+    hipLaunchKernelGGL((KERNEL), BLOCKS, dim3(THREADS), 0, on, w.rec, n, w.grp_off, w.item_off, P, R, num_keys, J,   \
+                       prefix_len, ra.wa, cm, max_W, lru_in, lru_out, stats, w.aborted, err)
+#define CR_HASH(C)                                                                                                  \
+    else if (cls == (C)) {                                                                                          \
+        if (seq) CR_REPLAY((k_replay_hash<kHashSlots[C], kHashW[C], true>), b1, 64);                                 \
+        else CR_REPLAY((k_replay_hash<kHashSlots[C], kHashW[C], false>), b1, 64);                                    \
     }
-    // The list sizes' launches and the grouped ones are independent of each other (other
+        if (cls == 0) {
+            if (seq) CR_REPLAY(k_replay<true>, b4, kReplayThreads);
+            else CR_REPLAY(k_replay<false>, b4, kReplayThreads);
+        }
+        CR_HASH(1) CR_HASH(2) CR_HASH(3) CR_HASH(4)
+#undef CR_HASH
+#undef CR_REPLAY
+    };
+    // The list classes' launches and the grouped ones are independent of each other (other
     // candidates; the marked-segment bitmap takes atomic ORs); the kSeq passes read what all
     // of them marked, so they follow on the caller's stream after the join. A call under
     // stream capture keeps everything on the caller's stream.
@@ -1858,19 +2022,19 @@ extern "C" cr_status cr_replay_lru(const uint32_t* prefix_len, uint32_t num_keys
     }
     // Launches in order of their work, each onto the stream with less work so far. A
     // launch's work is its candidates times a cost per candidate and request by list form,
-    // in hundredths of the one-register list's (as measured alone on the 1e8-request sweep:
-    // 0.98, 1.96, 2.2, 2.8 and 3.75 ms per candidate for 1, 2, 3, 5 and 8 registers, 0.55 and
-    // 0.75 for the lists of 8 and 16 slots replayed 8 and 4 per wavefront).
-    static constexpr uint32_t kCost[9] = {0u, 100u, 200u, 225u, 255u, 285u, 320u, 350u, 385u};
-    struct Launch { uint32_t kind; uint64_t work; };  // kind 1..8: k_replay<kind>; 100 + G: k_replay_grp<G>
-    Launch todo[10];
+    // in hundredths of the one-register list's (as measured alone: 0.47, 0.34, 0.35, 0.39 and
+    // 0.44 ms per candidate and 4e7 requests; lists of 8 and 16 slots, replayed 8 and 4 per
+    // wavefront, 0.56 and 0.77 of the one-register list).
+    static constexpr uint32_t kCost[kClasses] = {100u, 71u, 74u, 82u, 93u};
+    struct Launch { uint32_t kind; uint64_t work; };  // kind < kClasses: that class; 100 + G: k_replay_grp<G>
+    Launch todo[kClasses + 2];
     uint32_t nt = 0;
-    for (uint32_t SL = 1; SL <= 8; ++SL)
-        if (ra.wclasses & (1u << (SL - 1))) {
+    for (uint32_t cls = 0; cls < kClasses; ++cls)
+        if (ra.wclasses & (1u << cls)) {
             uint64_t wk = 0;
             for (uint32_t c = 0; c < P; ++c)
-                if (slot_class(W[c]) == SL && ra.wa.grp[c] == 1u) wk += kCost[SL];
-            todo[nt++] = Launch{SL, wk};
+                if (rep_class(W[c]) == cls && ra.wa.grp[c] == 1u) wk += kCost[cls];
+            todo[nt++] = Launch{cls, wk};
         }
     for (uint32_t G = 4; G <= 8; G += 4)
         if (ra.groups & (1u << G)) {
@@ -1891,18 +2055,8 @@ extern "C" cr_status cr_replay_lru(const uint32_t* prefix_len, uint32_t num_keys
         load[li] += todo[t].work;
         const hipStream_t ls = lane_st[li];
         const uint32_t k = todo[t].kind;
-#define CR_ON(SL)                                                                                                  \
-        if (k == (SL)) {                                                                                          \
-            const uint64_t nw = cand_map(SL, false);                                                              \
-            if (nw)                                                                                               \
-                hipLaunchKernelGGL((k_replay<SL, (SL) >= kTwoLevelFrom, false>),                                  \
-                                   dim3((uint32_t)((nw + (kReplayThreads / 64) - 1) / (kReplayThreads / 64))),     \
-                                   dim3(kReplayThreads), 0, ls, w.rec, n, w.grp_off, w.item_off, P, R, num_keys, J, \
-                                   prefix_len, ra.wa, cm, max_W, lru_in, lru_out, stats, w.aborted, err);           \
-        }
-        CR_ON(1) CR_ON(2) CR_ON(3) CR_ON(4) CR_ON(5) CR_ON(6) CR_ON(7) CR_ON(8)
-#undef CR_ON
-        // several lists per wavefront; their marked segments join the kSeq pass of k_replay<1>
+        if (k < kClasses) launch_class(k, false, ls);
+        // several lists per wavefront; their marked segments join the kSeq pass of k_replay
 #define CR_GRP(G)                                                                                                  \
         if (k == 100u + (G))                                                                                       \
             hipLaunchKernelGGL((k_replay_grp<G>), dim3((uint32_t)gblocks), dim3(kReplayThreads), 0, ls, w.rec, n,   \
@@ -1918,10 +2072,8 @@ extern "C" cr_status cr_replay_lru(const uint32_t* prefix_len, uint32_t num_keys
                 return CR_EHIP;
         side_lock.unlock();
     }
-    CR_CLASS(1, true); CR_CLASS(2, true); CR_CLASS(3, true); CR_CLASS(4, true);
-    CR_CLASS(5, true); CR_CLASS(6, true); CR_CLASS(7, true); CR_CLASS(8, true);
-#undef CR_CLASS
-#undef CR_REPLAY
+    for (uint32_t cls = 0; cls < kClasses; ++cls)
+        if (ra.classes & (1u << cls)) launch_class(cls, true, st);
     return hipGetLastError() == hipSuccess ? CR_OK : CR_EHIP;
 }
 
