@@ -8,7 +8,7 @@
 //        arrival order; each record packs (key, suffix, interval) into 8 bytes;
 //        k_seg_items also splits every (candidate, destination) stream into segments of
 //        S records;
-//   k_replay, k_replay_hash
+//   k_replay
 //        one wavefront per segment. The LRU state before a segment is exactly the most
 //        recent W distinct keys seen at that destination (carried state appended), so a
 //        wavefront rebuilds it by scanning backwards, then replays its segment. This
@@ -35,10 +35,11 @@ struct WArg {
     uint16_t W[CR_MAX_CANDS];
     uint8_t grp[CR_MAX_CANDS];  // lists per wavefront: G > 1 for k_replay_grp<G>, else 1
     uint32_t seg_min;  // shortest segment for this call's record count
+    uint32_t seg_per;  // records per segment and cache slot, at least
 };
 
-// The candidates one k_replay or k_replay_hash launch serves and the first wavefront of each: wavefront v
-// takes work item v - wv0[i] of candidate cand[i] for wv0[i] <= v < wv0[i + 1]. Each
+// The candidates one k_replay launch serves and the first wavefront of each: wavefront v takes
+// work item v - wv0[i] of candidate cand[i] for wv0[i] <= v < wv0[i + 1]. Each
 // candidate gets as many wavefronts as it can have work items (one per stream plus one per
 // full segment), so a launch runs no wavefront for another list size's candidates. n = 0
 // when the launch serves every candidate of the call: wavefront v then takes work item v.
@@ -67,19 +68,28 @@ __host__ __device__ __forceinline__ uint32_t seg_start(uint32_t i, uint32_t nseg
 // longer segments only save the backward rebuild of the initial state.
 constexpr uint64_t kSegTarget = 16384;
 
-// Shortest segment; the launch sizes its grid for segments of this length.
+// Shortest segments. A call with enough records to fill the chip (kSegFull) cuts nothing
+// shorter than kSegFloor records or kSegPerSlot W, so that the rebuild of the initial state
+// stays a small part. Smaller calls leave most of the chip idle, and their time is the chain
+// of one segment, so they are cut down to kSegShort records or kSegPerSlotShort W, between
+// the two in proportion, which keeps about 4,096 wavefronts. One list of 48 slots over 64
+// streams: 1e6 requests 61 -> 49 us with segments of 256 instead of 1,024; 4e6 requests 86 us
+// with 1,024 and 98 us with 488.
+constexpr uint64_t kSegFull = 4u << 20;
 constexpr uint32_t kSegFloor = 1024;
+constexpr uint32_t kSegShort = 256;
 constexpr uint32_t kSegPerSlot = 16;
+constexpr uint32_t kSegPerSlotShort = 4;
 
-// Records per segment: at least kSegPerSlot W (the rebuild scans back to W distinct keys)
-// and at least the share that keeps the number of segments near kSegTarget. A candidate
+// Records per segment: at least the call's shortest, seg_per W (the rebuild scans back to W
+// distinct keys) and the share that keeps the number of segments near kSegTarget. A candidate
 // whose wavefronts hold G lists (k_replay_grp) takes segments G times shorter, so that it
 // still has as many wavefronts.
-__host__ __device__ __forceinline__ uint32_t seg_len(uint32_t W, uint32_t seg_min, uint32_t G)
+__host__ __device__ __forceinline__ uint32_t seg_len(uint32_t W, const WArg& wa, uint32_t G)
 {
-    uint32_t s = kSegPerSlot * W;
-    s = s > seg_min ? s : seg_min;
-    s = s < kSegFloor ? kSegFloor : (s > 65536u ? 65536u : s);
+    uint32_t s = wa.seg_per * W;
+    s = s > wa.seg_min ? s : wa.seg_min;
+    s = s > 65536u ? 65536u : s;
     if (G > 1u) s = s / G < kSegFloor ? kSegFloor : s / G;
     return s;
 }
@@ -94,22 +104,21 @@ __host__ __device__ __forceinline__ uint32_t grp_of(uint32_t W, uint32_t J)
     return W <= 8u ? 8u : 4u;
 }
 
-// How a list of W slots is replayed one per wavefront: class 0 the list in a register
-// (k_replay), 1 .. 4 the hash table (k_replay_hash) for up to kHashW[class] slots. The hash
-// form needs W >= 64. Table sizes by measurement, 4e7 requests x 8 candidates over 1,024
+// Classes of k_replay: the largest W and the slots of the hash table. Class 0 replays by the
+// list in a register; the hash form, in the others, needs W >= 64. Table sizes by measurement, 4e7 requests x 8 candidates over 1,024
 // streams: W = 86 2.67 / 2.69 / 2.83 ms with 384 / 512 / 640 slots, W = 156 3.12 / 2.95 / 2.78
 // with 512 / 640 / 768, W = 283 3.21 / 3.10 / 3.49 with 768 / 1,024 / 1,280, W = 512 3.93 /
 // 3.60 / 3.51 / 3.96 with 1,024 / 1,280 / 1,536 / 2,048: a small table is refreshed more often
 // and probes further, a large one leaves fewer wavefronts per CU.
-constexpr uint32_t kHashFrom = 64;
 constexpr uint32_t kClasses = 5;
-constexpr int kHashW[kClasses] = {0, 96, 192, 384, 512};
-constexpr int kHashSlots[kClasses] = {0, 384, 768, 1024, 1536};
+constexpr int kMaxW[kClasses] = {63, 96, 192, 384, 512};
+constexpr int kSlots[kClasses] = {256, 384, 768, 1024, 1536};
 
 __host__ __device__ __forceinline__ uint32_t rep_class(uint32_t W)
 {
-    if (W < kHashFrom) return 0u;
-    return W <= (uint32_t)kHashW[1] ? 1u : (W <= (uint32_t)kHashW[2] ? 2u : (W <= (uint32_t)kHashW[3] ? 3u : 4u));
+    uint32_t cls = 0;
+    while (cls + 1u < kClasses && W > (uint32_t)kMaxW[cls]) ++cls;
+    return cls;
 }
 
 struct PartGeom {
@@ -672,7 +681,7 @@ __global__ __launch_bounds__(1024) void k_seg_items(const uint32_t* __restrict__
         uint32_t cnt = 0, nseg = 0;
         if (e < total) {
             cnt = dtot[e];
-            const uint32_t S = seg_len(wa.W[e / R], wa.seg_min, wa.grp[e / R]);
+            const uint32_t S = seg_len(wa.W[e / R], wa, wa.grp[e / R]);
             nseg = cnt ? (cnt + S - 1) / S : 1u;
         }
         uint32_t tot, itot;
@@ -741,65 +750,22 @@ __device__ __forceinline__ uint32_t mtf_step(uint32_t& sk, uint32_t kk, uint64_t
     return p;
 }
 
-// Rebuild step over one full batch of 64 valid records, newest first: every key not yet
-// collected is appended at lane q. Positions q and up are free while the list is rebuilt, so
-// every key is written into lane q and q advances only past a new one; a repeated key left in
-// lane q duplicates an entry at a smaller position, which every later lookup finds first, and
-// the next new key overwrites it. Lanes past the final q are cleared once the rebuild ends. q
-// is compared with W once per 8 records; near W, where 8 keys might not fit the wave, a key
-// is put by a select on lane == q. Returns the new q.
-__device__ __forceinline__ uint32_t rebuild_batch(uint32_t& sk, const uint64_t* __restrict__ rb, uint32_t q, uint32_t W,
-                                                  uint32_t lane)
-{
-    // keys by scalar loads from the batch's records (rb is uniform), 8 per load
-    for (int g = 7; g >= 0 && q < W; --g) {
-        uint64_t rk[8];
-#pragma unroll
-        for (uint32_t t = 0; t < 8; ++t) rk[t] = rb[8u * (uint32_t)g + t];
-        uint32_t key[8];
-#pragma unroll
-        for (uint32_t t = 0; t < 8; ++t) key[t] = (uint32_t)rk[7u - t];  // newest first
-        if (q + 8u <= W) {
-#pragma unroll
-            for (uint32_t t = 0; t < 8; ++t) {
-                const uint64_t m = ballot(sk == key[t]);
-                sk = wrlane(sk, key[t], q);
-                asm("s_cmp_eq_u64 %1, 0\n\ts_addc_u32 %0, %0, 0" : "+s"(q) : "s"(m) : "scc");  // q += (m == 0)
-            }
-            continue;
-        }
-#pragma unroll
-        for (uint32_t t = 0; t < 8; ++t) {
-            const bool fresh = ballot(sk == key[t]) == 0;
-            const uint32_t target = fresh ? q : 0xFFFFFFFFu;
-            sk = lane == target ? key[t] : sk;
-            q += fresh ? 1u : 0u;
-        }
-    }
-    return q;
-}
-
-// 64 records (lane t of kl = key of record t, all valid) through the move-to-front list;
-// returns lane t = hit depth of record t. Keys are read 16 at a time ahead of their use.
-template <bool kMasked>
+// 64 records (all valid) through the move-to-front list; returns lane t = hit depth of record
+// t. The keys come from the batch's records (rb is uniform) by scalar loads, 8 records per
+// load: no vector instruction moves a key into a scalar register, and the other wavefronts of
+// the SIMD cover the wait for each load.
 __device__ __forceinline__ uint32_t mtf_batch(uint32_t& sk, const uint64_t* __restrict__ rb, uint64_t wmask)
 {
-    // The keys come from the batch's records (rb is uniform) by scalar loads, 8 records per
-    // load: no vector instruction moves a key into a scalar register. A wavefront waits for
-    // each load; the other wavefronts of its SIMD cover the wait.
     uint32_t depth = 0xFFFFFFFFu;
 #pragma unroll
     for (uint32_t g = 0; g < 8; ++g) {
-        uint64_t rk[8];
+        uint32_t key[8];
 #pragma unroll
-        for (uint32_t t = 0; t < 8; ++t) rk[t] = rb[8u * g + t];
+        for (uint32_t t = 0; t < 8; ++t) key[t] = (uint32_t)rb[8u * g + t];
 #pragma unroll
         for (uint32_t t = 0; t < 8; ++t) {
-            const uint32_t key = (uint32_t)rk[t];
-            uint64_t m = ballot(sk == key);
-            if (kMasked) m &= wmask;
-            const uint32_t p = mtf_core(sk, m);
-            sk = wrlane(sk, key, 0u);
+            const uint32_t p = mtf_core(sk, ballot(sk == key[t]) & wmask);
+            sk = wrlane(sk, key[t], 0u);
             depth = wrlane(depth, p, 8u * g + t);
         }
     }
@@ -876,10 +842,16 @@ struct StreamStats {
 // counting it and writing the final state if the run ends the stream. Each marked record
 // is thus replayed once more, and every record is scanned at most kRebuildBudget + 1 times,
 // whatever the keys. The kSeq launch rebuilds without a budget: a run's predecessor is an
-// unmarked segment, whose rebuild ended within its budget. Eight segment lengths: with two,
-// the whale-dominated destinations of the component ablation (8 keys at 6 % each) sent most
-// of their segments to the serial kSeq pass (1.8 ms per step against 0.01 ms with eight).
-constexpr uint32_t kRebuildBudget = 8;
+// unmarked segment, whose rebuild ended within its budget. A scan that meets known keys only
+// takes 256 records a step, about a tenth of the time their replay takes, and a marked run is
+// one serial chain, so the budget is wide: 2,000 keys over 30 streams of 133,000 requests took
+// 1.40, 0.69 and 0.30 ms at W = 512 with budgets of 8, 32 and 64 segment lengths (1.74, 1.58
+// and 1.31 ms at W = 100); streams that fill their caches never come near it.
+constexpr uint32_t kRebuildBudget = 64;
+
+// Records the backward rebuild of a segment of length S may scan (of segments cut shorter
+// than kSegFloor, as many as of those).
+__device__ __forceinline__ uint32_t rebuild_budget(uint32_t S) { return kRebuildBudget * (S > kSegFloor ? S : kSegFloor); }
 
 // Budget of k_replay_grp's forward rebuild, in its own (G times shorter) segment lengths.
 // Its rebuild windows run in lockstep with the other lists of the wavefront, so a deep one
@@ -887,172 +859,9 @@ constexpr uint32_t kRebuildBudget = 8;
 // against 12.7 ms with two (kSeq pass included).
 constexpr uint32_t kGrpRebuildBudget = 2;
 
-__device__ __forceinline__ bool item_marked(const uint32_t* __restrict__ aborted, uint64_t it)
-{
-    return (aborted[it >> 5] >> (it & 31u)) & 1u;
-}
-
-// At most 96 scalar registers, so that eight wavefronts fit on a SIMD.
-template <bool kSeq>
-__global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))) void k_replay(
-    const uint64_t* __restrict__ rec, uint64_t n, const uint32_t* __restrict__ grp_off,
-    const uint32_t* __restrict__ item_off, uint32_t P, uint32_t R, uint32_t K, uint32_t J,
-    const uint32_t* __restrict__ prefix_len, WArg wa, CandMap cm, uint32_t max_W,
-    const uint32_t* __restrict__ lru_in, uint32_t* __restrict__ lru_out, uint64_t* __restrict__ stats,
-    uint32_t* __restrict__ aborted, uint32_t* __restrict__ err)
-{
-    const uint32_t lane = lane_id();
-    const uint32_t v = blockIdx.x * (kReplayThreads / 64u) + wave_in_block();
-    uint64_t item;
-    uint32_t lo, hi;  // the item's stream is searched for in [lo, hi)
-    if (cm.n == 0) {  // every candidate of the call: wavefront v takes work item v
-        item = v;
-        if (item >= item_off[P * R]) return;
-        lo = 0;
-        hi = P * R;
-    } else {
-        if (v >= cm.wv0[cm.n]) return;
-        uint32_t ci = 0;  // the last i with wv0[i] <= v
-        {
-            uint32_t h = cm.n;
-            while (h - ci > 1) {
-                const uint32_t mid = (ci + h) >> 1;
-                if (cm.wv0[mid] <= v) ci = mid;
-                else h = mid;
-            }
-        }
-        const uint32_t cc = cm.cand[ci];
-        item = (uint64_t)item_off[cc * R] + (v - cm.wv0[ci]);
-        if (item >= item_off[(cc + 1) * R]) return;
-        lo = cc * R;
-        hi = (cc + 1) * R;
-    }
-    if (kSeq && !item_marked(aborted, item)) return;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (item_off[mid] <= item) lo = mid;
-        else hi = mid;
-    }
-    const uint32_t c = lo / R;
-    // kSeq: only the first marked segment of a run, which is never a stream's first item
-    if (kSeq && (item == item_off[lo] || item_marked(aborted, item - 1))) return;
-    const uint32_t d = lo - c * R;
-    const uint32_t W = wa.W[c];
-    if (W >= kHashFrom) return;
-    if (!kSeq && wa.grp[c] > 1u) return;  // k_replay_grp's segments (its marked ones come here in kSeq)
-    const uint32_t* go = grp_off + (uint64_t)c * (R + 1u);
-    const uint32_t gs = go[d], cnt = go[d + 1] - gs;
-    const uint32_t S = seg_len(W, wa.seg_min, wa.grp[c]);
-    const uint32_t nseg = item_off[lo + 1] - item_off[lo];
-    // [s0, s1): the records this wavefront replays; [s0, sc) of them are replayed only to
-    // reach the state at sc (the run's predecessor in the kSeq pass)
-    uint64_t i0 = item, i1 = item + 1;
-    if (kSeq) {
-        i0 = item - 1;
-        while (i1 < item_off[lo + 1] && item_marked(aborted, i1)) ++i1;
-    }
-    const uint32_t s0 = seg_start((uint32_t)(i0 - item_off[lo]), nseg, cnt);
-    const uint32_t sc = kSeq ? seg_start((uint32_t)(item - item_off[lo]), nseg, cnt) : s0;
-    const uint32_t s1 = seg_start((uint32_t)(i1 - item_off[lo]), nseg, cnt);
-    const uint64_t* __restrict__ rl = rec + (uint64_t)c * n + gs;
-
-    // Slot q of the rebuilt state is the q-th most recent key, which is already the
-    // move-to-front order.
-    uint32_t skey = CR_EMPTY_SLOT;
-    const uint64_t wmask = W >= 64u ? ~0ull : (1ull << W) - 1ull;  // lanes whose position is < W
-    uint32_t q = 0;
-    {
-        // State before record s0: the most recent W distinct keys, newest first. Records
-        // are read backwards 64 at a time, the next (older) batch in flight while one is
-        // scanned. (A kSeq wavefront rebuilds an unmarked segment, which stays in budget.)
-        uint32_t pos = s0, scanned = 0;
-        const uint32_t budget = kRebuildBudget * S;
-        uint32_t nb = pos < 64u ? pos : 64u;
-        uint32_t kl_next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
-        while (q < W && pos > 0) {
-            if (!kSeq && scanned >= budget) {  // too few distinct keys: left to the kSeq pass
-                if (lane == 0) atomicOr(&aborted[item >> 5], 1u << (item & 31u));
-                return;
-            }
-            const uint32_t kl = kl_next;
-            const uint32_t cnb = nb;
-            pos -= cnb;
-            scanned += cnb;
-            nb = pos < 64u ? pos : 64u;
-            kl_next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
-            if (cnb == 64u && ballot(kl < K) == ~0ull) {
-                q = rebuild_batch(skey, rl + pos, q, W, lane);
-                continue;
-            }
-            for (int t = (int)cnb - 1; t >= 0 && q < W; --t) {
-                const uint32_t kk = rdlane(kl, (uint32_t)t);
-                if (kk >= K) continue;
-                if (ballot(skey == kk) == 0) {
-                    skey = wrlane(skey, kk, q);
-                    ++q;
-                }
-            }
-        }
-    }
-    if (q < W && lru_in) {
-        const uint32_t* __restrict__ li = lru_in + ((uint64_t)c * R + d) * max_W;
-        bool done = false;
-        for (uint32_t s = 0; s < W && q < W && !done; s += 64) {
-            const uint32_t nb = W - s < 64u ? W - s : 64u;
-            const uint32_t v = lane < nb ? li[s + lane] : CR_EMPTY_SLOT;
-            for (uint32_t t = 0; t < nb && q < W; ++t) {
-                const uint32_t kk = rdlane(v, t);
-                if (kk == CR_EMPTY_SLOT) {
-                    done = true;
-                    break;
-                }
-                if (kk >= K) continue;
-                if (ballot(skey == kk) == 0) {
-                    skey = wrlane(skey, kk, q);
-                    ++q;
-                }
-            }
-        }
-    }
-
-    if (q < W) skey = lane >= q ? CR_EMPTY_SLOT : skey;  // drop what the rebuild left past q
-
-    StreamStats st{stats, P, R, J, c, d, lane};
-    bool bad = false;
-    // Forward replay of records [r0, r1); the next batch of records is in flight while one
-    // is replayed. With `on` false the list advances but nothing is counted.
-    auto run = [&](uint32_t r0, uint32_t r1, bool on) {
-        uint64_t rv_next = r0 + lane < r1 ? rl[r0 + lane] : 0ull;
-        for (uint32_t b0 = r0; b0 < r1; b0 += 64) {
-            const uint32_t nb = r1 - b0 < 64u ? r1 - b0 : 64u;
-            const uint64_t rv = rv_next;
-            rv_next = b0 + 64u + lane < r1 ? rl[b0 + 64u + lane] : 0ull;
-            const uint32_t kl = lane < nb ? (uint32_t)rv : CR_EMPTY_SLOT;
-            const bool vl = lane < nb && kl < K;
-            bad |= lane < nb && kl >= K;
-            const uint32_t pl = vl && on ? prefix_len[kl] : 0u;  // consumed after the batch
-            uint32_t depth = 0xFFFFFFFFu;  // lane t: hit depth of record t
-            if (ballot(vl) == ~0ull) {
-                depth = W == 64u ? mtf_batch<false>(skey, rl + b0, wmask) : mtf_batch<true>(skey, rl + b0, wmask);
-            } else {
-                for (uint32_t t = 0; t < nb; ++t) {
-                    const uint32_t kk = rdlane(kl, t);
-                    if (kk < K) depth = wrlane(depth, mtf_step(skey, kk, wmask), t);
-                }
-            }
-            if (on) st.add(rv, ballot(vl), ballot(depth != 0xFFFFFFFFu), pl);
-        }
-        st.flush();
-    };
-    if (sc > s0) run(s0, sc < s1 ? sc : s1, false);
-    run(sc, s1, true);
-    if (ballot(bad) && lane == 0) atomicOr(err, CR_ERR_KEY_RANGE);
-    if (s1 == cnt) {
-        uint32_t* __restrict__ lo_ = lru_out + ((uint64_t)c * R + d) * max_W;
-        if (lane < W) lo_[lane] = skey;
-        for (uint32_t idx = W + lane; idx < max_W; idx += 64) lo_[idx] = CR_EMPTY_SLOT;
-    }
-}
+// Marks: one byte per work item, which the item's wavefront of the first pass writes (1: its
+// rebuild ran out of budget, and the kSeq pass replays it).
+__device__ __forceinline__ bool item_marked(const uint8_t* __restrict__ aborted, uint64_t it) { return aborted[it] != 0u; }
 
 // ---------------------------------------------------------------------------------------
 // Lists of 64 slots and more: 64 records per step instead of one. A wavefront keeps the
@@ -1072,8 +881,8 @@ __global__ __launch_bounds__(kReplayThreads) __attribute__((amdgpu_num_sgpr(96))
 //     cleared, and T moves to the W-th bit.
 // The cost of a step hardly depends on W, where a list in registers paid a compare and a move
 // per 64 slots for every record. Measured (the cr_replay_lru call, 4e7 requests x 8 candidates
-// over 1,024 streams; list in registers before): W = 64 3.83 -> 2.46 ms, 86 6.64 -> 2.48,
-// 156 7.64 -> 2.72, 283 10.5 -> 3.10, 512 14.3 -> 3.86. Bound by instruction issue up to W of
+// over 1,024 streams; list in registers before): W = 64 3.83 -> 2.35 ms, 86 6.64 -> 2.39,
+// 156 7.64 -> 2.50, 283 10.5 -> 2.74, 512 14.3 -> 3.17. Bound by instruction issue up to W of
 // about 200, and by the latency of the dependent LDS round trips where the tables leave few
 // wavefronts per CU.
 // Entries past T stay in the table (their keys may come back to the same slot); when the
@@ -1316,15 +1125,113 @@ struct HashCache {
         wave_lds_fence();
         return q + total;
     }
+
+    // Whether every key of k[0..3] (lanes of am[0..3]) is in the table: four lookups in flight.
+    __device__ __forceinline__ bool all_known(const uint32_t (&k)[4], const uint64_t (&am)[4])
+    {
+        uint32_t a[4];
+        uint4 v[4];
+        uint64_t todo[4], any = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            a[u] = __umulhi(k[u] * 0x9E3779B1u, NS / 2u) * 16u;
+            v[u] = *reinterpret_cast<const uint4*>(at(a[u]));
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            todo[u] = ballot(v[u].x != k[u]) & ballot(v[u].z != k[u]) & am[u];
+            any |= todo[u];
+        }
+        while (any) {  // the next bucket, unless this one ends the probe
+            any = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (todo[u] & ballot(v[u].z == CR_EMPTY_SLOT)) return false;
+                const uint32_t next = a[u] + 16u;
+                a[u] = lane_in(todo[u]) ? (next < NS * 8u ? next : 0u) : a[u];
+                v[u] = *reinterpret_cast<const uint4*>(at(a[u]));
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                todo[u] = ballot(v[u].x != k[u]) & ballot(v[u].z != k[u]) & am[u];
+                any |= todo[u];
+            }
+        }
+        return true;
+    }
+
+    // The entries of the W most recent distinct keys of records [0, s0) of the stream rl into
+    // lds.list, newest first; q counts the distinct keys met. Records are read backwards 64 at
+    // a time, the next (older) batch in flight while one is scanned; after a batch that brought
+    // no new key, 256 at a time for as long as they bring none. False if `budget` records ran
+    // out with fewer than W keys and records left.
+    __device__ __forceinline__ bool rebuild(const uint64_t* __restrict__ rl, uint32_t s0, uint32_t K, uint32_t budget,
+                                            uint32_t& q)
+    {
+        uint32_t pos = s0;
+        const uint32_t stop = s0 > budget ? s0 - budget : 0u;
+        while (q < W && pos > stop) {
+            bool none = false;
+            uint32_t nb = pos < 64u ? pos : 64u;
+            uint32_t next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
+            while (q < W && pos > stop && !none) {
+                const uint32_t kl = next;
+                pos -= nb;
+                nb = pos < 64u ? pos : 64u;
+                next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
+                const uint32_t was = q;
+                q = rebuild_step(kl, ballot(kl < K), q);
+                none = q == was;
+            }
+            bool known = q < W && pos >= 256u && pos > stop;
+            uint32_t kn[4];
+            if (known)
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u) kn[u] = (uint32_t)rl[pos - 256u + 64u * u + lane];
+            while (known) {
+                uint32_t k[4];
+                uint64_t am[4];
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u) {
+                    k[u] = kn[u];
+                    am[u] = ballot(k[u] < K);
+                }
+                const bool more = pos >= 512u;
+                if (more)
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u) kn[u] = (uint32_t)rl[pos - 512u + 64u * u + lane];
+                if (!all_known(k, am)) break;
+                pos -= 256u;
+                known = more && pos > stop;
+            }
+        }
+        return q >= W || pos == 0u;
+    }
+
+    // The same over a carried state row, newest first and up to its first empty entry.
+    __device__ __forceinline__ void rebuild_carried(const uint32_t* __restrict__ li, uint32_t K, uint32_t& q)
+    {
+        for (uint32_t s = 0; s < W && q < W; s += 64) {
+            const uint32_t i = s + 63u - lane;  // lane 63 takes the newest of 64 entries
+            const uint32_t kk = i < W ? li[i] : CR_EMPTY_SLOT;
+            const uint64_t empty = ballot(kk == CR_EMPTY_SLOT);
+            const uint64_t valid = empty ? ~0ull << (63u - (uint32_t)__builtin_clzll(empty)) : ~0ull;
+            q = rebuild_step(kk, ballot(kk < K) & valid, q);
+            if (empty) break;
+        }
+    }
 };
 
-template <int NS, int kMaxW, bool kSeq>
-__global__ __launch_bounds__(64) void k_replay_hash(
+// One wavefront per segment (or run of marked segments), of candidates with kMinW <= W <= kMaxW.
+// With kList the cache is the list in a register and the hash table serves the rebuild alone.
+// At most 96 scalar registers, so that eight wavefronts fit on a SIMD.
+template <int NS, int kMinW, int kMaxW, bool kList, bool kSeq>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_num_sgpr(96))) void k_replay(
     const uint64_t* __restrict__ rec, uint64_t n, const uint32_t* __restrict__ grp_off,
     const uint32_t* __restrict__ item_off, uint32_t P, uint32_t R, uint32_t K, uint32_t J,
     const uint32_t* __restrict__ prefix_len, WArg wa, CandMap cm, uint32_t max_W,
     const uint32_t* __restrict__ lru_in, uint32_t* __restrict__ lru_out, uint64_t* __restrict__ stats,
-    uint32_t* __restrict__ aborted, uint32_t* __restrict__ err)
+    uint8_t* __restrict__ aborted, uint32_t* __restrict__ err)
 {
     __shared__ HashLds<NS, kMaxW> lds;
     const uint32_t lane = lane_id();
@@ -1364,11 +1271,12 @@ __global__ __launch_bounds__(64) void k_replay_hash(
     if (kSeq && (item == item_off[lo] || item_marked(aborted, item - 1))) return;
     const uint32_t d = lo - c * R;
     const uint32_t W = wa.W[c];
-    if (W < kHashFrom || W > (uint32_t)kMaxW) return;
-    static_assert(kHashFrom >= 64u, "a key repeated within 64 records is always a hit");
+    if (W < (uint32_t)kMinW || W > (uint32_t)kMaxW) return;
+    if (!kSeq && wa.grp[c] > 1u) return;  // k_replay_grp's segments (its marked ones come here in kSeq)
+    static_assert(kList ? kMaxW < 64 : kMinW >= 64, "a list fits a register; a key repeated within 64 records always hits");
     const uint32_t* go = grp_off + (uint64_t)c * (R + 1u);
     const uint32_t gs = go[d], cnt = go[d + 1] - gs;
-    const uint32_t S = seg_len(W, wa.seg_min, 1u);
+    const uint32_t S = seg_len(W, wa, wa.grp[c]);
     const uint32_t nseg = item_off[lo + 1] - item_off[lo];
     // [s0, s1): the records this wavefront replays; [s0, sc) of them are replayed only to
     // reach the state at sc (the run's predecessor in the kSeq pass)
@@ -1381,43 +1289,23 @@ __global__ __launch_bounds__(64) void k_replay_hash(
     const uint32_t sc = kSeq ? seg_start((uint32_t)(item - item_off[lo]), nseg, cnt) : s0;
     const uint32_t s1 = seg_start((uint32_t)(i1 - item_off[lo]), nseg, cnt);
     const uint64_t* __restrict__ rl = rec + (uint64_t)c * n + gs;
+    if (!kSeq && lane == 0) aborted[item] = 0u;
 
+    // State before record s0: the most recent W distinct keys of the records before it, then
+    // those of the carried state. (A kSeq wavefront rebuilds an unmarked segment: in budget.)
     HashCache<NS, kMaxW> cache(lds, W, lane);
     cache.clear();
     uint32_t q = 0;
-    {
-        // State before record s0: the most recent W distinct keys. Records are read backwards
-        // 64 at a time, the next (older) batch in flight while one is scanned.
-        uint32_t pos = s0, scanned = 0;
-        const uint32_t budget = kRebuildBudget * S;
-        uint32_t nb = pos < 64u ? pos : 64u;
-        uint32_t kl_next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
-        while (q < W && pos > 0) {
-            if (!kSeq && scanned >= budget) {  // too few distinct keys: left to the kSeq pass
-                if (lane == 0) atomicOr(&aborted[item >> 5], 1u << (item & 31u));
-                return;
-            }
-            const uint32_t kl = kl_next;
-            pos -= nb;
-            scanned += nb;
-            nb = pos < 64u ? pos : 64u;
-            kl_next = lane < nb ? (uint32_t)rl[pos - nb + lane] : CR_EMPTY_SLOT;
-            q = cache.rebuild_step(kl, ballot(kl < K), q);
-        }
+    if (!cache.rebuild(rl, s0, K, kSeq ? 0xFFFFFFFFu : rebuild_budget(S), q)) {
+        if (lane == 0) aborted[item] = 1u;  // too few distinct keys in reach: left to the kSeq pass
+        return;
     }
-    if (q < W && lru_in) {
-        // the carried state, newest first: lane 63 takes the newest of 64 entries
-        const uint32_t* __restrict__ li = lru_in + ((uint64_t)c * R + d) * max_W;
-        for (uint32_t s = 0; s < W && q < W; s += 64) {
-            const uint32_t i = s + 63u - lane;
-            const uint32_t kk = i < W ? li[i] : CR_EMPTY_SLOT;
-            const uint64_t empty = ballot(kk == CR_EMPTY_SLOT);  // entries end at the first empty one
-            const uint64_t valid = empty ? ~0ull << (63u - (uint32_t)__builtin_clzll(empty)) : ~0ull;
-            q = cache.rebuild_step(kk, ballot(kk < K) & valid, q);
-            if (empty) break;
-        }
-    }
-    cache.place(q < W ? q : W);
+    if (q < W && lru_in) cache.rebuild_carried(lru_in + ((uint64_t)c * R + d) * max_W, K, q);
+    q = q < W ? q : W;
+    uint32_t skey = CR_EMPTY_SLOT;                 // kList: lane i = i-th most recent key
+    const uint64_t wmask = (1ull << (W & 63u)) - 1ull;  // kList: lanes whose position is < W
+    if (kList) skey = lane < q ? *cache.at(lds.list[lane]) : CR_EMPTY_SLOT;
+    else cache.place(q);
 
     StreamStats st{stats, P, R, J, c, d, lane};
     bool bad = false;
@@ -1432,9 +1320,23 @@ __global__ __launch_bounds__(64) void k_replay_hash(
             const uint32_t kl = lane < nb ? (uint32_t)rv : CR_EMPTY_SLOT;
             const bool vl = lane < nb && kl < K;
             bad |= lane < nb && kl >= K;
-            const uint32_t pl = vl && on ? prefix_len[kl] : 0u;  // consumed after the step
+            const uint32_t pl = vl && on ? prefix_len[kl] : 0u;  // consumed after the batch
             const uint64_t vm = ballot(vl);
-            const uint64_t hm = cache.step(kl, vm);
+            uint64_t hm;  // the lanes whose records hit
+            if (!kList) {
+                hm = cache.step(kl, vm);
+            } else {
+                uint32_t depth = 0xFFFFFFFFu;  // lane t: hit depth of record t
+                if (vm == ~0ull) {
+                    depth = mtf_batch(skey, rl + b0, wmask);
+                } else {
+                    for (uint32_t t = 0; t < nb; ++t) {
+                        const uint32_t kk = rdlane(kl, t);
+                        if (kk < K) depth = wrlane(depth, mtf_step(skey, kk, wmask), t);
+                    }
+                }
+                hm = ballot(depth != 0xFFFFFFFFu);
+            }
             if (on) st.add(rv, vm, hm, pl);
         }
         st.flush();
@@ -1444,8 +1346,12 @@ __global__ __launch_bounds__(64) void k_replay_hash(
     if (ballot(bad) && lane == 0) atomicOr(err, CR_ERR_KEY_RANGE);
     if (s1 == cnt) {
         uint32_t* __restrict__ lo_ = lru_out + ((uint64_t)c * R + d) * max_W;
-        cache.each_live([&](uint32_t key, uint32_t depth) { lo_[depth] = key; });
-        for (uint32_t idx = cache.live + lane; idx < max_W; idx += 64) lo_[idx] = CR_EMPTY_SLOT;
+        if (kList) {
+            for (uint32_t idx = lane; idx < max_W; idx += 64) lo_[idx] = idx < W ? skey : CR_EMPTY_SLOT;
+        } else {
+            cache.each_live([&](uint32_t key, uint32_t depth) { lo_[depth] = key; });
+            for (uint32_t idx = cache.live + lane; idx < max_W; idx += 64) lo_[idx] = CR_EMPTY_SLOT;
+        }
     }
 }
 
@@ -1501,7 +1407,7 @@ __global__ __launch_bounds__(kReplayThreads) void k_replay_grp(
     const uint64_t* __restrict__ rec, uint64_t n, const uint32_t* __restrict__ grp_off,
     const uint32_t* __restrict__ item_off, const uint32_t* __restrict__ gwave_off, uint32_t P, uint32_t R, uint32_t K,
     const uint32_t* __restrict__ prefix_len, WArg wa, uint32_t max_W, const uint32_t* __restrict__ lru_in,
-    uint32_t* __restrict__ lru_out, uint64_t* __restrict__ stats, uint32_t* __restrict__ aborted,
+    uint32_t* __restrict__ lru_out, uint64_t* __restrict__ stats, uint8_t* __restrict__ aborted,
     uint32_t* __restrict__ err)
 {
     constexpr uint32_t w = 64u / G;
@@ -1535,13 +1441,14 @@ __global__ __launch_bounds__(kReplayThreads) void k_replay_grp(
         }
     }
     const uint32_t d = lo - c * R;
-    const uint32_t S = seg_len(W, wa.seg_min, G);
+    const uint32_t S = seg_len(W, wa, G);
     const uint32_t* go = grp_off + (uint64_t)c * (R + 1u);
     const uint32_t gs = live ? go[d] : 0u, cnt = live ? go[d + 1] - gs : 0u;
     const uint32_t nseg = live ? item_off[lo + 1] - item_off[lo] : 1u;
     const uint32_t s0 = live ? seg_start((uint32_t)(item - item_off[lo]), nseg, cnt) : 0u;
     const uint32_t s1 = live ? seg_start((uint32_t)(item - item_off[lo]) + 1u, nseg, cnt) : 0u;
     const uint64_t* __restrict__ rl = rec + (uint64_t)c * n + gs;
+    if (live && j == 0) aborted[item] = 0u;
     uint32_t* __restrict__ stage = s_stage[wv] + g * kStride;
 
     uint64_t START = 0, END = 0;
@@ -1676,7 +1583,7 @@ __global__ __launch_bounds__(kReplayThreads) void k_replay_grp(
         const bool full = (F >> (g * w + W - 1u)) & 1ull;
         const bool ok = part && (full || dg == s0);
         if (part && !ok && dg == dmax) {  // too few distinct keys in reach: left to the kSeq pass
-            if (j == 0) atomicOr(&aborted[item >> 5], 1u << (item & 31u));
+            if (j == 0) aborted[item] = 1u;
             live = false;
         }
         ready = ready || ok || (part && dg == dmax);
@@ -1705,12 +1612,6 @@ __global__ __launch_bounds__(kReplayThreads) void k_replay_grp(
     }
 }
 
-__global__ void k_zero_u32(uint32_t* __restrict__ p, uint64_t n)
-{
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0u;
-}
-
 struct ReplayWs {
     uint64_t* rec;
     uint32_t* tcnt;
@@ -1718,13 +1619,9 @@ struct ReplayWs {
     uint32_t* grp_off;
     uint32_t* item_off;
     uint32_t* gwave_off;  // [P + 1] first k_replay_grp wavefront of each candidate
-    uint32_t* aborted;  // bit per work item: its rebuild ran out of budget
-    uint64_t flag_words;
+    uint8_t* aborted;  // byte per work item: its rebuild ran out of budget
     size_t bytes;
 };
-
-// Upper bound on replay work items: one per (c, d) plus one per full shortest segment.
-inline uint64_t max_items(uint64_t n, uint32_t P, uint32_t R) { return (uint64_t)P * R + (uint64_t)P * n / kSegFloor + 1u; }
 
 inline ReplayWs replay_layout(void* base, uint64_t n, uint32_t P, uint32_t R)
 {
@@ -1745,9 +1642,13 @@ inline ReplayWs replay_layout(void* base, uint64_t n, uint32_t P, uint32_t R)
     o = up(o + ((uint64_t)P * R + 1u) * 4u);
     w.gwave_off = reinterpret_cast<uint32_t*>(b + o);
     o = up(o + ((uint64_t)P + 1u) * 4u);
-    w.aborted = reinterpret_cast<uint32_t*>(b + o);
-    w.flag_words = (max_items(n, P, R) + 31u) / 32u;
-    o = up(o + w.flag_words * 4u);
+    // The marks of cr_replay_lru take the place of the tile counts, which the scatter was the
+    // last to read: P R + P n / S items at most, S >= max(kSegShort, P n / kSegTarget), against
+    // 4 P R ntiles bytes with ntiles >= min(n / 1024, kSegTarget / P - 1); without requests,
+    // P R items in the 4 P R bytes of the destination totals.
+    w.aborted = reinterpret_cast<uint8_t*>(g.ntiles ? w.tcnt : w.dtot);
+    // a bit per P R + P n / kSegFloor items, which earlier layouts kept here: the size stays
+    o = up(o + (((uint64_t)P * R + (uint64_t)P * n / kSegFloor + 1u + 31u) / 32u) * 4u);
     w.bytes = (size_t)o + 256u;
     return w;
 }
@@ -1772,7 +1673,14 @@ inline cr_status replay_args(uint64_t n, uint32_t J, uint32_t P, uint32_t R, con
         max_W > CR_MAX_W || !ws || n >= 0xFFFFFFFFull)
         return CR_EINVAL;
     ra->wa = WArg{};
-    ra->wa.seg_min = (uint32_t)(((uint64_t)n * P + kSegTarget - 1) / kSegTarget);
+    const uint64_t recs = n * P;
+    const uint64_t share = (recs + kSegTarget - 1) / kSegTarget;
+    const uint32_t floor_ = recs >= kSegFull ? kSegFloor : (uint32_t)(recs * kSegFloor / kSegFull);
+    ra->wa.seg_min = share > 65536u ? 65536u : (uint32_t)share;
+    ra->wa.seg_min = ra->wa.seg_min > floor_ ? ra->wa.seg_min : floor_;
+    ra->wa.seg_min = ra->wa.seg_min > kSegShort ? ra->wa.seg_min : kSegShort;
+    ra->wa.seg_per = recs >= kSegFull ? kSegPerSlot : (uint32_t)(recs * kSegPerSlot / kSegFull);
+    ra->wa.seg_per = ra->wa.seg_per > kSegPerSlotShort ? ra->wa.seg_per : kSegPerSlotShort;
     ra->classes = 0;
     ra->wclasses = 0;
     ra->groups = 0;
@@ -1787,7 +1695,7 @@ inline cr_status replay_args(uint64_t n, uint32_t J, uint32_t P, uint32_t R, con
         ra->wa.grp[c] = (uint8_t)G;
         ra->classes |= 1u << rep_class(W[c]);
         if (G == 1u) ra->wclasses |= 1u << rep_class(W[c]);
-        const uint32_t S = seg_len(W[c], ra->wa.seg_min, G);
+        const uint32_t S = seg_len(W[c], ra->wa, G);
         if (G > 1u) {  // at most R + n / S work items, G per wavefront
             ra->groups |= 1u << G;
             ra->grp_waves += ((uint64_t)R + n / S) / G + 1u;
@@ -1969,7 +1877,7 @@ extern "C" cr_status cr_replay_lru(const uint32_t* prefix_len, uint32_t num_keys
             if (rep_class(W[c]) != cls || (!seq && ra.wa.grp[c] > 1u)) continue;
             cm.cand[cm.n] = (uint16_t)c;
             cm.wv0[cm.n++] = (uint32_t)wv;
-            wv += (uint64_t)R + n / seg_len(W[c], ra.wa.seg_min, ra.wa.grp[c]) + 1u;
+            wv += (uint64_t)R + n / seg_len(W[c], ra.wa, ra.wa.grp[c]) + 1u;
         }
         cm.wv0[cm.n] = (uint32_t)wv;
         if (cm.n == P) cm.n = 0;  // every candidate, in order: work item v is wavefront v
@@ -1978,25 +1886,19 @@ extern "C" cr_status cr_replay_lru(const uint32_t* prefix_len, uint32_t num_keys
     for (uint32_t cls = 0; cls < kClasses; ++cls)
         if (cand_map(cls, true) > 0x7FFFFFFFull) return CR_EINVAL;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_zero_u32, dim3(256), dim3(256), 0, st, w.aborted, w.flag_words);
     auto launch_class = [&](uint32_t cls, bool seq, hipStream_t on) {
         const uint64_t nw = cand_map(cls, seq);
         if (!nw) return;
-        const dim3 b4((uint32_t)((nw + (kReplayThreads / 64) - 1) / (kReplayThreads / 64))), b1((uint32_t)nw);
-#define CR_REPLAY(KERNEL, BLOCKS, THREADS)                                                                          \
-    hipLaunchKernelGGL((KERNEL), BLOCKS, dim3(THREADS), 0, on, w.rec, n, w.grp_off, w.item_off, P, R, num_keys, J,   \
-                       prefix_len, ra.wa, cm, max_W, lru_in, lru_out, stats, w.aborted, err)
-#define CR_HASH(C)                                                                                                  \
-    else if (cls == (C)) {                                                                                          \
-        if (seq) CR_REPLAY((k_replay_hash<kHashSlots[C], kHashW[C], true>), b1, 64);                                 \
-        else CR_REPLAY((k_replay_hash<kHashSlots[C], kHashW[C], false>), b1, 64);                                    \
+#define CR_REPLAY(KERNEL)                                                                                            \
+    hipLaunchKernelGGL(KERNEL, dim3((uint32_t)nw), dim3(64), 0, on, w.rec, n, w.grp_off, w.item_off, P, R, num_keys, \
+                       J, prefix_len, ra.wa, cm, max_W, lru_in, lru_out, stats, w.aborted, err)
+#define CR_CLASS(C, LIST)                                                                                            \
+    if (cls == (C)) {                                                                                               \
+        if (seq) CR_REPLAY((k_replay<kSlots[C], (C) ? kMaxW[(C) - 1] + 1 : 1, kMaxW[C], LIST, true>));               \
+        else CR_REPLAY((k_replay<kSlots[C], (C) ? kMaxW[(C) - 1] + 1 : 1, kMaxW[C], LIST, false>));                  \
     }
-        if (cls == 0) {
-            if (seq) CR_REPLAY(k_replay<true>, b4, kReplayThreads);
-            else CR_REPLAY(k_replay<false>, b4, kReplayThreads);
-        }
-        CR_HASH(1) CR_HASH(2) CR_HASH(3) CR_HASH(4)
-#undef CR_HASH
+        CR_CLASS(0, true) CR_CLASS(1, false) CR_CLASS(2, false) CR_CLASS(3, false) CR_CLASS(4, false)
+#undef CR_CLASS
 #undef CR_REPLAY
     };
     // The list classes' launches and the grouped ones are independent of each other (other
