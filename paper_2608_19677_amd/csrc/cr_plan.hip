@@ -1213,11 +1213,29 @@ __global__ __launch_bounds__(64) void k_lpt_small(uint32_t KW, uint32_t R, uint3
 // charged to the positions before it in the batch (position q is then the least (L, r) pair
 // when job t+q is placed), found by a block-wide exclusive prefix minimum; ties end the
 // batch. A job with k > 1 is a batch of its own that charges positions 0..k-1, its members in
-// that order. After a batch the charged positions are merged back into the sorted state:
-// when their new (L, r) pairs are still in order, by a merge path (each element's rank in the
-// other sorted list by binary search in LDS); otherwise by a bitonic sort of all N pairs.
-// On the large sweep (R = 1,024, up to 524,288 jobs per plan) a plan takes about 600
-// batches. Route words are written afterwards by k_route_words, in parallel.
+// that order. After a batch the charged positions are merged back into the sorted state. Jobs
+// of one count keep the positions they charge in order, so the charged list is one sorted run
+// per count: up to kLptRuns of them are merged with the uncharged positions by a merge path
+// (each element's rank in every other run by binary search in LDS); more, or in blocks below
+// kLptRunsFrom threads, by a bitonic sort of all N pairs.
+//
+// The tail of the order is long runs of one count x. Placing them is popping the smallest of
+// the pairs {(L_i + j x, i), j >= 0} J times, and as long as no load leaves the power of two
+// that the smallest load lies in, every such sum is exact (all are multiples of its last bit).
+// With L_0 the smallest load, write L_i = L_0 + e_i x + f_i, 0 <= f_i < x: in epoch e the loads
+// in [L_0 + e x, L_0 + (e + 1) x) are charged, once each, in the order of (f_i, i) among the
+// destinations with e_i <= e. So one sort by (f, i) serves up to kLptEpochs epochs (each a
+// batch of its own otherwise): the epochs' sizes are prefix lengths of the sorted state, a
+// job's place in its epoch is a count of active destinations before it (ballots), and the
+// new state is that sort order followed by the destinations still ahead.
+// One plan of 524,288 jobs over 1,024 destinations (611 batches, 403 of them of one count, bound
+// by their barriers and LDS round trips): 4,000 -> 2,480 us; 92 plans over 257 destinations
+// 709 -> 384 us. Route words are written afterwards by k_route_words, in parallel.
+constexpr uint32_t kLptEpochs = 64;
+constexpr uint32_t kLptMinRounds = 2;  // rounds of R a run must cover for it (1 and 4 measured slower)
+constexpr uint32_t kLptRuns = 3;       // sorted runs merged at once (2 and 4 measured slower)
+constexpr int kLptRunsFrom = 512;      // block size from which that beats the sort (small blocks: 98 against 86 us)
+
 template <int N>
 struct LptBlockLds {
     double v[2][N];        // sorted state (double-buffered for the merge)
@@ -1232,7 +1250,9 @@ struct LptBlockLds {
     double l0v[N / 64];
     uint32_t l0r[N / 64];
     uint32_t wfail[N / 64];  // per-wavefront first position that fails the batch rule
-    uint32_t wuns[N / 64];   // per-wavefront: the charged pairs are out of order
+    uint32_t wuns[N / 64];   // per-wavefront: 1 some charged pairs are out of order, 2 of one count
+    unsigned long long wbrk[N / 64];  // per-wavefront: positions whose next job has another count
+    uint32_t en[kLptEpochs + 2];      // destinations active in an epoch
 };
 
 // Number of pairs among (v[lo .. lo+len)) smaller than (x, rx); the list is sorted.
@@ -1243,7 +1263,8 @@ __device__ __forceinline__ uint32_t lower_bound_pair(const double* __restrict__ 
     while (n > 0) {
         const uint32_t h = n >> 1;
         const uint32_t m = b + h;
-        if (lt_pair(v[m], r[m], x, rx)) {
+        const double y = v[m];
+        if (y < x || (y == x && r[m] < rx)) {  // the index is read on ties only
             b = m + 1;
             n -= h + 1;
         } else {
@@ -1251,6 +1272,36 @@ __device__ __forceinline__ uint32_t lower_bound_pair(const double* __restrict__ 
         }
     }
     return b - lo;
+}
+
+// Bitonic sort of the block's N pairs, one per thread; tv and tr are scratch.
+template <int N>
+__device__ __forceinline__ void block_sort_pairs(double& v, uint32_t& r, double* tv, uint32_t* tr)
+{
+    const uint32_t i = threadIdx.x;
+    for (uint32_t kk = 2; kk <= N; kk <<= 1) {
+        for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
+            double pv;
+            uint32_t pr;
+            if (j >= 64) {
+                tv[i] = v;
+                tr[i] = r;
+                __syncthreads();
+                pv = tv[i ^ j];
+                pr = tr[i ^ j];
+                __syncthreads();
+            } else {
+                pv = __shfl_xor(v, (int)j, 64);
+                pr = __shfl_xor(r, (int)j, 64);
+            }
+            const bool up = (i & kk) == 0, lower = (i & j) == 0;
+            const bool pless = lt_pair(pv, pr, v, r) != 0;
+            if (pless == (lower == up)) {
+                v = pv;
+                r = pr;
+            }
+        }
+    }
 }
 
 template <int N>
@@ -1294,12 +1345,99 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
         sh.jc[N + i] = c, sh.jo[N + i] = o, sh.jk[N + i] = (uint16_t)k;
         job(2 * N + i, pc, po, pk);
     }
+    static_assert(kLptEpochs == 64 && kLptEpochs * NWV * 4u <= sizeof(sh.cv), "epochs by lane; counts in cv");
     uint32_t cur = 0, base = 0, t = 0;
     __syncthreads();
     while (t < A) {
         const uint32_t rj = (t + i) & (2u * N - 1u), r0 = t & (2u * N - 1u);
         const uint32_t c = sh.jc[rj], o = sh.jo[rj], k = sh.jk[rj];
         const uint32_t k0 = sh.jk[r0];
+        if (k0 == 1 && t + R <= A && sh.jc[(t + R - 1u) & (2u * N - 1u)] == sh.jc[r0]) {
+            // a run of at least R jobs of one count (which then all have the same k)
+            const uint32_t c0 = sh.jc[r0], o0 = sh.jo[r0];
+            const double x = (double)c0, v0 = sh.v[cur][0];
+            // epochs before a load may leave the power of two of v0
+            const double top = __longlong_as_double((long long)(((((uint64_t)__double_as_longlong(v0)) >> 52) + 1ull) << 52));
+            const double fit = (top - v0) / x - 2.0;
+            const uint32_t emax = fit >= (double)kLptEpochs ? kLptEpochs : (fit >= 2.0 ? (uint32_t)fit : 0u);
+            const uint64_t last = (uint64_t)t + (uint64_t)(lane + 1u) * R - 1u;
+            const uint32_t m = (uint32_t)__popcll(ballot(last < A && ocnt[last < A ? (uint32_t)last : t] == c0));
+            if (emax >= 2u && m >= kLptMinRounds) {
+                // the run's jobs, up to 64 R of them: m R, and those of the next R
+                const uint64_t more = (uint64_t)t + (uint64_t)m * R + i;
+                const uint64_t same = ballot(m < 64u && i < R && more < A && ocnt[more < A ? (uint32_t)more : t] == c0);
+                uint32_t e = emax + 1u;
+                double f = 0.0;
+                if (i < R && v < v0 + (double)(emax + 1u) * x) {
+                    const double d = v - v0;
+                    double q = floor(d / x);
+                    f = d - q * x;
+                    if (f < 0.0) q -= 1.0, f += x;
+                    else if (f >= x) q += 1.0, f -= x;
+                    e = (uint32_t)q;
+                }
+                sh.cr[i] = e;  // nondecreasing in i
+                if (lane == 0) sh.wfail[wv] = (uint32_t)__popcll(same);
+                __syncthreads();
+                const uint32_t en = i + 1u < (uint32_t)N ? sh.cr[i + 1u] : emax + 1u;
+                for (uint32_t u = e; u < en && u <= emax; ++u) sh.en[u] = i + 1u;
+                const uint32_t J = m * R + rdlane(wave_incl_scan_u32(lane < NWV ? sh.wfail[lane] : 0u), 63u);
+                __syncthreads();
+                // lane u: destinations active in epoch u and jobs before it; the epochs J covers
+                // whole (E of them, at least one) and what it takes of the next
+                const uint32_t na = lane < emax ? sh.en[lane] : 0u;
+                const uint32_t incl = wave_incl_scan_u32(na);
+                const uint32_t first = incl - na;
+                const uint32_t E = (uint32_t)__popcll(ballot(lane + 1u < emax && incl <= J));
+                const uint32_t whole = rdlane(incl, E - 1u), nE = sh.en[E];
+                const uint32_t left = J - whole < nE ? J - whole : 0u;
+                const uint32_t nP = sh.en[E + 1u];
+                double sf = i < nP ? f : INF;
+                uint32_t sr = i < nP ? (r << 7) | e : 0xFFFFFFFFu;
+                block_sort_pairs<N>(sf, sr, sh.v[cur ^ 1u], sh.r[cur ^ 1u]);
+                const uint32_t se = sr & 127u;
+                const bool in = i < nP;
+                uint32_t* __restrict__ wc = reinterpret_cast<uint32_t*>(sh.cv);  // [epoch][wavefront]
+                uint32_t mine = 0;
+                for (uint32_t u = 0; u <= E; ++u) {
+                    const uint32_t n = (uint32_t)__popcll(ballot(in && se <= u));
+                    mine = lane == u ? n : mine;
+                }
+                wc[lane * NWV + wv] = mine;
+                __syncthreads();
+                uint32_t at = 0;  // lane u: epoch u's active destinations in earlier wavefronts
+                for (uint32_t u = 0; u < wv; ++u) at += wc[lane * NWV + u];
+                uint32_t place = 0;
+                for (uint32_t u = 0; u <= E; ++u) {
+                    const bool on = in && se <= u;
+                    const uint64_t om = ballot(on);
+                    place = rdlane(at, u) + __builtin_amdgcn_mbcnt_hi((uint32_t)(om >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)om, 0u));
+                    if (on && (u < E || place < left)) mem[o0 + rdlane(first, u) + place] = (uint16_t)(sr >> 7);
+                }
+                if (in) {
+                    // epoch E's uncharged ones, then epoch E + 1's
+                    const bool stay = se <= E && place >= left;
+                    const uint32_t pos = stay ? place - left : nE - left + i - (place > left ? place - left : 0u);
+                    sh.v[cur][pos] = (v0 + (double)(stay ? E : E + 1u) * x) + sf;
+                    sh.r[cur][pos] = sr >> 7;
+                }
+                t += whole + left;
+                // the ring starts again around t
+                base = t & ~(uint32_t)(N - 1);
+#pragma unroll
+                for (uint32_t h = 0; h < 2; ++h) {
+                    const uint32_t ja = base + h * N + i, slot = ja & (2u * N - 1u);
+                    uint32_t cc, oo, kk;
+                    job(ja, cc, oo, kk);
+                    sh.jc[slot] = cc, sh.jo[slot] = oo, sh.jk[slot] = (uint16_t)kk;
+                }
+                job(base + 2 * N + i, pc, po, pk);
+                __syncthreads();
+                v = sh.v[cur][i];
+                r = sh.r[cur][i];
+                continue;
+            }
+        }
         double a;
         uint32_t M;
         if (k0 > 1) {
@@ -1318,7 +1456,7 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
             const bool single = k == 1 && i < R;
             a = single ? v + (double)c : INF;  // position i's load once charged with job t+i
             double pm = wave_exclusive_min_f64(a);
-            const double wtot = __shfl(fmin(pm, a), 63, 64);
+            const double wtot = rdlane_f64(fmin(pm, a), 63u);
             if (lane == 0) {
                 sh.wmin[wv] = wtot;
                 sh.l0a[wv] = a;
@@ -1345,22 +1483,56 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
             nr = sh.l0r[wv + 1];
         }
         const bool out_of_order = i + 1 < M && !lt_pair(wv_, r, nx, nr);
-        const uint64_t uns = ballot(out_of_order);
-        if (lane == 0) sh.wuns[wv] = uns != 0;
+        const bool brk = k0 == 1 && i + 1 < M && c != sh.jc[(t + i + 1u) & (2u * N - 1u)];
+        const uint64_t uns = ballot(out_of_order), bad = ballot(out_of_order && !brk), brks = ballot(brk);
+        if (lane == 0) {
+            sh.wuns[wv] = (uns != 0 ? 1u : 0u) | (bad != 0 ? 2u : 0u);
+            sh.wbrk[wv] = brks;
+        }
         if (charged) {
             sh.cv[i] = a;
             sh.cr[i] = r;
         }
         __syncthreads();
-        uint32_t any_uns = 0;
-        for (uint32_t u = 0; u < NWV; ++u) any_uns |= sh.wuns[u];
+        const uint32_t flags = lane < NWV ? sh.wuns[lane] : 0u;
+        const uint64_t wbrk = lane < NWV ? sh.wbrk[lane] : 0ull;
+        const uint32_t any_uns = (ballot((flags & 1u) != 0u) ? 1u : 0u) | (ballot((flags & 2u) != 0u) ? 2u : 0u);
+        const uint32_t nbrk = rdlane(wave_incl_scan_u32((uint32_t)__popcll(wbrk)), 63u);
         const uint32_t nxt = cur ^ 1u;
-        if (!any_uns) {
-            // merge path: charged list cv[0..M) and the unchanged sorted positions M..R-1
+        if (any_uns == 0 || (N >= kLptRunsFrom && any_uns == 1u && nbrk < kLptRuns)) {
+            // merge path: the charged list cv[0..M), one sorted run or one per count, and the
+            // unchanged sorted positions M..R-1
+            uint32_t rs[kLptRuns + 1];  // the runs' starts
+            uint32_t nr_ = 1;
+            rs[0] = 0;
+            if (any_uns) {
+#pragma unroll
+                for (uint32_t q = 1; q < kLptRuns; ++q) rs[q] = M;
+                for (uint64_t waves = ballot(wbrk != 0ull); waves; waves &= waves - 1ull) {
+                    const uint32_t u = first_lane(waves);
+                    for (uint64_t w = rdlane64(wbrk, u); w; w &= w - 1ull) {
+                        const uint32_t at = u * 64u + (uint32_t)__builtin_ctzll(w) + 1u;
+#pragma unroll
+                        for (uint32_t q = 1; q < kLptRuns; ++q)
+                            if (q == nr_) rs[q] = at;
+                        ++nr_;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (uint32_t q = 1; q < kLptRuns; ++q) rs[q] = M;
+            }
+            rs[kLptRuns] = M;
             if (i < R) {
-                const uint32_t pos = charged ? i + lower_bound_pair(sh.v[cur], sh.r[cur], M, R - M, a, r)
-                                             : (i - M) + lower_bound_pair(sh.cv, sh.cr, 0, M, v, r);
-                sh.v[nxt][pos] = charged ? a : v;
+                const double y = charged ? a : v;
+                uint32_t pos = charged ? lower_bound_pair(sh.v[cur], sh.r[cur], M, R - M, y, r) : i - M;
+#pragma unroll
+                for (uint32_t q = 0; q < kLptRuns; ++q) {
+                    if (rs[q] >= rs[q + 1]) continue;
+                    const bool own = charged && i >= rs[q] && i < rs[q + 1];
+                    pos += own ? i - rs[q] : lower_bound_pair(sh.cv, sh.cr, rs[q], rs[q + 1] - rs[q], y, r);
+                }
+                sh.v[nxt][pos] = y;
                 sh.r[nxt][pos] = r;
             } else {
                 sh.v[nxt][i] = INF;
@@ -1372,29 +1544,7 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
         } else {
             // bitonic sort of all N pairs (positions >= R hold (+inf, ~0) and stay last)
             v = wv_;
-            for (uint32_t kk = 2; kk <= N; kk <<= 1) {
-                for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-                    double pv;
-                    uint32_t pr;
-                    if (j >= 64) {
-                        sh.v[nxt][i] = v;
-                        sh.r[nxt][i] = r;
-                        __syncthreads();
-                        pv = sh.v[nxt][i ^ j];
-                        pr = sh.r[nxt][i ^ j];
-                        __syncthreads();
-                    } else {
-                        pv = __shfl_xor(v, (int)j, 64);
-                        pr = __shfl_xor(r, (int)j, 64);
-                    }
-                    const bool up = (i & kk) == 0, lower = (i & j) == 0;
-                    const bool pless = lt_pair(pv, pr, v, r) != 0;
-                    if (pless == (lower == up)) {
-                        v = pv;
-                        r = pr;
-                    }
-                }
-            }
+            block_sort_pairs<N>(v, r, sh.v[nxt], sh.r[nxt]);
             sh.v[nxt][i] = v;
             sh.r[nxt][i] = r;
         }

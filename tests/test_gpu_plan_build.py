@@ -30,3 +30,31 @@ def test_admission_edges(case):
     gp = Pipeline(wl)
     gp.step()
     compare_all(wl, gp, gp.host(), opipe.run(wl))
+
+
+# Long runs of equal counts over 65 to 1,024 destinations (LPT by epochs): runs shorter and
+# longer than 64 rounds, loads that cross powers of two inside a run, everything admitted
+# (loads from zero), whales that stay ahead of the rest, fractional charges.
+LPT = [
+    # seed, K, n, R, W, J, hot, hot_share, q, zipf
+    (311, 30_000, 90_000, 65, 400, 1, 2, 0.2, (1, 1), 0.7),
+    (312, 60_000, 150_000, 129, 300, 2, 0, 0.0, (2, 5), 0.3),
+    (313, 60_000, 400_000, 257, 256, 1, 5, 0.6, (1, 2), 0.2),
+    (314, 200_000, 300_000, 512, 300, 1, 0, 0.0, (1, 1), 0.1),
+    (315, 250_000, 900_000, 1024, 256, 1, 3, 0.5, (3, 7), 0.4),
+    (316, 70_000, 70_000, 1000, 512, 1, 0, 0.0, (1, 1), 0.0),
+    (317, 3000, 300_000, 700, 30, 3, 0, 0.0, (1, 9), 0.05),
+    (318, 40_000, 200_000, 30, 512, 2, 2, 0.3, (1, 1), 0.5),
+    (319, 40_000, 120_000, 64, 512, 1, 0, 0.0, (2, 3), 0.2),
+    (320, 9000, 200_000, 7, 512, 1, 1, 0.4, (1, 2), 0.1),
+]
+
+
+@pytest.mark.parametrize("case", LPT, ids=[f"r{c[3]}_{c[0]}" for c in LPT])
+def test_lpt_runs_of_equal_counts(case):
+    seed, K, n, R, W, J, hot, share, q, zipf = case
+    wl = wl_mod.small_random(seed, num_keys=K, n=n, R=R, Ws=[W], J=J, hot=hot, hot_share=share, qs=[q], zipf_s=zipf)
+    say(f"[case] lpt {seed} K={K} R={R} W={W}")
+    gp = Pipeline(wl)
+    gp.step()
+    compare_all(wl, gp, gp.host(), opipe.run(wl))
