@@ -608,6 +608,545 @@ __global__ __launch_bounds__(kSortBlock, kNpl <= 20 ? 8 : 1) void k_sort_window_
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// Rows of kWideKeys keys and more (C_max >= kWideCmax): the same order by many blocks per window. A row of a million counts kept one CU busy for 3.1 ms (its reads of 4 MB one after
+// another, then three radix passes over 524,288 entries), while the other 255 idled.
+//   k_wide_hist     histogram of the row over 1,728 bins that are exact below 128 and 1/64 of
+//                   an octave wide above; row sum and maximum
+//   k_wide_refine   three launches: where the bin of the C_max-th count is wider than one
+//                   count, histograms of its next 10, 10 and 5 bits (else they exit)
+//   k_wide_count    threshold t; per tile, the counts above it and equal to it
+//   k_wide_compact  kept entries in key order, at places from the tiles' prefix
+//   k_wide_sort     C_max <= 4,096: one block per window, radix passes in LDS
+//   k_wide_digits / k_wide_offsets / k_wide_scatter  else, per 11 bits of (max - count): digit
+//                   counts per tile of 4,096 entries, their prefix over the tiles, and the
+//                   stable scatter (passes past the range exit)
+// Scratch: the window's two buffers in the workspace and, before anything is known to be kept,
+// its rows of order and order_count. Every launch is a few microseconds of latency: cr_admit of 1,920
+// from 128,824 keys 326 -> 74 us, of 524,288 from 1,000,000 3,290 -> 365 us, 24 windows of
+// 128,824 244 -> 155 us.
+// ---------------------------------------------------------------------------------------
+constexpr uint32_t kWideCmax = 1024;   // smallest C_max whose buffers hold the bins
+// Smallest row. 100 windows of 50,000 keys took 99 us with a block each (they fill the chip by
+// themselves) and 162 us this way.
+constexpr uint32_t kWideKeys = 65536;
+constexpr uint32_t kWideBins = 1728;
+constexpr uint32_t kWideSub = 1024;    // bins of a refinement: 10 bits
+constexpr uint32_t kWideThreads = 256;
+constexpr uint32_t kWideSmall = 4096;  // largest C_max sorted by one block
+constexpr uint32_t kWideTile = 4096;   // entries per tile of a radix pass
+constexpr uint32_t kWideDigits = 2048; // 11 bits
+
+// Per window, at the start of its second buffer.
+struct WideHead {
+    uint32_t mx, t, take, M;  // largest count, threshold, entries equal to it that are kept, entries kept
+    uint32_t low[32];         // the last refinement's bins
+};
+
+// Keys per block: at most 129 blocks per row, and about 512 in all (the blocks of a row meet
+// in its bins' atomics: 24 rows of 128,824 keys 51 us with 63 blocks a row, 17 with 19).
+inline uint32_t wide_tile(uint32_t K, uint32_t NW)
+{
+    const uint64_t share = (uint64_t)K * NW / 512u;
+    const uint64_t t = share > K / 128u ? share : K / 128u;
+    const uint64_t u = ((t > K ? K : t) + 1023u) & ~1023ull;
+    return u < 2048u ? 2048u : (uint32_t)u;
+}
+
+__device__ __forceinline__ uint32_t wide_bin(uint32_t c)
+{
+    if (c < 64u) return c;
+    const uint32_t e = 31u - (uint32_t)__builtin_clz(c);
+    return 64u + (e - 6u) * 64u + ((c >> (e - 6u)) & 63u);
+}
+
+struct WideWin {
+    uint32_t* bins;           // [kWideBins], in the first buffer until it takes the entries
+    WideHead* head;
+    uint2* tiles;             // per tile {above, equal}, after the head
+    uint32_t *sub1, *sub2;    // [kWideSub] each, in order and order_count
+    uint2* b0;
+    uint32_t* counters;       // [tile][kWideDigits], then the totals: the second buffer again
+};
+
+__device__ __forceinline__ WideWin wide_win(uint2* buf, uint32_t* order, uint32_t* order_count, uint32_t Cmax, uint32_t w)
+{
+    uint2* b0 = buf + (uint64_t)w * 2u * Cmax;
+    uint2* b1 = b0 + Cmax;
+    return WideWin{reinterpret_cast<uint32_t*>(b0), reinterpret_cast<WideHead*>(b1),
+                   b1 + (sizeof(WideHead) + 7u) / 8u, order + (uint64_t)w * Cmax, order_count + (uint64_t)w * Cmax, b0,
+                   reinterpret_cast<uint32_t*>(b1 + (sizeof(WideHead) + 7u) / 8u)};
+}
+
+// From the top of `nbins` bins down: the bin in which the need-th entry lies, and how many of
+// it are needed. One wavefront; uniform results.
+__device__ __forceinline__ uint32_t wide_select(const uint32_t* __restrict__ bins, uint32_t nbins, uint32_t& need)
+{
+    const uint32_t lane = lane_id();
+    const uint32_t per = (nbins + 63u) / 64u;
+    uint32_t sum = 0;
+    for (uint32_t q = 0; q < per; ++q) {
+        const uint32_t d = lane * per + q;
+        sum += d < nbins ? bins[nbins - 1u - d] : 0u;
+    }
+    const uint32_t incl = wave_incl_scan_u32(sum);
+    const uint32_t own = first_lane(ballot(incl >= need));  // need <= the bins' total
+    uint32_t above = rdlane(incl - sum, own);
+    for (uint32_t q = 0;; ++q) {
+        const uint32_t b = nbins - 1u - (own * per + q);
+        const uint32_t h = bins[b];
+        if (above + h >= need) {
+            need -= above;
+            return b;
+        }
+        above += h;
+    }
+}
+
+// What the levels known so far say of the threshold: counts in [base, base + 2^bits) hold it,
+// with `need` entries kept of them (bits = 0: the threshold is base). One wavefront.
+struct WideSel {
+    uint32_t base, bits, need, M;
+};
+
+__device__ __forceinline__ WideSel wide_threshold(const WideWin& ww, uint32_t Cmax, int levels)
+{
+    const uint32_t lane = lane_id();
+    uint32_t nnz = 0;
+    for (uint32_t b = 1u + lane; b < kWideBins; b += 64u) nnz += ww.bins[b];
+    nnz = rdlane(wave_incl_scan_u32(nnz), 63u);
+    if (nnz <= Cmax) return WideSel{0u, 0u, 0u, nnz};  // every nonzero key
+    WideSel s{0u, 0u, Cmax, Cmax};
+    const uint32_t b = wide_select(ww.bins, kWideBins, s.need);
+    if (b < 128u) {
+        s.base = b;
+        return s;
+    }
+    s.bits = (b - 64u) / 64u;
+    s.base = (64u | (b & 63u)) << s.bits;
+    for (int l = 1; l < levels && s.bits; ++l) {
+        const uint32_t rest = s.bits > 10u && l < 3 ? s.bits - 10u : 0u;
+        const uint32_t d = wide_select(l == 1 ? ww.sub1 : (l == 2 ? ww.sub2 : ww.head->low), 1u << (s.bits - rest), s.need);
+        s.base += d << rest;
+        s.bits = rest;
+    }
+    return s;
+}
+
+__global__ __launch_bounds__(kWideThreads) void k_wide_zero(uint32_t Cmax, uint32_t* __restrict__ order,
+                                                            uint32_t* __restrict__ order_count, uint2* __restrict__ buf,
+                                                            uint64_t* __restrict__ row_sum)
+{
+    const uint32_t w = blockIdx.x;
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    for (uint32_t b = threadIdx.x; b < kWideBins; b += kWideThreads) ww.bins[b] = 0u;
+    for (uint32_t b = threadIdx.x; b < kWideSub; b += kWideThreads) {
+        ww.sub1[b] = 0u;
+        ww.sub2[b] = 0u;
+    }
+    uint32_t* h = reinterpret_cast<uint32_t*>(ww.head);
+    if (threadIdx.x < sizeof(WideHead) / 4u) h[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) row_sum[w] = 0ull;
+}
+
+__global__ __launch_bounds__(kWideThreads) void k_wide_hist(const uint32_t* __restrict__ counts, uint32_t K, uint32_t tile,
+                                                            uint32_t Cmax, uint32_t* __restrict__ order,
+                                                            uint32_t* __restrict__ order_count, uint2* __restrict__ buf,
+                                                            uint64_t* __restrict__ row_sum)
+{
+    __shared__ uint32_t s_h[kWideBins];
+    const uint32_t w = blockIdx.y, tid = threadIdx.x;
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    const uint32_t* __restrict__ row = counts + (uint64_t)w * K;
+    const bool vec = (((uintptr_t)row) & 15u) == 0;
+    for (uint32_t b = tid; b < kWideBins; b += kWideThreads) s_h[b] = 0u;
+    __syncthreads();
+    const uint32_t lo = blockIdx.x * tile, hi = K - lo < tile ? K : lo + tile;  // lo < K
+    uint32_t mx = 0, n1 = 0, n2 = 0, n3 = 0;  // the bulk of a long tail without LDS atomics
+    uint64_t sum = 0;
+    for (uint32_t b = lo + 4u * tid; b < hi; b += 4u * kWideThreads) {
+        const uint4 q = load4(row, hi, b, vec);
+        const uint32_t cs[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t c = cs[u];
+            n1 += c == 1u;
+            n2 += c == 2u;
+            n3 += c == 3u;
+            mx = c > mx ? c : mx;
+            sum += c;
+            if (c >= 4u) atomicAdd(&s_h[wide_bin(c)], 1u);
+        }
+    }
+    n1 = wave_sum_u32(n1);
+    n2 = wave_sum_u32(n2);
+    n3 = wave_sum_u32(n3);
+    mx = wave_max_u32(mx);
+    sum = wave_sum_u64(sum);
+    if (lane_id() == 0) {
+        if (n1) atomicAdd(&s_h[1], n1);
+        if (n2) atomicAdd(&s_h[2], n2);
+        if (n3) atomicAdd(&s_h[3], n3);
+        if (mx) atomicMax(&ww.head->mx, mx);
+        if (sum) atomicAdd(reinterpret_cast<unsigned long long*>(row_sum + w), (unsigned long long)sum);
+    }
+    __syncthreads();
+    for (uint32_t b = 1u + tid; b < kWideBins; b += kWideThreads)
+        if (s_h[b]) atomicAdd(&ww.bins[b], s_h[b]);
+}
+
+template <int kLevel>
+__global__ __launch_bounds__(kWideThreads) void k_wide_refine(const uint32_t* __restrict__ counts, uint32_t K,
+                                                              uint32_t tile, uint32_t Cmax, uint32_t* __restrict__ order,
+                                                              uint32_t* __restrict__ order_count, uint2* __restrict__ buf)
+{
+    __shared__ uint32_t s_h[kWideSub];
+    __shared__ WideSel s_sel;
+    const uint32_t w = blockIdx.y, tid = threadIdx.x;
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    if (tid < 64u) {
+        const WideSel s = wide_threshold(ww, Cmax, kLevel);
+        if (tid == 0) s_sel = s;
+    }
+    for (uint32_t b = tid; b < kWideSub; b += kWideThreads) s_h[b] = 0u;
+    __syncthreads();
+    const WideSel s = s_sel;
+    if (s.bits == 0u) return;
+    const uint32_t rest = s.bits > 10u && kLevel < 3 ? s.bits - 10u : 0u;
+    const uint32_t* __restrict__ row = counts + (uint64_t)w * K;
+    const uint32_t lo = blockIdx.x * tile, hi = K - lo < tile ? K : lo + tile;
+    for (uint32_t b = lo + tid; b < hi; b += kWideThreads) {
+        const uint32_t u = row[b] - s.base;  // wraps below base
+        if (u >> s.bits == 0u) atomicAdd(&s_h[u >> rest], 1u);
+    }
+    __syncthreads();
+    uint32_t* __restrict__ out = kLevel == 1 ? ww.sub1 : (kLevel == 2 ? ww.sub2 : ww.head->low);
+    for (uint32_t b = tid; b < 1u << (s.bits - rest); b += kWideThreads)
+        if (s_h[b]) atomicAdd(&out[b], s_h[b]);
+}
+
+__global__ __launch_bounds__(kWideThreads) void k_wide_count(const uint32_t* __restrict__ counts, uint32_t K, uint32_t tile,
+                                                             uint32_t Cmax, uint32_t* __restrict__ order,
+                                                             uint32_t* __restrict__ order_count,
+                                                             uint32_t* __restrict__ n_order, uint2* __restrict__ buf)
+{
+    __shared__ WideSel s_sel;
+    __shared__ uint32_t s_gt, s_eq;
+    const uint32_t w = blockIdx.y, tid = threadIdx.x;
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    if (tid < 64u) {
+        const WideSel s = wide_threshold(ww, Cmax, 4);
+        if (tid == 0) {
+            s_sel = s;
+            s_gt = 0;
+            s_eq = 0;
+        }
+    }
+    __syncthreads();
+    const WideSel s = s_sel;
+    const uint32_t* __restrict__ row = counts + (uint64_t)w * K;
+    const bool vec = (((uintptr_t)row) & 15u) == 0;
+    const uint32_t lo = blockIdx.x * tile, hi = K - lo < tile ? K : lo + tile;
+    uint32_t gt = 0, eq = 0;
+    for (uint32_t b = lo + 4u * tid; b < hi; b += 4u * kWideThreads) {
+        const uint4 q = load4(row, hi, b, vec);
+        gt += (q.x > s.base) + (q.y > s.base) + (q.z > s.base) + (q.w > s.base);
+        eq += (q.x == s.base) + (q.y == s.base) + (q.z == s.base) + (q.w == s.base);  // past hi only for base 0: none kept
+    }
+    gt = wave_sum_u32(gt);
+    eq = wave_sum_u32(eq);
+    if (lane_id() == 0) {
+        atomicAdd(&s_gt, gt);
+        atomicAdd(&s_eq, eq);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        ww.tiles[blockIdx.x] = make_uint2(s_gt, s_eq);
+        if (blockIdx.x == 0) {
+            ww.head->t = s.base;
+            ww.head->take = s.need;
+            ww.head->M = s.M;
+            n_order[w] = s.M;
+        }
+    }
+}
+
+// 11-bit radix passes that the range of the kept counts takes.
+__device__ __forceinline__ uint32_t wide_passes(const WideHead& h)
+{
+    const uint32_t range = h.M ? h.mx - (h.t ? h.t : 1u) : 0u;
+    const uint32_t bits = range ? 32u - (uint32_t)__builtin_clz(range) : 0u;
+    return (bits + 10u) / 11u;
+}
+
+// Kept entries in key order into the first buffer, or, for an even number of radix passes by
+// many blocks, into order and order_count, where the last pass has to end.
+__global__ __launch_bounds__(kWideThreads) void k_wide_compact(const uint32_t* __restrict__ counts, uint32_t K, uint32_t tile,
+                                                               uint32_t Cmax, uint32_t* __restrict__ order,
+                                                               uint32_t* __restrict__ order_count, uint2* __restrict__ buf)
+{
+    constexpr uint32_t kWaves = kWideThreads / 64u;
+    __shared__ uint32_t s_w[kWaves][2];
+    const uint32_t w = blockIdx.y, lane = lane_id(), wv = wave_in_block();
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    const uint32_t t = ww.head->t, take = ww.head->take, M = ww.head->M;
+    if (M == 0) return;
+    const bool soa = Cmax > kWideSmall && (wide_passes(*ww.head) & 1u) == 0u;
+    uint32_t gt0 = 0, eq0 = 0;  // in the tiles before
+    for (uint32_t q = lane; q < blockIdx.x; q += 64u) {
+        const uint2 c = ww.tiles[q];
+        gt0 += c.x;
+        eq0 += c.y;
+    }
+    gt0 = wave_sum_u32(gt0);
+    eq0 = wave_sum_u32(eq0);
+    const uint32_t* __restrict__ row = counts + (uint64_t)w * K;
+    const uint32_t lo = blockIdx.x * tile, hi = K - lo < tile ? K : lo + tile;
+    const uint32_t span = tile / kWaves;  // a multiple of 64
+    const uint32_t a = lo + wv * span < hi ? lo + wv * span : hi, z = a + span < hi ? a + span : hi;
+    uint32_t gt = 0, eq = 0;
+    for (uint32_t b = a + lane; b < z; b += 64u) {
+        const uint32_t c = row[b];
+        gt += c > t;
+        eq += c == t;
+    }
+    gt = wave_sum_u32(gt);
+    eq = wave_sum_u32(eq);
+    if (lane == 0) {
+        s_w[wv][0] = gt;
+        s_w[wv][1] = eq;
+    }
+    __syncthreads();
+    for (uint32_t q = 0; q < wv; ++q) {
+        gt0 += s_w[q][0];
+        eq0 += s_w[q][1];
+    }
+    uint32_t at = gt0 + (eq0 < take ? eq0 : take);
+    for (uint32_t base = a; base < z; base += 64u) {
+        const uint32_t b = base + lane;
+        const uint32_t c = b < z ? row[b] : 0u;
+        const uint64_t meq = ballot(b < z && c == t);
+        const bool sel = b < z && (c > t || (c == t && eq0 + (uint32_t)__popcll(meq & lanemask_lt()) < take));
+        const uint64_t ms = ballot(sel);
+        const uint32_t pos = at + (uint32_t)__popcll(ms & lanemask_lt());
+        if (sel && pos < M) {
+            if (soa) {
+                order[(uint64_t)w * Cmax + pos] = b;
+                order_count[(uint64_t)w * Cmax + pos] = c;
+            } else {
+                ww.b0[pos] = make_uint2(c, b);
+            }
+        }
+        at += (uint32_t)__popcll(ms);
+        eq0 += (uint32_t)__popcll(meq);
+    }
+}
+
+// C_max <= kWideSmall: stable LSD radix sort by (max - count) in LDS, as in k_sort_window_reg.
+__global__ __launch_bounds__(kSortBlock) void k_wide_sort(uint32_t Cmax, uint32_t* __restrict__ order,
+                                                          uint32_t* __restrict__ order_count, uint2* __restrict__ buf)
+{
+    extern __shared__ uint2 s_ent[];  // [2][Cmax]
+    __shared__ uint32_t s_hist[kSortNW][256];
+    __shared__ uint32_t s_scan[16];
+    const uint32_t w = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wv = wave_in_block();
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    const uint32_t M = ww.head->M, mx = ww.head->mx, t = ww.head->t;
+    if (M == 0) return;
+    for (uint32_t e = tid; e < M; e += kSortBlock) s_ent[e] = ww.b0[e];
+    __syncthreads();
+    const uint32_t range = mx - t;
+    const uint32_t bits = range ? 32u - (uint32_t)__builtin_clz(range) : 0u;
+    const uint32_t passes = (bits + 7u) / 8u;
+    const uint32_t espan = (((M + kSortNW - 1) / kSortNW) + 63u) & ~63u;
+    const uint32_t elo = wv * espan < M ? wv * espan : M, ehi = elo + espan < M ? elo + espan : M;
+    uint2* src = s_ent;
+    uint2* dst = s_ent + Cmax;
+    for (uint32_t pass = 0; pass < passes; ++pass) {
+        const uint32_t shift = 8u * pass;
+        for (uint32_t d = lane; d < 256; d += 64) s_hist[wv][d] = 0;
+        for (uint32_t e = elo + lane; e < ehi; e += 64) atomicAdd(&s_hist[wv][((mx - src[e].x) >> shift) & 255u], 1u);
+        __syncthreads();
+        {  // offsets in (digit, wavefront) order: thread tid owns digit tid / 4, waves 4 (tid % 4) ..
+            const uint32_t d = tid >> 2, x0 = (tid & 3u) * 4u;
+            uint32_t hv[4], hs = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                hv[q] = s_hist[x0 + q][d];
+                hs += hv[q];
+            }
+            uint32_t tot;
+            uint32_t ex = block_exscan_u32(hs, s_scan, &tot);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                s_hist[x0 + q][d] = ex;
+                ex += hv[q];
+            }
+        }
+        __syncthreads();
+        for (uint32_t e0 = elo; e0 < ehi; e0 += 64) {
+            const uint32_t e = e0 + lane;
+            const bool valid = e < ehi;
+            const uint2 kv = valid ? src[e] : make_uint2(0u, 0u);
+            const uint32_t d = valid ? ((mx - kv.x) >> shift) & 255u : 0u;
+            uint64_t peers = ballot(valid);
+#pragma unroll
+            for (int bit = 0; bit < 8; ++bit) {
+                const bool on = (d >> bit) & 1u;
+                const uint64_t bb = ballot(on);
+                peers &= on ? bb : ~bb;
+            }
+            const uint32_t rk = (uint32_t)__popcll(peers & lanemask_lt());
+            const uint32_t at = valid ? s_hist[wv][d] + rk : 0u;
+            if (valid && at < M) dst[at] = kv;
+            if (valid && rk == 0) atomicAdd(&s_hist[wv][d], (uint32_t)__popcll(peers));
+        }
+        __syncthreads();
+        uint2* tmp = src;
+        src = dst;
+        dst = tmp;
+    }
+    for (uint32_t e = tid; e < M; e += kSortBlock) {
+        ww.sub1[e] = src[e].y;  // the window's rows of order and order_count
+        ww.sub2[e] = src[e].x;
+    }
+}
+
+// One radix pass: entries of the pass's source, by index.
+__device__ __forceinline__ uint2 wide_entry(const WideWin& ww, bool from_b0, uint32_t e)
+{
+    return from_b0 ? ww.b0[e] : make_uint2(ww.sub2[e], ww.sub1[e]);
+}
+
+__global__ __launch_bounds__(kWideThreads) void k_wide_digits(uint32_t Cmax, uint32_t pass, uint32_t* __restrict__ order,
+                                                              uint32_t* __restrict__ order_count, uint2* __restrict__ buf)
+{
+    __shared__ uint32_t s_h[kWideDigits];
+    const uint32_t w = blockIdx.y, tid = threadIdx.x;
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    const uint32_t M = ww.head->M, mx = ww.head->mx, np = wide_passes(*ww.head);
+    const uint32_t e0 = blockIdx.x * kWideTile;
+    if (pass >= np || e0 >= M) return;
+    const bool from_b0 = ((np - pass) & 1u) != 0u;  // the last pass ends in order and order_count
+    for (uint32_t d = tid; d < kWideDigits; d += kWideThreads) s_h[d] = 0u;
+    __syncthreads();
+    const uint32_t e1 = M - e0 < kWideTile ? M : e0 + kWideTile;
+    for (uint32_t e = e0 + tid; e < e1; e += kWideThreads)
+        atomicAdd(&s_h[((mx - (from_b0 ? ww.b0[e].x : ww.sub2[e])) >> (11u * pass)) & (kWideDigits - 1u)], 1u);
+    __syncthreads();
+    uint32_t* __restrict__ out = ww.counters + (uint64_t)blockIdx.x * kWideDigits;
+    for (uint32_t d = tid; d < kWideDigits; d += kWideThreads) out[d] = s_h[d];
+}
+
+// Per digit, the exclusive prefix of its tile counts in place; the total after the tiles.
+__global__ __launch_bounds__(64) void k_wide_offsets(uint32_t Cmax, uint32_t pass, uint32_t* __restrict__ order,
+                                                     uint32_t* __restrict__ order_count, uint2* __restrict__ buf)
+{
+    const uint32_t w = blockIdx.y, d = blockIdx.x * 64u + threadIdx.x;
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    if (pass >= wide_passes(*ww.head)) return;
+    const uint32_t nt = (ww.head->M + kWideTile - 1u) / kWideTile;
+    uint32_t* __restrict__ c = ww.counters + d;
+    uint32_t run = 0;
+    for (uint32_t q0 = 0; q0 < nt; q0 += 8u) {
+        uint32_t v[8];
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) v[q] = q0 + q < nt ? c[(uint64_t)(q0 + q) * kWideDigits] : 0u;
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) {
+            if (q0 + q < nt) c[(uint64_t)(q0 + q) * kWideDigits] = run;
+            run += v[q];
+        }
+    }
+    c[(uint64_t)nt * kWideDigits] = run;
+}
+
+// Stable scatter of a tile: every wavefront ranks its 1,024 entries in order, 64 at a time. The
+// lanes of one digit find each other in LDS (a tag byte per digit names a representative lane,
+// whose 64-bit mask collects them), and a counter per wavefront and digit carries the rank on.
+__global__ __launch_bounds__(kWideThreads) void k_wide_scatter(uint32_t Cmax, uint32_t pass, uint32_t* __restrict__ order,
+                                                               uint32_t* __restrict__ order_count, uint2* __restrict__ buf)
+{
+    constexpr uint32_t kWaves = kWideThreads / 64u, kChunks = kWideTile / kWideThreads;
+    __shared__ uint32_t s_cnt[kWaves][kWideDigits];
+    __shared__ uint8_t s_tag[kWaves][kWideDigits];
+    __shared__ unsigned long long s_peer[kWaves][64];
+    __shared__ uint32_t s_scan[16];
+    const uint32_t w = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wv = wave_in_block();
+    const WideWin ww = wide_win(buf, order, order_count, Cmax, w);
+    const uint32_t M = ww.head->M, mx = ww.head->mx, np = wide_passes(*ww.head);
+    const uint32_t e0 = blockIdx.x * kWideTile;
+    if (pass >= np || e0 >= M) return;
+    const bool from_b0 = ((np - pass) & 1u) != 0u;
+    for (uint32_t d = lane; d < kWideDigits; d += 64u) s_cnt[wv][d] = 0u;
+    const uint32_t a = e0 + wv * (kWideTile / kWaves);
+    uint2 kv[kChunks];
+    uint32_t dr[kChunks];  // digit | rank among the wavefront's entries of it << 16
+#pragma unroll
+    for (uint32_t m = 0; m < kChunks; ++m) {
+        const uint32_t e = a + 64u * m + lane;
+        kv[m] = e < M ? wide_entry(ww, from_b0, e) : make_uint2(0u, 0u);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t m = 0; m < kChunks; ++m) {
+        const bool valid = a + 64u * m + lane < M;
+        const uint32_t d = valid ? ((mx - kv[m].x) >> (11u * pass)) & (kWideDigits - 1u) : 0u;
+        s_peer[wv][lane] = 0ull;
+        if (valid) s_tag[wv][d] = (uint8_t)lane;
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t rep = valid ? s_tag[wv][d] : lane;
+        if (valid) atomicOr(&s_peer[wv][rep], 1ull << lane);
+        __builtin_amdgcn_wave_barrier();
+        const uint64_t peers = valid ? (uint64_t)s_peer[wv][rep] : 0ull;
+        const uint32_t rk = (uint32_t)__popcll(peers & lanemask_lt());
+        uint32_t old = 0;
+        if (valid && rk == 0) old = atomicAdd(&s_cnt[wv][d], (uint32_t)__popcll(peers));
+        const uint32_t leader = valid ? (uint32_t)__builtin_ctzll(peers) : lane;
+        old = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(leader << 2), (int)old);
+        dr[m] = d | ((old + rk) << 16);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    // first output position of every (digit, wavefront): digits before, tiles before, wavefronts before
+    const uint32_t nt = (M + kWideTile - 1u) / kWideTile;
+    const uint32_t* __restrict__ tot = ww.counters + (uint64_t)nt * kWideDigits;
+    const uint32_t* __restrict__ off = ww.counters + (uint64_t)blockIdx.x * kWideDigits;
+    constexpr uint32_t kPer = kWideDigits / kWideThreads;
+    uint32_t tv[kPer], sum = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        tv[q] = tot[kPer * tid + q];
+        sum += tv[q];
+    }
+    uint32_t all;
+    uint32_t ex = block_exscan_u32(sum, s_scan, &all);
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        const uint32_t d = kPer * tid + q;
+        uint32_t at = ex + off[d];
+        for (uint32_t u = 0; u < kWaves; ++u) {
+            const uint32_t c = s_cnt[u][d];
+            s_cnt[u][d] = at;
+            at += c;
+        }
+        ex += tv[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t m = 0; m < kChunks; ++m) {
+        if (a + 64u * m + lane >= M) continue;
+        const uint32_t at = s_cnt[wv][dr[m] & 0xFFFFu] + (dr[m] >> 16);
+        if (at >= M) continue;
+        if (from_b0) {
+            ww.sub1[at] = kv[m].y;
+            ww.sub2[at] = kv[m].x;
+        } else {
+            ww.b0[at] = kv[m];
+        }
+    }
+}
+
 // One block per plan: Eq. 1, the prefix admission and the plan's key index (bit b % 64 of word
 // b / 64 set for every admitted key b, and per word the key rank of its first admitted key, an
 // exclusive scan of the word popcounts; built in LDS when the words fit, else with global
@@ -1896,6 +2435,31 @@ extern "C" cr_status cr_admit(const uint32_t* counts, const cr_plan_set* plans, 
         else if (K <= 1024u * 20u) CR_SORT_REG(20);
         else CR_SORT_REG(32);
 #undef CR_SORT_REG
+    } else if (K >= kWideKeys && K <= 0xFFF00000u && cmax >= kWideCmax && plans->num_windows <= 65535u) {
+        const uint32_t NW = plans->num_windows, tile = wide_tile(K, NW);
+        const dim3 tiles((K + tile - 1u) / tile, NW), th(kWideThreads);
+        uint32_t *ord = plans->order, *ocnt = plans->order_count;
+        hipLaunchKernelGGL(k_wide_zero, dim3(NW), th, 0, st, cmax, ord, ocnt, buf, row_sum);
+        hipLaunchKernelGGL(k_wide_hist, tiles, th, 0, st, counts, K, tile, cmax, ord, ocnt, buf, row_sum);
+        hipLaunchKernelGGL(k_wide_refine<1>, tiles, th, 0, st, counts, K, tile, cmax, ord, ocnt, buf);
+        hipLaunchKernelGGL(k_wide_refine<2>, tiles, th, 0, st, counts, K, tile, cmax, ord, ocnt, buf);
+        hipLaunchKernelGGL(k_wide_refine<3>, tiles, th, 0, st, counts, K, tile, cmax, ord, ocnt, buf);
+        hipLaunchKernelGGL(k_wide_count, tiles, th, 0, st, counts, K, tile, cmax, ord, ocnt, plans->n_order, buf);
+        hipLaunchKernelGGL(k_wide_compact, tiles, th, 0, st, counts, K, tile, cmax, ord, ocnt, buf);
+        if (cmax <= kWideSmall) {
+            const size_t lds = (size_t)cmax * 16u;
+            if (hipFuncSetAttribute((const void*)k_wide_sort, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+                hipSuccess)
+                return CR_EHIP;
+            hipLaunchKernelGGL(k_wide_sort, dim3(NW), dim3(kSortBlock), lds, st, cmax, ord, ocnt, buf);
+        } else {
+            const dim3 et((cmax + kWideTile - 1u) / kWideTile, NW);
+            for (uint32_t pass = 0; pass < 3u; ++pass) {
+                hipLaunchKernelGGL(k_wide_digits, et, th, 0, st, cmax, pass, ord, ocnt, buf);
+                hipLaunchKernelGGL(k_wide_offsets, dim3(kWideDigits / 64u, NW), dim3(64), 0, st, cmax, pass, ord, ocnt, buf);
+                hipLaunchKernelGGL(k_wide_scatter, et, th, 0, st, cmax, pass, ord, ocnt, buf);
+            }
+        }
     } else if ((uint64_t)plans->num_keys * 4u <= kSortLdsRowBytes) {
         const uint32_t lds = plans->num_keys * 4u;
         if (hipFuncSetAttribute((const void*)k_sort_window<true>, hipFuncAttributeMaxDynamicSharedMemorySize,

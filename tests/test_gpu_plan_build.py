@@ -3,8 +3,10 @@ around the two block sizes, key indexes in LDS and (beyond 1,179,648 keys) in gl
 heads of keys with k > 1 longer than a block or cut inside one, windows admitted whole."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import pipeline as opipe
+from paper_2608_19677_amd import binding as B
 from paper_2608_19677_amd import workload as wl_mod
 from paper_2608_19677_amd.pipeline import Pipeline
 
@@ -58,3 +60,50 @@ def test_lpt_runs_of_equal_counts(case):
     gp = Pipeline(wl)
     gp.step()
     compare_all(wl, gp, gp.host(), opipe.run(wl))
+
+
+# The window order of rows sorted by many blocks (K >= 65,536, budgets from 1,024 slots): thresholds
+# inside the exact bins and inside refined ones, ties cut by key, rows with fewer nonzero keys
+# than slots, odd row lengths, budgets sorted by one block and by 1 to 3 radix passes.
+WIDE = [
+    # K, R, W, windows, kind
+    (65_535, 64, 16, 3, "zipf"), (65_537, 32, 64, 5, "zipf"), (128_824, 30, 64, 2, "big"), (70_000, 30, 64, 4, "flat"),
+    (66_666, 64, 64, 2, "few"), (65_536, 128, 64, 2, "zipf"), (100_003, 64, 300, 40, "big"), (90_000, 100, 100, 1, "huge"),
+    (70_000, 200, 200, 2, "flat"), (262_147, 1024, 128, 1, "zipf"), (66_001, 33, 125, 2, "huge"), (80_001, 64, 65, 1, "one"),
+    (200_000, 7, 100, 2, "big"),
+]
+
+
+@pytest.mark.parametrize("K,R,W,NW,kind", WIDE, ids=[f"{c[4]}_{c[0]}_{c[1] * c[2]}" for c in WIDE])
+def test_window_order_of_wide_rows(K, R, W, NW, kind):
+    rng = np.random.default_rng(K + R)
+    if kind == "zipf":
+        rows = rng.poisson(3000.0 * (1 + rng.permutation(K)) ** -0.7, (NW, K))
+    elif kind == "big":      # thresholds in the thousands: one or two refinements
+        rows = rng.integers(2000, 90_000, (NW, K))
+    elif kind == "huge":     # up to 2^32 - 1: all three
+        rows = rng.integers(1, 1 << 32, (NW, K))
+    elif kind == "flat":     # ties everywhere
+        rows = rng.integers(5, 8, (NW, K))
+    elif kind == "few":      # fewer nonzero keys than slots, an empty row
+        rows = np.where(rng.random((NW, K)) < 0.02, rng.integers(1, 500, (NW, K)), 0)
+        rows[-1] = 0
+    else:                    # one value
+        rows = np.full((NW, K), 70_001)
+    rows = rows.astype(np.uint32)
+    say(f"[case] wide rows {kind} K={K} Cmax={R * W}")
+    specs = [(w, W, B.CR_WINDOW_SUM, 1, 1, B.CR_PLAN_AFFINITY, 0) for w in range(NW)]
+    ps = B.PlanSet(specs, 1, R, W, K, NW, "cuda")
+    ws = torch.empty(B.cr_admit_workspace_bytes(NW, R, W), dtype=torch.uint8, device="cuda")
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    B.cr_admit(torch.from_numpy(rows.view(np.int32)).cuda(), ps.c, ws, err)
+    torch.cuda.synchronize()
+    for w in range(NW):
+        keys = np.nonzero(rows[w])[0]
+        keys = keys[np.lexsort((keys, -rows[w][keys].astype(np.int64)))][: R * W]
+        m = int(ps.n_order[w])
+        assert m == len(keys) == int(ps.num_admitted[w])
+        np.testing.assert_array_equal(ps.order[w, :m].cpu().numpy().view(np.uint32), keys)
+        np.testing.assert_array_equal(ps.order_count[w, :m].cpu().numpy().view(np.uint32), rows[w][keys])
+        assert int(ps.cold[w]) == int(rows[w].astype(np.uint64).sum() - rows[w][keys].astype(np.uint64).sum())
+    assert int(err) == 0
