@@ -1,14 +1,21 @@
 // Rate counting per control interval (Algorithm 1 input "rates").
 //
 // HBM-bound stream: every request's key is read once (4 B per request) and every
-// counts row is written once. Three launch shapes, chosen on the host:
+// counts row is written once. Launch shapes, chosen on the host:
 //   owner  many intervals, key space fits LDS: one block owns whole intervals, counts
 //          them in an LDS histogram and writes each row with plain coalesced stores
 //          (no zeroing pass, no global atomics);
 //   tiled  few long intervals: rows are zeroed, blocks count tiles of requests into
-//          LDS-private bins (u32, or two u16 per word for up to 2x more keys with tiles
-//          of at most 65,535 requests) and merge nonzero bins with one atomic each;
-//   global key spaces beyond LDS: rows are zeroed and each request adds one atomic.
+//          LDS-private bins and merge nonzero bins with one atomic each;
+//   ranges key spaces beyond LDS, up to 32 ranges that fit: a block per (range, interval,
+//          part of a long interval) counts its range's keys in LDS;
+//   global larger key spaces: rows are zeroed and each request adds one atomic.
+// A device-scope atomic per request costs about 0.12 ns of the whole chip, and far more where
+// a Zipf head puts millions of them on one address. Against one per request: 4e6 requests over
+// 24 intervals of 128,824 keys 527 -> 45 us, 2e7 over 5 of 200,000 keys 7,420 -> 134 us, 5e6
+// over 10 of 1,000,000 keys 470 -> 113 us; against 16-bit bins of the whole key space per tile
+// of 64,512 requests: 5e7 over 100 intervals of 50,000 keys 189 -> 148 us (its hot keys' LDS
+// conflicts now bound it), 1e6 over 200 of 45,000 92 -> 29 us.
 #include "cr_common.h"
 
 namespace cr {
@@ -16,7 +23,7 @@ namespace {
 
 constexpr int kCountThreads = 1024;
 
-enum Bins { kBinsNone = 0, kBinsU32 = 1, kBinsU16 = 2 };
+enum Bins { kBinsNone = 0, kBinsU32 = 1, kBinsRange = 2 };
 
 __global__ void k_zero(uint32_t* __restrict__ p, uint64_t n)
 {
@@ -25,11 +32,14 @@ __global__ void k_zero(uint32_t* __restrict__ p, uint64_t n)
 }
 
 template <int kBins>
-__device__ __forceinline__ void add_key(uint32_t b, uint32_t K, uint32_t* hist, uint32_t* row, bool& bad)
+__device__ __forceinline__ void add_key(uint32_t b, uint32_t K, uint32_t* hist, uint32_t* row, bool& bad, uint32_t b0,
+                                        uint32_t nb)
 {
-    if (b < K) {
+    if (kBins == kBinsRange) {  // the keys b0 .. b0 + nb - 1 only
+        if (b - b0 < nb) atomicAdd(&hist[b - b0], 1u);
+        bad |= b >= K;
+    } else if (b < K) {
         if (kBins == kBinsU32) atomicAdd(&hist[b], 1u);
-        else if (kBins == kBinsU16) atomicAdd(&hist[b >> 1], 1u << ((b & 1u) << 4));
         else atomicAdd(&row[b], 1u);
     } else {
         bad = true;
@@ -39,13 +49,13 @@ __device__ __forceinline__ void add_key(uint32_t b, uint32_t K, uint32_t* hist, 
 // Count keys[s, e) into hist (or row); head to a 16-byte boundary, uint4 body, tail.
 template <int kBins>
 __device__ __forceinline__ void count_range(const uint32_t* __restrict__ keys, uint64_t s, uint64_t e, uint32_t K,
-                                            uint32_t* hist, uint32_t* row, bool& bad)
+                                            uint32_t* hist, uint32_t* row, bool& bad, uint32_t b0 = 0, uint32_t nb = 0)
 {
     const uint32_t tid = threadIdx.x, bd = blockDim.x;
     const uint64_t mis = (((uintptr_t)keys >> 2) + s) & 3u;  // keys is 4-byte aligned
     uint64_t a = s + ((4u - mis) & 3u);
     if (a > e) a = e;
-    for (uint64_t i = s + tid; i < a; i += bd) add_key<kBins>(keys[i], K, hist, row, bad);
+    for (uint64_t i = s + tid; i < a; i += bd) add_key<kBins>(keys[i], K, hist, row, bad, b0, nb);
     const uint64_t nv = (e - a) >> 2;
     const uint4* __restrict__ k4 = reinterpret_cast<const uint4*>(keys + a);
     uint64_t v = tid;
@@ -54,16 +64,16 @@ __device__ __forceinline__ void count_range(const uint32_t* __restrict__ keys, u
         const uint32_t bs[16] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w,
                                  q2.x, q2.y, q2.z, q2.w, q3.x, q3.y, q3.z, q3.w};
 #pragma unroll
-        for (int t = 0; t < 16; ++t) add_key<kBins>(bs[t], K, hist, row, bad);
+        for (int t = 0; t < 16; ++t) add_key<kBins>(bs[t], K, hist, row, bad, b0, nb);
     }
     for (; v < nv; v += bd) {
         const uint4 q = k4[v];
-        add_key<kBins>(q.x, K, hist, row, bad);
-        add_key<kBins>(q.y, K, hist, row, bad);
-        add_key<kBins>(q.z, K, hist, row, bad);
-        add_key<kBins>(q.w, K, hist, row, bad);
+        add_key<kBins>(q.x, K, hist, row, bad, b0, nb);
+        add_key<kBins>(q.y, K, hist, row, bad, b0, nb);
+        add_key<kBins>(q.z, K, hist, row, bad, b0, nb);
+        add_key<kBins>(q.w, K, hist, row, bad, b0, nb);
     }
-    for (uint64_t i = a + (nv << 2) + tid; i < e; i += bd) add_key<kBins>(keys[i], K, hist, row, bad);
+    for (uint64_t i = a + (nv << 2) + tid; i < e; i += bd) add_key<kBins>(keys[i], K, hist, row, bad, b0, nb);
 }
 
 __global__ __launch_bounds__(kCountThreads) void k_count_owner(const uint32_t* __restrict__ keys, uint64_t n,
@@ -89,6 +99,50 @@ __global__ __launch_bounds__(kCountThreads) void k_count_owner(const uint32_t* _
     if (bad) atomicOr(err, CR_ERR_KEY_RANGE);
 }
 
+// Key spaces beyond LDS: block (range u, interval j, part s) reads part s of interval j and counts
+// the keys of range u in LDS. An interval of up to kRangePart requests is one part, whose block
+// owns its piece of the row and stores it; the parts of a longer one add their nonzero bins to
+// the zeroed row. Every key is read once per range (from the L2 after the first), which costs
+// far less than a device-scope atomic per request does.
+constexpr uint32_t kMaxRanges = 32;
+constexpr uint64_t kRangePart = 1u << 17;
+
+__global__ __launch_bounds__(kCountThreads) void k_count_ranges(const uint32_t* __restrict__ keys, uint64_t n,
+                                                                const uint64_t* __restrict__ off, uint32_t J, uint32_t K,
+                                                                uint32_t per, uint32_t* __restrict__ counts,
+                                                                uint32_t* __restrict__ err)
+{
+    extern __shared__ uint32_t hist[];
+    const uint32_t tid = threadIdx.x, bd = blockDim.x;
+    const uint32_t b0 = blockIdx.x * per, nb = K - b0 < per ? K - b0 : per;  // b0 < K
+    bool bad = false;
+    for (uint32_t j = blockIdx.y; j < J; j += gridDim.y) {
+        uint64_t e = off[j + 1], s = off[j];
+        e = e < n ? e : n;
+        s = s < e ? s : e;
+        const uint64_t len = e - s;
+        uint64_t parts = (len + kRangePart - 1u) / kRangePart;
+        parts = parts < 1u ? 1u : (parts > gridDim.z ? gridDim.z : parts);
+        if (blockIdx.z >= parts) continue;
+        const uint64_t per_part = (len + parts - 1u) / parts;
+        const uint64_t ps = s + blockIdx.z * per_part < e ? s + blockIdx.z * per_part : e;
+        const uint64_t pe = ps + per_part < e ? ps + per_part : e;
+        for (uint32_t b = tid; b < nb; b += bd) hist[b] = 0u;
+        __syncthreads();
+        count_range<kBinsRange>(keys, ps, pe, K, hist, nullptr, bad, b0, nb);
+        __syncthreads();
+        uint32_t* __restrict__ row = counts + (uint64_t)j * K + b0;
+        if (parts == 1u) {
+            for (uint32_t b = tid; b < nb; b += bd) row[b] = hist[b];
+        } else {
+            for (uint32_t b = tid; b < nb; b += bd)
+                if (hist[b]) atomicAdd(&row[b], hist[b]);
+        }
+        __syncthreads();
+    }
+    if (bad) atomicOr(err, CR_ERR_KEY_RANGE);
+}
+
 template <int kBins>
 __global__ __launch_bounds__(kCountThreads) void k_count_tiled(const uint32_t* __restrict__ keys, uint64_t n,
                                                                const uint64_t* __restrict__ off, uint32_t J,
@@ -102,7 +156,6 @@ __global__ __launch_bounds__(kCountThreads) void k_count_tiled(const uint32_t* _
     if (t0 >= n) return;
     const uint64_t t1 = t0 + tile < n ? t0 + tile : n;
     const uint32_t tid = threadIdx.x, bd = blockDim.x;
-    const uint32_t words = kBins == kBinsU16 ? (K + 1) >> 1 : K;
     bool bad = false;
     uint64_t i0 = t0;
     while (i0 < t1) {
@@ -113,7 +166,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_tiled(const uint32_t* _
             s_end = (e > i0 && e < t1) ? e : t1;
         }
         if (kBins != kBinsNone)
-            for (uint32_t b = tid; b < words; b += bd) hist[b] = 0;
+            for (uint32_t b = tid; b < K; b += bd) hist[b] = 0;
         __syncthreads();
         const uint32_t j = s_j;
         const uint64_t e = s_end;
@@ -121,15 +174,9 @@ __global__ __launch_bounds__(kCountThreads) void k_count_tiled(const uint32_t* _
         count_range<kBins>(keys, i0, e, K, hist, row, bad);
         if (kBins != kBinsNone) {
             __syncthreads();
-            for (uint32_t q = tid; q < words; q += bd) {
+            for (uint32_t q = tid; q < K; q += bd) {
                 const uint32_t v = hist[q];
-                if (!v) continue;
-                if (kBins == kBinsU32) {
-                    atomicAdd(&row[q], v);
-                } else {
-                    if (v & 0xFFFFu) atomicAdd(&row[2 * q], v & 0xFFFFu);
-                    if (v >> 16) atomicAdd(&row[2 * q + 1], v >> 16);
-                }
+                if (v) atomicAdd(&row[q], v);
             }
         }
         __syncthreads();
@@ -292,7 +339,6 @@ extern "C" cr_status cr_count_rates(const uint32_t* keys, uint64_t n, const uint
     const int cus = device_cus();
     const uint64_t rows = (uint64_t)J * num_keys;
     const bool fits32 = (uint64_t)num_keys * 4u <= (uint64_t)max_lds;
-    const bool fits16 = (uint64_t)((num_keys + 1) / 2) * 4u <= (uint64_t)max_lds;
     (void)hipGetLastError();
     if (fits32 && J >= (uint32_t)cus) {
         const uint32_t lds = num_keys * 4u;
@@ -304,29 +350,39 @@ extern "C" cr_status cr_count_rates(const uint32_t* keys, uint64_t n, const uint
                            counts, err);
         return hipGetLastError() == hipSuccess ? CR_OK : CR_EHIP;
     }
+    const uint32_t fit = (uint32_t)max_lds / 4u;  // bins of one block
+    const uint32_t ranges = (uint32_t)(((uint64_t)num_keys + fit - 1u) / fit);
+    if (n > 0 && !fits32 && ranges <= kMaxRanges) {
+        const uint32_t per = (num_keys + ranges - 1u) / ranges;
+        const uint32_t gy = J < 65535u ? J : 65535u;
+        // parts per interval: enough blocks for the chip even if one interval holds most requests
+        uint64_t parts = (4ull * cus + (uint64_t)ranges * J - 1u) / ((uint64_t)ranges * J);
+        const uint64_t most = (n + kRangePart - 1u) / kRangePart;
+        parts = parts < 4u ? 4u : parts;
+        parts = parts > most ? most : (parts > 256u ? 256u : parts);
+        const uint32_t lds = per * 4u;
+        if (hipFuncSetAttribute((const void*)k_count_ranges, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+            hipSuccess)
+            return CR_EHIP;
+        if (parts > 1u) hipLaunchKernelGGL(k_zero, dim3(2048), dim3(256), 0, st, counts, rows);
+        hipLaunchKernelGGL(k_count_ranges, dim3(ranges, gy, (uint32_t)parts), dim3(kCountThreads), (size_t)lds, st, keys, n,
+                           off, J, num_keys, per, counts, err);
+        return hipGetLastError() == hipSuccess ? CR_OK : CR_EHIP;
+    }
     hipLaunchKernelGGL(k_zero, dim3(2048), dim3(256), 0, st, counts, rows);
     if (n == 0) return hipGetLastError() == hipSuccess ? CR_OK : CR_EHIP;
-    const int bins = fits32 ? kBinsU32 : (fits16 ? kBinsU16 : kBinsNone);
-    const uint64_t target_blocks = (uint64_t)cus * (bins != kBinsNone ? 2u : 8u);
-    uint64_t tile = (n + target_blocks - 1) / target_blocks;
-    const uint64_t min_tile = bins != kBinsNone ? (uint64_t)(num_keys > 16384 ? num_keys : 16384) : 8192u;
+    uint64_t tile = (n + (uint64_t)cus * (fits32 ? 2u : 8u) - 1) / ((uint64_t)cus * (fits32 ? 2u : 8u));
+    const uint64_t min_tile = fits32 ? (uint64_t)(num_keys > 16384 ? num_keys : 16384) : 8192u;
     if (tile < min_tile) tile = min_tile;
     tile = (tile + 1023) & ~1023ull;
-    if (bins == kBinsU16 && tile > 65535u) tile = 64512u;  // a u16 bin never overflows
     const uint64_t blocks = (n + tile - 1) / tile;
     if (blocks > 0x7FFFFFFFull) return CR_EINVAL;
-    const uint32_t lds = bins == kBinsU32 ? num_keys * 4u : (bins == kBinsU16 ? ((num_keys + 1) / 2) * 4u : 0u);
-    if (bins == kBinsU32) {
+    if (fits32) {
+        const uint32_t lds = num_keys * 4u;
         if (hipFuncSetAttribute((const void*)k_count_tiled<kBinsU32>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds) != hipSuccess)
             return CR_EHIP;
         hipLaunchKernelGGL(k_count_tiled<kBinsU32>, dim3((uint32_t)blocks), dim3(kCountThreads), (size_t)lds, st, keys,
-                           n, off, J, num_keys, counts, err, tile);
-    } else if (bins == kBinsU16) {
-        if (hipFuncSetAttribute((const void*)k_count_tiled<kBinsU16>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return CR_EHIP;
-        hipLaunchKernelGGL(k_count_tiled<kBinsU16>, dim3((uint32_t)blocks), dim3(kCountThreads), (size_t)lds, st, keys,
                            n, off, J, num_keys, counts, err, tile);
     } else {
         hipLaunchKernelGGL(k_count_tiled<kBinsNone>, dim3((uint32_t)blocks), dim3(kCountThreads), 0, st, keys, n, off,
