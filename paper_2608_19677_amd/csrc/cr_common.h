@@ -29,6 +29,21 @@ __device__ __forceinline__ uint64_t lanemask_lt()
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
+// Set bits of m below this lane; m uniform (mbcnt64) or per lane (mbcnt_mask).
+__device__ __forceinline__ uint32_t mbcnt64(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+__device__ __forceinline__ uint32_t mbcnt_mask(uint64_t m) { return (uint32_t)__popcll(m & lanemask_lt()); }
+
+// Compiler-level ordering of one wavefront's LDS accesses (the hardware keeps them in order).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ uint32_t rdlane(uint32_t v, uint32_t l)
 {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);

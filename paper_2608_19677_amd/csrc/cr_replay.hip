@@ -898,21 +898,9 @@ struct HashLds {
 constexpr uint32_t kNoPos = 4096u;     // position of an entry that is not cached
 constexpr uint32_t kMarkPos = 8192u;   // above it: marks of the lanes of one step
 
-// Compiler-level ordering of one wavefront's LDS accesses (the hardware keeps them in order).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 __device__ __forceinline__ uint32_t bperm(uint32_t src_lane, uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src_lane << 2), (int)v);
-}
-
-__device__ __forceinline__ uint32_t mbcnt64(uint64_t m)  // set bits of m below this lane
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }

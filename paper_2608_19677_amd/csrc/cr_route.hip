@@ -462,12 +462,37 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_group(
 // admitted keys take the least-loaded member of T(b) and the rest power of two choices,
 // on the running count of requests each destination has received in the interval. Every
 // decision depends on the earlier ones, so an interval is one serial chain; the chains of
-// different intervals and candidates are independent, one wavefront each. With R <= 64,
-// lane r holds destination r's count and a decision reads it with v_readlane; otherwise the
-// counts sit in LDS. For each batch of 64 requests the lanes look their requests up in
-// parallel (table entry, hash, both draws; a single-copy key is a choice between its
-// member and itself), then the wavefront walks the 64 decisions in order.
-template <bool kLds>
+// different intervals and candidates are independent, one wavefront each.
+//
+// A batch of 64 requests is decided by iteration instead of one request after another. With
+// every lane's choice so far in a 64-bit lane mask per destination (LDS), lane t counts the
+// earlier lanes at its two draws and chooses again, d2 iff load[d2] + n2 < load[d1] + n1; when
+// no lane changes, every choice is the one the sequence makes, because lane t's depends on
+// the lanes before it alone (lane 0's is right from the start, and each pass settles at least
+// one more, so it ends after at most 64 passes; a few are usual). A single-copy key is a choice
+// between its member and itself. The lookups of the next batches (key, key-index entry, route
+// word: three dependent gathers) are in flight while a batch is decided.
+//
+// The requests of a key of k > 1 members depend on each other one by one (each takes the least
+// loaded), so a batch that holds one is walked in order, with a member choice as one minimum
+// over the lanes: with R <= 64 lane r holds destination r's load and a request's members are a
+// lane mask; above, the loads sit in LDS and lane u takes member u, whose list is loaded while
+// the request before is decided.
+// 948 intervals of about 10,600 requests over 30 destinations: 498 us with the serial walk, 150
+// now; the longest interval's chain bounds it.
+// min over the 64 lanes
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
+{
+    auto step = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xF, 0xF, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xF, 0xF, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xF, 0xF, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xF, 0xF, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));
+    return rdlane(v, 63u);
+}
+
 __global__ __launch_bounds__(64) void k_route_live(
     const uint32_t* __restrict__ keys, uint64_t n, uint64_t first_index, uint32_t smix,
     const uint64_t* __restrict__ off, const uint32_t* __restrict__ gmap, uint32_t K, uint32_t R, uint32_t cands,
@@ -475,7 +500,8 @@ __global__ __launch_bounds__(64) void k_route_live(
     const uint32_t* __restrict__ member_off, uint32_t cmax, const uint16_t* __restrict__ members,
     uint16_t* __restrict__ dest, uint32_t* __restrict__ err)
 {
-    __shared__ uint32_t s_live[kLds ? CR_MAX_R : 1];
+    extern __shared__ unsigned long long s_mask[];  // [R] lanes of the batch that chose the destination, 0 between batches
+    uint32_t* s_live = reinterpret_cast<uint32_t*>(s_mask + R);  // [R] requests of this interval sent to it
     const uint32_t lane = threadIdx.x;
     const uint32_t j = blockIdx.x / cands, c = blockIdx.x % cands;
     const uint64_t i0 = off[j];
@@ -489,86 +515,137 @@ __global__ __launch_bounds__(64) void k_route_live(
     const uint32_t* __restrict__ mo = member_off + (uint64_t)p * (cmax + 1u);
     const uint16_t* __restrict__ mem = members + (uint64_t)p * cmax;
     uint16_t* __restrict__ dc = dest + (uint64_t)c * n;
-    uint32_t live = 0;  // lane r: requests of this interval sent to destination r (R <= 64)
-    if (kLds)
-        for (uint32_t r = lane; r < R; r += 64u) s_live[r] = 0;
-    auto load_of = [&](uint32_t d) -> uint32_t {
-        if (kLds) return (uint32_t)__builtin_amdgcn_readfirstlane((int)s_live[d]);
-        return rdlane(live, d);
+    for (uint32_t r = lane; r < R; r += 64u) {
+        s_mask[r] = 0ull;
+        s_live[r] = 0u;
+    }
+    wave_lds_fence();
+    // lookups of the request at i (unconditional loads at clamped places)
+    auto key_at = [&](uint64_t i) -> uint32_t { return keys[i < i1 ? i : i0]; };
+    auto entry_of = [&](uint32_t b) -> ulonglong2 {
+        return *reinterpret_cast<const ulonglong2*>(kx + 2u * (b < K ? b >> 6 : 0u));
     };
-    auto charge = [&](uint32_t d) {
-        if (kLds) {
-            if (lane == 0) s_live[d] = s_live[d] + 1u;
-        } else {
-            live += lane == d ? 1u : 0u;
-        }
+    auto admitted = [&](uint32_t b, ulonglong2 e) -> bool { return b < K && ((e.x >> (b & 63u)) & 1ull); };
+    auto word_of = [&](uint32_t b, ulonglong2 e) -> uint32_t {
+        const uint32_t rank = (uint32_t)e.y + (uint32_t)__popcll(e.x & ((1ull << (b & 63u)) - 1ull));
+        return rw[admitted(b, e) ? rank : 0u];
     };
+    uint32_t b0 = key_at(i0 + lane), b1 = key_at(i0 + 64u + lane), b2 = key_at(i0 + 128u + lane);
+    ulonglong2 e0 = entry_of(b0), e1 = entry_of(b1);
+    uint32_t w0 = word_of(b0, e0);
     bool bad = false;
     for (uint64_t base = i0; base < i1; base += 64u) {
         const uint64_t i = base + lane;
+        const uint32_t b3 = key_at(i + 192u);
+        const ulonglong2 e2 = entry_of(b2);
+        const uint32_t w1 = word_of(b1, e1);
         const bool in = i < i1;
-        const uint32_t b = in ? keys[i] : 0u;
-        const bool valid = in && b < K;
-        bad |= in && b >= K;
-        const ulonglong2 e = valid ? *reinterpret_cast<const ulonglong2*>(kx + 2u * (b >> 6))
-                                   : make_ulonglong2(0ull, 0ull);
-        const bool adm = valid && ((e.x >> (b & 63u)) & 1ull);
-        const uint32_t w =
-            adm ? rw[(uint32_t)e.y + (uint32_t)__popcll(e.x & ((1ull << (b & 63u)) - 1ull))] : 0u;
+        bad |= in && b0 >= K;
+        const bool adm = in && admitted(b0, e0);
+        const uint32_t w = adm ? w0 : 0u;
         const uint32_t h = req_hash(smix, first_index + i);
         uint32_t d1 = (uint32_t)(((uint64_t)(h & 0xFFFFu) * R) >> 16);
         uint32_t d2 = (uint32_t)(((uint64_t)(h >> 16) * R) >> 16);
         if (adm && (w & CR_ROUTE_SINGLE)) d1 = d2 = w & 0xFFFFu;
         const uint64_t multi = ballot(adm && !(w & CR_ROUTE_SINGLE));
-        const uint32_t nb = i1 - base < 64u ? (uint32_t)(i1 - base) : 64u;
         uint32_t out = 0;
-        if (!kLds && multi == 0 && nb == 64u) {
-            // Full batch without multi-copy keys: 64 branch-free decisions, draws read 16 ahead.
-#pragma unroll
-            for (uint32_t gq = 0; gq < 4; ++gq) {
-                uint32_t e1[16], e2[16];
-#pragma unroll
-                for (uint32_t t = 0; t < 16; ++t) {
-                    e1[t] = rdlane(d1, 16u * gq + t);
-                    e2[t] = rdlane(d2, 16u * gq + t);
+        if (multi == 0) {
+            const uint32_t l1 = s_live[d1], l2 = s_live[d2];
+            out = l2 < l1 ? d2 : d1;
+            if (in) atomicOr(&s_mask[out], 1ull << lane);
+            wave_lds_fence();
+            for (;;) {
+                const uint32_t n1 = mbcnt_mask(s_mask[d1]), n2 = mbcnt_mask(s_mask[d2]);
+                wave_lds_fence();
+                const uint32_t q = l2 + n2 < l1 + n1 ? d2 : d1;
+                const bool change = in && q != out;
+                if (ballot(change) == 0ull) break;
+                if (change) {
+                    atomicXor(&s_mask[out], 1ull << lane);
+                    atomicXor(&s_mask[q], 1ull << lane);
+                    out = q;
                 }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (uint32_t t = 0; t < 16; ++t) {
-                    const uint32_t d = rdlane(live, e2[t]) < rdlane(live, e1[t]) ? e2[t] : e1[t];
-                    live += lane == d ? 1u : 0u;
-                    out = wrlane(out, d, 16u * gq + t);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                wave_lds_fence();
             }
-            dc[i] = (uint16_t)out;
-            continue;
-        }
-        for (uint32_t t = 0; t < nb; ++t) {
-            uint32_t d;
-            if ((multi >> t) & 1ull) {
-                // least (load, destination) among the members of T(b)
-                const uint32_t a = rdlane(w, t);
-                const uint32_t o0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)mo[a]);
-                const uint32_t o1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)mo[a + 1u]);
-                d = (uint32_t)__builtin_amdgcn_readfirstlane((int)mem[o0]);
-                uint32_t ld = load_of(d);
-                for (uint32_t o = o0 + 1u; o < o1; ++o) {
-                    const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)mem[o]);
-                    const uint32_t lm = load_of(m);
-                    if (lm < ld || (lm == ld && m < d)) {
-                        d = m;
-                        ld = lm;
+            // the batch's counts, by the last lane of every destination
+            const uint64_t m = in ? (uint64_t)s_mask[out] : 0ull;
+            wave_lds_fence();
+            if (in) {
+                if ((m >> lane) == 1ull) s_live[out] += (uint32_t)__popcll(m);
+                s_mask[out] = 0ull;
+            }
+            wave_lds_fence();
+        } else {
+            const uint32_t nb = i1 - base < 64u ? (uint32_t)(i1 - base) : 64u;
+            const bool is = (multi >> lane) & 1ull;
+            const uint32_t o0 = is ? mo[w] : 0u, k = is ? mo[w + 1u] - o0 : 0u;  // this lane's member list
+            if (R <= 64u) {
+                uint64_t set = 0;
+                for (uint32_t u = 0; ballot(u < k); u += 4u) {
+                    uint32_t m[4];
+#pragma unroll
+                    for (uint32_t q = 0; q < 4; ++q) m[q] = mem[u + q < k ? o0 + u + q : 0u];
+#pragma unroll
+                    for (uint32_t q = 0; q < 4; ++q) set |= u + q < k ? 1ull << (m[q] & 63u) : 0ull;
+                }
+                uint32_t live = lane < R ? s_live[lane] : 0u;
+                for (uint32_t t = 0; t < nb; ++t) {
+                    uint32_t d;
+                    if ((multi >> t) & 1ull) {  // least (load, destination) among the members of T(b)
+                        const uint64_t sm = rdlane64(set, t);
+                        const uint32_t lm = __builtin_amdgcn_inverse_ballot_w64(sm) ? live : 0xFFFFFFFFu;
+                        d = first_lane(ballot(lm == wave_min_u32(lm)) & sm);
+                    } else {
+                        const uint32_t x1 = rdlane(d1, t), x2 = rdlane(d2, t);
+                        d = rdlane(live, x2) < rdlane(live, x1) ? x2 : x1;
                     }
+                    live += lane == d ? 1u : 0u;
+                    out = wrlane(out, d, t);
                 }
+                if (lane < R) s_live[lane] = live;
+                wave_lds_fence();
             } else {
-                const uint32_t e1 = rdlane(d1, t), e2 = rdlane(d2, t);
-                d = load_of(e2) < load_of(e1) ? e2 : e1;
+                uint64_t left = multi;  // requests whose first 64 members are still to be loaded
+                auto members_of = [&](uint32_t t, uint32_t u) -> uint32_t {
+                    const uint32_t kt = rdlane(k, t);
+                    return mem[rdlane(o0, t) + (u + lane < kt ? u + lane : 0u)];
+                };
+                uint32_t nextm = members_of(first_lane(left), 0u);
+                for (uint32_t t = 0; t < nb; ++t) {
+                    uint32_t d;
+                    if ((multi >> t) & 1ull) {
+                        uint32_t m = nextm;
+                        left &= left - 1ull;
+                        if (left) nextm = members_of(first_lane(left), 0u);
+                        const uint32_t kt = rdlane(k, t);
+                        uint32_t best = 0xFFFFFFFFu;
+                        d = 0;
+                        for (uint32_t u = 0;;) {
+                            const uint32_t lm = u + lane < kt ? s_live[m] : 0xFFFFFFFFu;
+                            const uint32_t lo = wave_min_u32(lm);
+                            const uint32_t dm = wave_min_u32(lm == lo && u + lane < kt ? m : 0xFFFFFFFFu);
+                            const bool less = lo < best || (lo == best && dm < d);
+                            d = less ? dm : d;
+                            best = less ? lo : best;
+                            u += 64u;
+                            if (u >= kt) break;
+                            m = members_of(t, u);
+                        }
+                    } else {
+                        const uint32_t x1 = rdlane(d1, t), x2 = rdlane(d2, t);
+                        const uint32_t l1 = s_live[x1], l2 = s_live[x2];
+                        d = (uint32_t)__builtin_amdgcn_readfirstlane((int)(l2 < l1 ? x2 : x1));
+                    }
+                    if (lane == 0) s_live[d] = s_live[d] + 1u;
+                    wave_lds_fence();
+                    out = wrlane(out, d, t);
+                }
             }
-            charge(d);
-            out = wrlane(out, d, t);
         }
         if (in) dc[i] = (uint16_t)out;
+        b0 = b1, b1 = b2, b2 = b3;
+        e0 = e1, e1 = e2;
+        w0 = w1;
     }
     if (ballot(bad) && lane == 0) atomicOr(err, CR_ERR_KEY_RANGE);
 }
@@ -592,14 +669,10 @@ extern "C" cr_status cr_route_live(const uint32_t* keys, uint64_t n, uint64_t fi
     if (blocks > 0x7FFFFFF0ull) return CR_EINVAL;
     const uint32_t cmax = plans->R * plans->max_W;
     (void)hipGetLastError();
-#define CR_LIVE_LAUNCH(L)                                                                                          \
-    hipLaunchKernelGGL(k_route_live<L>, dim3((uint32_t)blocks), dim3(64), 0, as_stream(stream), keys, n, first_index, \
-                       seed_mix(seed), off, gmap, plans->num_keys, plans->R, plans->cands,                          \
-                       plans->num_plans / plans->cands, (plans->num_keys + 63u) / 64u, plans->key_index, plans->route, \
-                       plans->member_off, cmax, plans->members, dest, err)
-    if (plans->R <= 64) CR_LIVE_LAUNCH(false);
-    else CR_LIVE_LAUNCH(true);
-#undef CR_LIVE_LAUNCH
+    hipLaunchKernelGGL(k_route_live, dim3((uint32_t)blocks), dim3(64), (size_t)plans->R * 12u, as_stream(stream), keys, n,
+                       first_index, seed_mix(seed), off, gmap, plans->num_keys, plans->R, plans->cands,
+                       plans->num_plans / plans->cands, (plans->num_keys + 63u) / 64u, plans->key_index, plans->route,
+                       plans->member_off, cmax, plans->members, dest, err);
     return hipGetLastError() == hipSuccess ? CR_OK : CR_EHIP;
 }
 
