@@ -29,7 +29,7 @@ __device__ __forceinline__ uint64_t lanemask_lt()
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-// Set bits of m below this lane; m uniform (mbcnt64) or per lane (mbcnt_mask).
+// Set bits of m below this lane; m uniform or per lane.
 __device__ __forceinline__ uint32_t mbcnt64(uint64_t m)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));

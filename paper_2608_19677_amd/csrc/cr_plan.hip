@@ -23,7 +23,6 @@ namespace cr {
 namespace {
 
 constexpr int kSortThreads = 1024;
-constexpr int kSortWaves = kSortThreads / kWave;
 
 __host__ __device__ __forceinline__ bool hash_placed(uint32_t variant)
 {

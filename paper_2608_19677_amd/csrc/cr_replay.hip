@@ -3,7 +3,7 @@
 // equal-slot model: W whole-prefix slots per destination).
 //
 // Pipeline (all on the caller's stream, workspace from the caller):
-//   k_part_hist / k_scan_dest / k_seg_items / k_part_scatter
+//   k_part_hist / k_scan_dest / k_seg_items / k_part_scatter64 / k_part_scatter_wide
 //        stable partition of every candidate's requests by destination, preserving
 //        arrival order; each record packs (key, suffix, interval) into 8 bytes;
 //        k_seg_items also splits every (candidate, destination) stream into segments of
@@ -206,131 +206,21 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_dest(uint32_t* __restrict
     if (threadIdx.x == 0) dtot[(uint64_t)c * R + d] = carry;
 }
 
-// One wavefront per (tile, candidate): stable scatter into packed records, kSub requests
-// at a time. Pass one ranks every request among the earlier ones of its destination in
-// the sub-tile (ballots over the destination bits, plus a per-destination counter in
-// LDS); the records are then staged in LDS in destination order and written out so that
-// consecutive lanes store consecutive addresses of one destination's run: whole cache
-// lines instead of a few bytes in each of R streams per instruction.
+// The scatter of a tile: stable, into packed records, a sub-tile of requests at a time. Every
+// request is ranked among the earlier ones of its destination in the sub-tile; the records are
+// then staged in LDS in destination order and written out so that consecutive lanes store
+// consecutive addresses of one destination's run: whole cache lines instead of a few bytes in
+// each of R streams per instruction.
+//
+// R <= 64: one wavefront per (tile, candidate), sub-tiles of kSub requests, each lane owning a
+// run of kRun consecutive requests of the sub-tile. A lane counts its run's destinations in a
+// private row of 16-bit counters in LDS, in request order, which ranks every request within its
+// run; a prefix sum of the rows across the lanes (packed pairs of counters, one wave scan per
+// pair of destinations) gives each lane's offset per destination. A request's rank within the
+// sub-tile is then its lane's offset plus its rank within the run: no cross-lane matching of
+// destinations at all. With aligned rows (kVec) a lane reads its run with 16-byte loads.
 constexpr uint32_t kSub = 1024;
-constexpr uint32_t kSubChunks = kSub / 64;
 static_assert(kSub == 1024, "part_geom rounds tiles to 1024 requests");
-
-inline size_t scatter_lds_bytes(uint32_t R) { return (size_t)kSub * 12u + (size_t)R * 12u; }
-
-__global__ __launch_bounds__(64) void k_part_scatter(const uint32_t* __restrict__ keys,
-                                                     const uint16_t* __restrict__ suffix,
-                                                     const uint16_t* __restrict__ dest, uint64_t n,
-                                                     const uint64_t* __restrict__ off, uint32_t J, uint32_t R,
-                                                     uint32_t nbits, uint64_t tile, uint64_t ntiles,
-                                                     const uint32_t* __restrict__ tcnt,
-                                                     const uint32_t* __restrict__ grp_off, uint64_t* __restrict__ rec)
-{
-    issue_priority_high();
-    extern __shared__ uint64_t lds[];
-    uint64_t* srec = lds;                                        // [kSub] staged records
-    uint32_t* spos = reinterpret_cast<uint32_t*>(srec + kSub);  // [kSub] their output positions
-    uint32_t* run = spos + kSub;                                 // [R] next output position
-    uint32_t* lcnt = run + R;                                    // [R] sub-tile count
-    uint32_t* loff = lcnt + R;                                   // [R] sub-tile offset
-    const uint32_t c = blockIdx.y, lane = lane_id();
-    const uint64_t t = xcd_tile(blockIdx.x, gridDim.x);
-    if (t >= ntiles) return;
-    const uint64_t t0 = t * tile, t1 = t0 + tile < n ? t0 + tile : n;
-    for (uint32_t d = lane; d < R; d += 64) {
-        run[d] = grp_off[(uint64_t)c * (R + 1u) + d] + tcnt[((uint64_t)c * R + d) * ntiles + t];
-        lcnt[d] = 0;
-    }
-    __syncthreads();
-    const uint16_t* __restrict__ dc = dest + (uint64_t)c * n;
-    uint64_t* __restrict__ rc = rec + (uint64_t)c * n;
-    const uint32_t per = (R + 63u) >> 6;  // destinations per lane in the offset scan
-    uint32_t j = find_interval(off, J, t0);
-    uint64_t jend = j + 1 < J ? off[j + 1] : ~0ull;  // first request of the next interval
-    for (uint64_t sb = t0; sb < t1; sb += kSub) {
-        const uint64_t se = sb + kSub < t1 ? sb + kSub : t1;
-        uint32_t dk[kSubChunks], kv[kSubChunks], mv[kSubChunks];
-#pragma unroll
-        for (uint32_t m = 0; m < kSubChunks; ++m) {
-            const uint64_t i = sb + m * 64u + lane;
-            const bool in = i < se;
-            dk[m] = in ? dc[i] : 0xFFFFu;
-            kv[m] = in ? keys[i] : 0u;
-            mv[m] = in ? suffix[i] : 0u;
-        }
-#pragma unroll
-        for (uint32_t m = 0; m < kSubChunks; ++m) {
-            const uint64_t base = sb + m * 64u;
-            if (base >= se) {  // past the end of the tile: nothing to stage
-                dk[m] = 0xFFFFFFFFu;
-                continue;
-            }
-            const uint64_t i = base + lane;
-            const uint32_t d = dk[m];
-            const bool valid = i < se && d < R;
-            uint32_t jl = j;
-            if (base + 63 >= jend) {  // an interval boundary falls inside these 64 requests
-                while (jl + 1 < J && off[jl + 1] <= i) ++jl;
-                j = rdlane(jl, 63);
-                jend = j + 1 < J ? off[j + 1] : ~0ull;
-            }
-            uint64_t peers = ballot(valid);
-            for (uint32_t bit = 0; bit < nbits; ++bit) {
-                const bool on = (d >> bit) & 1u;
-                const uint64_t bb = ballot(on);
-                peers &= on ? bb : ~bb;
-            }
-            const uint32_t rk = (uint32_t)__popcll(peers & lanemask_lt());
-            const uint32_t lr = valid ? lcnt[d] + rk : 0u;
-            __syncthreads();
-            if (valid && rk == 0) lcnt[d] += (uint32_t)__popcll(peers);
-            __syncthreads();
-            dk[m] = valid ? (d << 16) | lr : 0xFFFFFFFFu;
-            mv[m] |= jl << 16;
-        }
-        // exclusive offsets of the destinations within the sub-tile
-        uint32_t own = 0;
-        for (uint32_t q = 0; q < per; ++q) {
-            const uint32_t d = lane * per + q;
-            own += d < R ? lcnt[d] : 0u;
-        }
-        uint32_t acc = wave_incl_scan_u32(own) - own;
-        const uint32_t total = rdlane(acc + own, 63);
-        for (uint32_t q = 0; q < per; ++q) {
-            const uint32_t d = lane * per + q;
-            if (d < R) {
-                loff[d] = acc;
-                acc += lcnt[d];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (uint32_t m = 0; m < kSubChunks; ++m) {
-            if (dk[m] != 0xFFFFFFFFu) {
-                const uint32_t d = dk[m] >> 16, lr = dk[m] & 0xFFFFu;
-                const uint32_t slot = loff[d] + lr;
-                srec[slot] = (uint64_t)kv[m] | ((uint64_t)mv[m] << 32);
-                spos[slot] = run[d] + lr;
-            }
-        }
-        __syncthreads();
-        for (uint32_t q = lane; q < total; q += 64) rc[spos[q]] = srec[q];
-        __syncthreads();
-        for (uint32_t d = lane; d < R; d += 64) {
-            run[d] += lcnt[d];
-            lcnt[d] = 0;
-        }
-        __syncthreads();
-    }
-}
-
-// R <= 64: the same scatter with each lane owning a run of kRun consecutive requests of
-// the sub-tile. A lane counts its run's destinations in a private row of 16-bit counters in
-// LDS, in request order, which ranks every request within its run; a prefix sum of the rows
-// across the lanes (packed pairs of counters, one wave scan per pair of destinations) gives
-// each lane's offset per destination. A request's rank within the sub-tile is then its lane's
-// offset plus its rank within the run: no cross-lane matching of destinations at all. With
-// aligned rows (kVec) a lane reads its run with 16-byte loads.
 constexpr uint32_t kRun = kSub / 64;
 
 // Row stride in counters: R rounded up to 8 (16-byte pieces).
@@ -476,92 +366,134 @@ __global__ __launch_bounds__(64) void k_part_scatter64(const uint32_t* __restric
     }
 }
 
-// R > 64, several wavefronts per block: sub-tiles of kWideSub requests, wavefront w taking
-// the sub-tile's requests 1024 w .. 1024 w + 1023 as 16 chunks of 64 in order. A chunk ranks
-// each request among its chunk's requests to the same destination by ballots over the
-// destination bits; the chunk's leader adds the chunk's count to the wavefront's counter of
+// R > 64, several wavefronts per block: sub-tiles of kWideSub requests (1,024 per wavefront),
+// wavefront w taking the sub-tile's requests 1024 w .. 1024 w + 1023 as 16 chunks of 64 in
+// order. A chunk ranks each request among its chunk's requests to the same destination by a
+// matching in LDS; the chunk's leader adds the chunk's count to the wavefront's counter of
 // that destination in LDS and hands the old value to its peers, which ranks the request
 // within the wavefront's requests. Per destination, a block scan over the totals gives the
 // destination's run in the sub-tile and each wavefront's base in it; the records are staged
 // in LDS in destination order and written out run by run (about kWideSub / R consecutive
-// records per destination, against one in k_part_scatter's 1,024-request sub-tiles).
+// records per destination).
 // Blocks are dealt to the XCDs round-robin; block b takes candidate (b / 8) mod P of tile
 // ((b / 8) / P) * 8 + b mod 8, so that an XCD runs the P candidates of one tile together
 // and fetches the tile's keys and suffixes into its L2 once for all of them (with the
 // candidates fastest over the whole grid, each XCD held eight tiles' keys at a time, more
 // than its L2, and read them about once per candidate).
-constexpr uint32_t kWideWaves = 4;
-constexpr uint32_t kWideThreads = 64 * kWideWaves;
-constexpr uint32_t kWideSub = 1024 * kWideWaves;
 constexpr uint32_t kWideChunks = 16;  // chunks of 64 per wavefront and sub-tile
 
 __host__ __device__ __forceinline__ uint32_t wide_row(uint32_t R) { return (R + 3u) & ~3u; }  // padded to 4 per thread
 
-// LDS: staged records and their destinations, per-wavefront counters and the runs' bases,
-// and per wavefront two matching scratch areas (64 peer masks, then one byte per
-// destination), one for even and one for odd chunks.
-inline size_t scatter_wide_lds_bytes(uint32_t R)
+// The element at p + off + k, for a uniform p and a constant k.
+template <typename T>
+__device__ __forceinline__ T at_bytes(const T* p, uint32_t off, uint32_t k)
 {
-    return (size_t)kWideSub * 10u + (size_t)wide_row(R) * 4u * (kWideWaves + 1u) +
-           (size_t)kWideWaves * 2u * (512u + ((wide_row(R) + 7u) & ~7u));
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + off + (size_t)k);
 }
 
-__global__ __launch_bounds__(kWideThreads) void k_part_scatter_wide(
+// LDS: staged keys, suffixes, (with several intervals) intervals and destinations; then 16-bit
+// counters per wavefront and destination, which give way to the runs' bases once the records
+// are staged. The matching scratch (per wavefront two areas of 64 peer masks and a tag byte per
+// destination, one for even and one for odd chunks) and the scan's lie where the records are
+// staged later. The phases of a sub-tile are chains of LDS and memory round trips that only
+// other wavefronts can cover, and a destination's run in a sub-tile (4 or 8 records at R = 1,024)
+// is what a line of HBM gets at once: with one interval, eight wavefronts stage 8,192 records in
+// 80 KB, and two blocks share a CU (4 wavefronts per SIMD). 1e8 requests x
+// 64 candidates over 1,024 destinations: 46.1 -> 38.3 ms (four wavefronts, 74 KB with 8-byte
+// records, 32-bit counters and scratch of its own: 46.1; four, three blocks of 44 KB: 43.9).
+template <bool kOne>
+__host__ __device__ constexpr uint32_t wide_waves() { return kOne ? 8u : 4u; }
+
+constexpr uint64_t kWideMinBlocks = 256;
+
+template <bool kOne>
+__host__ __device__ constexpr uint32_t wide_stage_bytes() { return wide_waves<kOne>() * 1024u * (kOne ? 8u : 10u); }
+
+__host__ __device__ __forceinline__ uint32_t wide_area_bytes(uint32_t R) { return 512u + ((wide_row(R) + 8u) & ~7u); }
+
+// (the matching scratch, at most 2 x 1,544 bytes per wavefront, is smaller than the staged records)
+template <bool kOne>
+inline size_t scatter_wide_lds_bytes(uint32_t R)
+{
+    return wide_stage_bytes<kOne>() + (size_t)wide_row(R) * 2u * wide_waves<kOne>();
+}
+
+template <bool kOne>
+__global__ __launch_bounds__(64 * wide_waves<kOne>(), kOne ? 4 : 3) void k_part_scatter_wide(
     const uint32_t* __restrict__ keys, const uint16_t* __restrict__ suffix, const uint16_t* __restrict__ dest,
-    uint64_t n, const uint64_t* __restrict__ off, uint32_t J, uint32_t P, uint32_t R, uint32_t nbits,
+    uint64_t n, const uint64_t* __restrict__ off, uint32_t J, uint32_t P, uint32_t R,
     uint64_t tile, uint64_t ntiles, const uint32_t* __restrict__ tcnt, const uint32_t* __restrict__ grp_off,
     uint64_t* __restrict__ rec)
 {
+    constexpr uint32_t kWideWaves = wide_waves<kOne>(), kWideThreads = 64u * kWideWaves, kWideSub = 1024u * kWideWaves;
+    constexpr uint32_t kPer = 1024u / kWideThreads, kPairs = kPer / 2u;  // destinations per thread in the scan
     issue_priority_high();
     extern __shared__ uint64_t lds[];
-    const uint32_t R4 = wide_row(R);
-    uint64_t* srec = lds;                                           // [kWideSub] staged records
-    uint16_t* sdst = reinterpret_cast<uint16_t*>(srec + kWideSub);  // [kWideSub] their destinations
-    uint32_t* cnt = reinterpret_cast<uint32_t*>(sdst + kWideSub);  // [kWideWaves][R4] counts per wavefront, then its slot bases
-    uint32_t* gbase = cnt + kWideWaves * R4;  // [R4] output position of the destination's run minus its start
-    __shared__ uint32_t s_scan[16];
+    const uint32_t R4 = wide_row(R), area = wide_area_bytes(R);
+    char* base = reinterpret_cast<char*>(lds);
+    uint32_t* skey = reinterpret_cast<uint32_t*>(base);              // [kWideSub] staged keys
+    uint16_t* sfx = reinterpret_cast<uint16_t*>(skey + kWideSub);    // [kWideSub] their suffixes
+    uint16_t* sdst = sfx + kWideSub;                                 // [kWideSub] their destinations
+    uint16_t* sivl = sdst + kWideSub;                                // [kWideSub] their intervals (not kOne)
+    uint16_t* cnt = reinterpret_cast<uint16_t*>(base + wide_stage_bytes<kOne>());  // [kWideWaves][R4] counts per wavefront, then its slot bases
+    uint32_t* gbase = reinterpret_cast<uint32_t*>(cnt);              // [R4] output position of the destination's run minus its start
+    uint32_t* s_scan = reinterpret_cast<uint32_t*>(base);
     const uint32_t bi = blockIdx.x / kXcds;
     const uint32_t c = bi % P, lane = lane_id(), wv = wave_in_block(), tid = threadIdx.x;
-    // this wavefront's matching scratch, two areas (even and odd chunks): peer masks by
-    // representative lane, and a tag byte per destination naming the representative
-    const uint32_t area = 64u + (R4 + 7u) / 8u;  // 8-byte words
-    unsigned long long* pm0 = reinterpret_cast<unsigned long long*>(gbase + R4) + wv * 2u * area;
-    unsigned long long* pm1 = pm0 + area;
+    // this wavefront's matching scratch: peer masks by representative lane, and a tag byte per
+    // destination naming the representative
+    unsigned long long* pm0 = reinterpret_cast<unsigned long long*>(base + wv * 2u * area);
+    unsigned long long* pm1 = reinterpret_cast<unsigned long long*>(base + wv * 2u * area + area);
     uint8_t* tag0 = reinterpret_cast<uint8_t*>(pm0 + 64);
     uint8_t* tag1 = reinterpret_cast<uint8_t*>(pm1 + 64);
     const uint64_t t = (uint64_t)(bi / P) * kXcds + blockIdx.x % kXcds;
     if (t >= ntiles) return;
     const uint64_t t0 = t * tile, t1 = t0 + tile < n ? t0 + tile : n;
-    // thread tid owns destinations 4 tid .. 4 tid + 3 in the scans: their next output positions
-    const bool owner = 4u * tid < R4;
-    uint32_t run[4];
+    // thread tid owns destinations kPer tid .. kPer tid + kPer - 1 in the scans: their next output
+    // positions
+    const bool owner = kPer * tid < R4;
+    uint32_t run[kPer];
 #pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-        const uint32_t d = 4u * tid + q;
+    for (uint32_t q = 0; q < kPer; ++q) {
+        const uint32_t d = kPer * tid + q;
         run[q] = d < R ? grp_off[(uint64_t)c * (R + 1u) + d] + tcnt[((uint64_t)c * R + d) * ntiles + t] : 0u;
     }
     const uint16_t* __restrict__ dc = dest + (uint64_t)c * n;
     uint64_t* __restrict__ rc = rec + (uint64_t)c * n;
-    uint32_t* __restrict__ wc = cnt + wv * R4;
+    uint16_t* wc = cnt + wv * R4;
+    uint32_t* wc2 = reinterpret_cast<uint32_t*>(wc);  // counter pairs
     for (uint64_t sb = t0; sb < t1; sb += kWideSub) {
         const uint64_t se = sb + kWideSub < t1 ? sb + kWideSub : t1;
-        if (owner)
-#pragma unroll
-            for (uint32_t w = 0; w < kWideWaves; ++w)
-                *reinterpret_cast<uint4*>(cnt + w * R4 + 4u * tid) = make_uint4(0u, 0u, 0u, 0u);
+        for (uint32_t q = tid; q < kWideWaves * R4 / 4u; q += kWideThreads)
+            reinterpret_cast<uint64_t*>(cnt)[q] = 0ull;
         __syncthreads();
         // this wavefront's requests: ws .. ws + 1023 of the sub-tile
         const uint64_t ws = sb + 1024u * wv;
-        uint32_t jl = ws < se ? find_interval(off, J, ws) : 0u;
-        uint64_t jend = jl + 1 < J ? off[jl + 1] : ~0ull;
+        const uint32_t len = ws < se ? (uint32_t)(se - ws < 1024u ? se - ws : 1024u) : 0u;
+        const uint16_t *dw = dc + ws, *xw = suffix + ws;
+        const uint32_t* kw = keys + ws;
+        uint32_t jl = !kOne && ws < se ? find_interval(off, J, ws) : 0u;
+        uint64_t jend = !kOne && jl + 1 < J ? off[jl + 1] : ~0ull;
         uint32_t dk[kWideChunks], kv[kWideChunks], mv[kWideChunks];
+        // (uniform bases and 32-bit offsets, and no lane masks for a full 1,024: with them the
+        // loads' addresses spill)
+        if (len == 1024u) {
 #pragma unroll
-        for (uint32_t m = 0; m < kWideChunks; ++m) {
-            const uint64_t i = ws + 64u * m + lane;
-            const bool in = i < se;
-            dk[m] = in ? dc[i] : 0xFFFFu;
-            kv[m] = in ? keys[i] : 0u;
-            mv[m] = in ? suffix[i] : 0u;
+            for (uint32_t m = 0; m < kWideChunks; ++m) {
+                dk[m] = at_bytes(dw, 2u * lane, 128u * m);
+                kv[m] = at_bytes(kw, 4u * lane, 256u * m);
+                mv[m] = at_bytes(xw, 2u * lane, 128u * m);
+            }
+        } else {
+#pragma unroll
+            for (uint32_t m = 0; m < kWideChunks; ++m) {
+                dk[m] = 0xFFFFu, kv[m] = 0u, mv[m] = 0u;
+                if (64u * m + lane < len) {
+                    dk[m] = at_bytes(dw, 2u * lane, 128u * m);
+                    kv[m] = at_bytes(kw, 4u * lane, 256u * m);
+                    mv[m] = at_bytes(xw, 2u * lane, 128u * m);
+                }
+            }
         }
         // Chunks in pairs, each with its own matching area, so that the LDS round trips of
         // the two chunks overlap. Lanes with the same destination: every lane writes its id
@@ -577,12 +509,11 @@ __global__ __launch_bounds__(kWideThreads) void k_part_scatter_wide(
 #pragma unroll
             for (uint32_t h = 0; h < 2; ++h) {
                 const uint64_t base = ws + 64u * (m + h);
-                const uint64_t i = base + lane;
                 dd[h] = dk[m + h];
-                vv[h] = i < se && dd[h] < R;
+                vv[h] = dd[h] < R;  // (0xFFFF past the end)
                 uint32_t j = jl;
-                if (base < se && base + 63 >= jend) {  // an interval boundary falls inside these 64
-                    while (j + 1 < J && off[j + 1] <= i) ++j;
+                if (!kOne && base < se && base + 63 >= jend) {  // an interval boundary falls inside these 64
+                    while (j + 1 < J && off[j + 1] <= base + lane) ++j;
                     jl = rdlane(j, 63);
                     jend = jl + 1 < J ? off[jl + 1] : ~0ull;
                 }
@@ -590,61 +521,63 @@ __global__ __launch_bounds__(kWideThreads) void k_part_scatter_wide(
             }
             pm0[lane] = 0ull;
             pm1[lane] = 0ull;
-            if (vv[0]) tag0[dd[0]] = (uint8_t)lane;
-            if (vv[1]) tag1[dd[1]] = (uint8_t)lane;
-            const uint32_t rep0 = vv[0] ? (uint32_t)tag0[dd[0]] : lane;
-            const uint32_t rep1 = vv[1] ? (uint32_t)tag1[dd[1]] : lane;
-            if (vv[0]) atomicOr(&pm0[rep0], 1ull << lane);
-            if (vv[1]) atomicOr(&pm1[rep1], 1ull << lane);
-            const uint64_t peers0 = vv[0] ? (uint64_t)pm0[rep0] : 0ull;
-            const uint64_t peers1 = vv[1] ? (uint64_t)pm1[rep1] : 0ull;
-            const uint32_t rk0 = (uint32_t)__popcll(peers0 & lanemask_lt());
-            const uint32_t rk1 = (uint32_t)__popcll(peers1 & lanemask_lt());
-            const uint32_t ld0 = vv[0] ? (uint32_t)__builtin_ctzll(peers0) : lane;
-            const uint32_t ld1 = vv[1] ? (uint32_t)__builtin_ctzll(peers1) : lane;
+            // (a lane without a destination takes the tag byte past the last one and counts nothing)
+            const uint32_t b0 = vv[0] ? dd[0] : R4, b1 = vv[1] ? dd[1] : R4;
+            tag0[b0] = (uint8_t)lane;
+            tag1[b1] = (uint8_t)lane;
+            const uint32_t rep0 = tag0[b0], rep1 = tag1[b1];
+            atomicOr(&pm0[rep0], 1ull << lane);
+            atomicOr(&pm1[rep1], 1ull << lane);
+            const uint64_t peers0 = pm0[rep0], peers1 = pm1[rep1];
+            const uint32_t rk0 = mbcnt64(peers0), rk1 = mbcnt64(peers1);
+            const uint32_t ld0 = (uint32_t)__builtin_ctzll(peers0), ld1 = (uint32_t)__builtin_ctzll(peers1);
             uint32_t old0 = 0, old1 = 0;
-            if (vv[0] && rk0 == 0) old0 = atomicAdd(&wc[dd[0]], (uint32_t)__popcll(peers0));
-            if (vv[1] && rk1 == 0) old1 = atomicAdd(&wc[dd[1]], (uint32_t)__popcll(peers1));
+            const uint32_t h0 = (b0 & 1u) * 16u, h1 = (b1 & 1u) * 16u;
+            if (vv[0] && rk0 == 0) old0 = (atomicAdd(&wc2[b0 >> 1], (uint32_t)__popcll(peers0) << h0) >> h0) & 0xFFFFu;
+            if (vv[1] && rk1 == 0) old1 = (atomicAdd(&wc2[b1 >> 1], (uint32_t)__popcll(peers1) << h1) >> h1) & 0xFFFFu;
             old0 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(ld0 << 2), (int)old0);
             old1 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(ld1 << 2), (int)old1);
             dk[m] = vv[0] ? (dd[0] << 16) | (old0 + rk0) : 0xFFFFFFFFu;  // destination, rank in the wavefront
             dk[m + 1] = vv[1] ? (dd[1] << 16) | (old1 + rk1) : 0xFFFFFFFFu;
-            mv[m] |= jj[0] << 16;
-            mv[m + 1] |= jj[1] << 16;
+            asm volatile("" : "+v"(dk[m]), "+v"(dk[m + 1]));  // (formed here, not from its parts where it is used)
+            if (!kOne) {
+                mv[m] |= jj[0] << 16;
+                mv[m + 1] |= jj[1] << 16;
+            }
         }
         __syncthreads();
         // destination runs in the sub-tile: each wavefront's slot base within its destination's
-        // run, and the run's output position minus its start (16-byte accesses, one thread per
-        // four destinations)
-        uint4 cw[kWideWaves];
-        uint32_t tq[4] = {0u, 0u, 0u, 0u};
-        if (owner) {
+        // run, and the run's output position minus its start
+        uint32_t cw[kWideWaves][kPairs];
+        uint32_t tq[kPer] = {}, sum = 0;
+        if (owner)
 #pragma unroll
-            for (uint32_t w = 0; w < kWideWaves; ++w) {
-                cw[w] = *reinterpret_cast<const uint4*>(cnt + w * R4 + 4u * tid);
-                tq[0] += cw[w].x, tq[1] += cw[w].y, tq[2] += cw[w].z, tq[3] += cw[w].w;
-            }
-        }
+            for (uint32_t w = 0; w < kWideWaves; ++w)
+#pragma unroll
+                for (uint32_t h = 0; h < kPairs; ++h) {
+                    const uint32_t x = reinterpret_cast<const uint32_t*>(cnt + w * R4 + kPer * tid)[h];
+                    cw[w][h] = x;
+                    tq[2 * h] += x & 0xFFFFu, tq[2 * h + 1] += x >> 16;
+                }
+#pragma unroll
+        for (uint32_t q = 0; q < kPer; ++q) sum += tq[q];
         uint32_t total;
-        uint32_t acc = block_exscan_u32(tq[0] + tq[1] + tq[2] + tq[3], s_scan, &total);
+        uint32_t acc = block_exscan_u32(sum, s_scan, &total);
+        uint32_t gb[kPer];
         if (owner) {
-            uint32_t st[4];
 #pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) {
-                st[q] = acc;
-                acc += tq[q];
+            for (uint32_t h = 0; h < kPairs; ++h) {
+                uint32_t b0 = acc, b1 = acc + tq[2 * h];  // bases are below kWideSub
+                gb[2 * h] = run[2 * h] - b0, gb[2 * h + 1] = run[2 * h + 1] - b1;
+                run[2 * h] += tq[2 * h], run[2 * h + 1] += tq[2 * h + 1];
+                acc = b1 + tq[2 * h + 1];
+#pragma unroll
+                for (uint32_t w = 0; w < kWideWaves; ++w) {
+                    const uint32_t x = cw[w][h];
+                    reinterpret_cast<uint32_t*>(cnt + w * R4 + kPer * tid)[h] = b0 | (b1 << 16);
+                    b0 += x & 0xFFFFu, b1 += x >> 16;
+                }
             }
-            uint32_t b[4] = {st[0], st[1], st[2], st[3]};
-#pragma unroll
-            for (uint32_t w = 0; w < kWideWaves; ++w) {
-                const uint4 x = cw[w];
-                *reinterpret_cast<uint4*>(cnt + w * R4 + 4u * tid) = make_uint4(b[0], b[1], b[2], b[3]);
-                b[0] += x.x, b[1] += x.y, b[2] += x.z, b[3] += x.w;
-            }
-            *reinterpret_cast<uint4*>(gbase + 4u * tid) =
-                make_uint4(run[0] - st[0], run[1] - st[1], run[2] - st[2], run[3] - st[3]);
-#pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) run[q] += tq[q];
         }
         __syncthreads();
 #pragma unroll
@@ -652,12 +585,21 @@ __global__ __launch_bounds__(kWideThreads) void k_part_scatter_wide(
             if (dk[m] != 0xFFFFFFFFu) {
                 const uint32_t d = dk[m] >> 16, lr = dk[m] & 0xFFFFu;
                 const uint32_t slot = wc[d] + lr;
-                srec[slot] = (uint64_t)kv[m] | ((uint64_t)mv[m] << 32);
+                skey[slot] = kv[m];
+                sfx[slot] = (uint16_t)mv[m];
                 sdst[slot] = (uint16_t)d;
+                if (!kOne) sivl[slot] = (uint16_t)(mv[m] >> 16);
             }
         }
         __syncthreads();
-        for (uint32_t q = tid; q < total; q += kWideThreads) rc[gbase[sdst[q]] + q] = srec[q];
+        if (owner)
+#pragma unroll
+            for (uint32_t q = 0; q < kPer; ++q) gbase[kPer * tid + q] = gb[q];
+        __syncthreads();
+        for (uint32_t q = tid; q < total; q += kWideThreads) {
+            const uint32_t hi = kOne ? (uint32_t)sfx[q] : (uint32_t)sfx[q] | ((uint32_t)sivl[q] << 16);
+            rc[gbase[sdst[q]] + q] = (uint64_t)skey[q] | ((uint64_t)hi << 32);
+        }
         __syncthreads();
     }
 }
@@ -1750,10 +1692,16 @@ extern "C" cr_status cr_replay_partition(const uint32_t* keys, const uint16_t* s
     if (v != CR_OK) return v;
     if (!off || !err || (n > 0 && (!keys || !suffix || !dest))) return CR_EINVAL;
     const ReplayWs w = replay_layout(ws_base(ws), n, P, R);
-    const PartGeom g = part_geom(n, P);
+    PartGeom g = part_geom(n, P);
+    // R > 64: whole sub-tiles of the wide scatter (a tile of 1,024 occupies one wavefront of a
+    // block: 4,000,037 x 4 candidates, 257 destinations 210 -> 81 us), where the chip
+    // then still holds a block per CU (below that, smaller tiles spread the work over more CUs)
+    const uint64_t sub = 1024u * (J == 1 ? wide_waves<true>() : wide_waves<false>());
+    if (R > 64 && P * ((n + sub - 1) / sub) >= kWideMinBlocks) {
+        g.tile = (g.tile + sub - 1) / sub * sub;
+        g.ntiles = (n + g.tile - 1) / g.tile;
+    }
     const hipStream_t st = as_stream(stream);
-    uint32_t nbits = 0;
-    while ((1u << nbits) < R) ++nbits;
     (void)hipGetLastError();
     // 16-byte loads of keys, destinations and suffixes need 16-byte aligned rows
     const bool vec = ((uintptr_t)keys & 15u) == 0 && ((uintptr_t)suffix & 15u) == 0 && ((uintptr_t)dest & 15u) == 0 &&
@@ -1775,16 +1723,21 @@ extern "C" cr_status cr_replay_partition(const uint32_t* keys, const uint16_t* s
         hipLaunchKernelGGL(k_part_scatter64<false>, dim3(xcd_grid((uint32_t)g.ntiles), P), dim3(64),
                            scatter64_lds_bytes(R), st, keys, suffix, dest, n, off, J, R, g.tile, g.ntiles, w.tcnt,
                            w.grp_off, w.rec);
-    else if (g.ntiles && g.ntiles <= 65535u) {
-        const size_t lds = scatter_wide_lds_bytes(R);
-        if (hipFuncSetAttribute((const void*)k_part_scatter_wide, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return CR_EHIP;
-        hipLaunchKernelGGL(k_part_scatter_wide, dim3(P * xcd_grid((uint32_t)g.ntiles)), dim3(kWideThreads), lds, st,
-                           keys, suffix, dest, n, off, J, P, R, nbits, g.tile, g.ntiles, w.tcnt, w.grp_off, w.rec);
-    } else if (g.ntiles)
-        hipLaunchKernelGGL(k_part_scatter, dim3(xcd_grid((uint32_t)g.ntiles), P), dim3(64), scatter_lds_bytes(R), st, keys,
-                           suffix, dest, n, off, J, R, nbits, g.tile, g.ntiles, w.tcnt, w.grp_off, w.rec);
+    else if (g.ntiles) {
+#define CR_WIDE(ONE)                                                                                                \
+    do {                                                                                                            \
+        const size_t lds = scatter_wide_lds_bytes<ONE>(R);                                                          \
+        if (hipFuncSetAttribute((const void*)k_part_scatter_wide<ONE>, hipFuncAttributeMaxDynamicSharedMemorySize,   \
+                                (int)lds) != hipSuccess)                                                            \
+            return CR_EHIP;                                                                                         \
+        hipLaunchKernelGGL(k_part_scatter_wide<ONE>, dim3(P * xcd_grid((uint32_t)g.ntiles)), dim3(64u * wide_waves<ONE>()), lds, \
+                           st, keys, suffix, dest, n, off, J, P, R, g.tile, g.ntiles, w.tcnt, w.grp_off,       \
+                           w.rec);                                                                                  \
+    } while (0)
+        if (J == 1) CR_WIDE(true);
+        else CR_WIDE(false);
+#undef CR_WIDE
+    }
     return hipGetLastError() == hipSuccess ? CR_OK : CR_EHIP;
 }
 
