@@ -210,7 +210,7 @@ def run_sweep(args):
         "count": dict(kernel="k_count_*", bound="hbm", unit="GB/s", work=4.0 * n, peak=HBM_PEAK_GBS),
         "route": dict(kernel="k_route_group<true,1> + group tables", bound="hbm", unit="GB/s",
                       work=(4.0 + 2.0 * P) * n, peak=HBM_PEAK_GBS),
-        "lru": dict(kernel="k_replay<1..8> (one cr_replay_lru call)", bound="alu", unit="Glane-op/s",
+        "lru": dict(kernel="k_replay, k_replay_grp (one cr_replay_lru call)", bound="alu", unit="Glane-op/s",
                     work=lru_work, peak=ALU_PEAK_GOPS),
     }
     for k, v in kern.items():
@@ -564,8 +564,7 @@ def main():
                       peak=ALU_PEAK_GOPS),
         # LRU: every request compares its key with the W slots and moves up to W of them one
         # place (a move-to-front list: one compare and one shift per slot).
-        "lru": dict(kernel="k_replay<%d, %s, false>" % (lambda sl: (sl, "true" if sl >= 5 else "false"))(
-                        max((c.W + 63) // 64 for c in wl.candidates)), bound="alu", unit="Glane-op/s",
+        "lru": dict(kernel="k_replay", bound="alu", unit="Glane-op/s",
                     work=float(sum(2.0 * c.W for c in wl.candidates)) * n, peak=ALU_PEAK_GOPS),
     }
     for k, v in kern.items():

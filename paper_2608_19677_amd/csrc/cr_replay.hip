@@ -223,16 +223,24 @@ constexpr uint32_t kSub = 1024;
 static_assert(kSub == 1024, "part_geom rounds tiles to 1024 requests");
 constexpr uint32_t kRun = kSub / 64;
 
-// Row stride in counters: R rounded up to 8 (16-byte pieces).
-__host__ __device__ __forceinline__ uint32_t scat64_row(uint32_t R) { return (R + 7u) & ~7u; }
+// Row stride in counters: R in 16-byte pieces, an odd number of them, so that the lanes' pieces
+// of one column lie in different banks (at 128 bytes, for R = 64, they all share four).
+__host__ __device__ __forceinline__ uint32_t scat64_row(uint32_t R) { return 8u * (((R + 7u) / 8u) | 1u); }
 
-inline size_t scatter64_lds_bytes(uint32_t R) { return (size_t)kSub * 12u + 64u * 8u + 64u * scat64_row(R) * 2u; }
+// LDS: the counter rows, and over them, once every request has its slot, the staged records and
+// a byte each for their destinations; then two words per destination. 9.7 KB, so that 16
+// wavefronts share a CU (21 KB at R = 64 with rows and 4-byte output positions of their own, 7
+// wavefronts): the sub-tile's phases are serial and only other wavefronts cover their latency.
+// 5e7 requests, 64 destinations: 276 -> 243 us (3.3 TB/s).
+constexpr uint32_t kStage64 = kSub * 9u;
+static_assert(kStage64 >= 64u * 72u * 2u, "the rows lie under the staged records");
+constexpr size_t kScatter64Lds = kStage64 + 64u * 8u;
 
 template <bool kVec>
 __global__ __launch_bounds__(64) void k_part_scatter64(const uint32_t* __restrict__ keys,
                                                        const uint16_t* __restrict__ suffix,
                                                        const uint16_t* __restrict__ dest, uint64_t n,
-                                                       const uint64_t* __restrict__ off, uint32_t J, uint32_t R,
+                                                       const uint64_t* __restrict__ off, uint32_t J, uint32_t P, uint32_t R,
                                                        uint64_t tile, uint64_t ntiles, const uint32_t* __restrict__ tcnt,
                                                        const uint32_t* __restrict__ grp_off,
                                                        uint64_t* __restrict__ rec)
@@ -240,13 +248,17 @@ __global__ __launch_bounds__(64) void k_part_scatter64(const uint32_t* __restric
     issue_priority_high();
     extern __shared__ uint64_t lds[];
     uint64_t* srec = lds;                                            // [kSub] staged records
-    uint32_t* spos = reinterpret_cast<uint32_t*>(srec + kSub);      // [kSub] their output positions
-    uint64_t* sbase = reinterpret_cast<uint64_t*>(spos + kSub);     // [64] {sub-tile offset, output position}
-    uint16_t* rows = reinterpret_cast<uint16_t*>(sbase + 64);       // [64][RW] counters per lane
-    uint32_t* stot = spos;  // [64] sub-tile count per destination (spos is free until staging)
-    const uint32_t RW = scat64_row(R);
-    const uint32_t c = blockIdx.y, lane = lane_id();
-    const uint64_t t = xcd_tile(blockIdx.x, gridDim.x);
+    uint8_t* sdst = reinterpret_cast<uint8_t*>(srec + kSub);         // [kSub] their destinations
+    uint16_t* rows = reinterpret_cast<uint16_t*>(lds);               // [64][RW] counters per lane (until staging)
+    uint32_t* sex = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lds) + kStage64);  // [64] sub-tile offset
+    uint32_t* gbase = sex + 64;                                      // [64] output position minus sub-tile offset
+    uint32_t* stot = gbase;  // [64] sub-tile count per destination, before
+    const uint32_t RW = scat64_row(R), R8 = (R + 7u) & ~7u;
+    // an XCD runs the candidates of one tile together (as below for R > 64): the tile's keys
+    // and suffixes come from its L2 for all but one of them (2e7 requests x 4 candidates, 16
+    // destinations: 300 -> 231 us)
+    const uint32_t bi = blockIdx.x / kXcds, c = bi % P, lane = lane_id();
+    const uint64_t t = (uint64_t)(bi / P) * kXcds + blockIdx.x % kXcds;
     if (t >= ntiles) return;
     const uint64_t t0 = t * tile, t1 = t0 + tile < n ? t0 + tile : n;
     // lane d: next output position of destination d
@@ -300,7 +312,7 @@ __global__ __launch_bounds__(64) void k_part_scatter64(const uint32_t* __restric
                 mv[v] = in ? suffix[i] : 0u;
             }
         }
-        for (uint32_t w = 0; w < RW; w += 8) *reinterpret_cast<uint4*>(row + w) = make_uint4(0u, 0u, 0u, 0u);
+        for (uint32_t w = 0; w < R8; w += 8) *reinterpret_cast<uint4*>(row + w) = make_uint4(0u, 0u, 0u, 0u);
         // interval of each request: from the sub-tile's, past the boundaries up to it
         uint32_t jl = jw;
         uint64_t nb = jl + 1 < J ? off[jl + 1] : ~0ull;  // first request of the next interval
@@ -325,7 +337,7 @@ __global__ __launch_bounds__(64) void k_part_scatter64(const uint32_t* __restric
         }
         // exclusive prefix of the rows across the lanes; lane 63's inclusive sums are the
         // sub-tile's counts per destination
-        for (uint32_t w = 0; w < RW; w += 8) {
+        for (uint32_t w = 0; w < R8; w += 8) {
             uint4* q = reinterpret_cast<uint4*>(row + w);
             const uint4 own = *q;
             const uint4 inc = make_uint4(wave_incl_scan_u32(own.x), wave_incl_scan_u32(own.y),
@@ -345,21 +357,25 @@ __global__ __launch_bounds__(64) void k_part_scatter64(const uint32_t* __restric
         const uint32_t tl = lane < R ? stot[lane] : 0u;
         const uint32_t ex = wave_incl_scan_u32(tl) - tl;
         const uint32_t total = rdlane(ex + tl, 63);
-        sbase[lane] = (uint64_t)ex | ((uint64_t)run << 32);
+        sex[lane] = ex;
         __syncthreads();
+        gbase[lane] = run - ex;
 #pragma unroll
-        for (uint32_t v = 0; v < kRun; ++v) {
+        for (uint32_t v = 0; v < kRun; ++v)
             if (dv[v] != 0xFFFFFFFFu) {
                 const uint32_t d = dv[v] & 0xFFFFu;
-                const uint32_t lr = row[d] + (dv[v] >> 16);
-                const uint64_t bs = sbase[d];
-                const uint32_t slot = (uint32_t)bs + lr;
-                srec[slot] = (uint64_t)kv[v] | ((uint64_t)mv[v] << 32);
-                spos[slot] = (uint32_t)(bs >> 32) + lr;
+                dv[v] = d | ((sex[d] + row[d] + (dv[v] >> 16)) << 16);
             }
-        }
         __syncthreads();
-        for (uint32_t q = lane; q < total; q += 64) rc[spos[q]] = srec[q];
+#pragma unroll
+        for (uint32_t v = 0; v < kRun; ++v)
+            if (dv[v] != 0xFFFFFFFFu) {
+                const uint32_t slot = dv[v] >> 16;
+                srec[slot] = (uint64_t)kv[v] | ((uint64_t)mv[v] << 32);
+                sdst[slot] = (uint8_t)dv[v];
+            }
+        __syncthreads();
+        for (uint32_t q = lane; q < total; q += 64) rc[gbase[sdst[q]] + q] = srec[q];
         run += tl;
         while (jw + 1 < J && off[jw + 1] <= se) ++jw;  // interval of the next sub-tile's first request
         __syncthreads();
@@ -1716,12 +1732,12 @@ extern "C" cr_status cr_replay_partition(const uint32_t* keys, const uint16_t* s
     hipLaunchKernelGGL(k_seg_items, dim3(1), dim3(1024), 0, st, w.dtot, P, R, ra.wa, w.grp_off, w.item_off,
                        w.gwave_off);
     if (g.ntiles && R <= 64 && vec)
-        hipLaunchKernelGGL(k_part_scatter64<true>, dim3(xcd_grid((uint32_t)g.ntiles), P), dim3(64),
-                           scatter64_lds_bytes(R), st, keys, suffix, dest, n, off, J, R, g.tile, g.ntiles, w.tcnt,
+        hipLaunchKernelGGL(k_part_scatter64<true>, dim3(P * xcd_grid((uint32_t)g.ntiles)), dim3(64),
+                           kScatter64Lds, st, keys, suffix, dest, n, off, J, P, R, g.tile, g.ntiles, w.tcnt,
                            w.grp_off, w.rec);
     else if (g.ntiles && R <= 64)
-        hipLaunchKernelGGL(k_part_scatter64<false>, dim3(xcd_grid((uint32_t)g.ntiles), P), dim3(64),
-                           scatter64_lds_bytes(R), st, keys, suffix, dest, n, off, J, R, g.tile, g.ntiles, w.tcnt,
+        hipLaunchKernelGGL(k_part_scatter64<false>, dim3(P * xcd_grid((uint32_t)g.ntiles)), dim3(64),
+                           kScatter64Lds, st, keys, suffix, dest, n, off, J, P, R, g.tile, g.ntiles, w.tcnt,
                            w.grp_off, w.rec);
     else if (g.ntiles) {
 #define CR_WIDE(ONE)                                                                                                \
