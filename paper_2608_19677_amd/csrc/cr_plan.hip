@@ -608,7 +608,10 @@ __global__ __launch_bounds__(kSortBlock, kNpl <= 20 ? 8 : 1) void k_sort_window_
 }
 
 // ---------------------------------------------------------------------------------------
-// Rows of kWideKeys keys and more (C_max >= kWideCmax): the same order by many blocks per window. A row of a million counts kept one CU busy for 3.1 ms (its reads of 4 MB one after
+// Rows of kWideKeys keys and more, and kWideKeysPerWindow more for every window (C_max >= kWideCmax):
+// the same order by many blocks per window. (One window of 66,000 keys: 65 us by one block, 69 by
+// many; 90,000: 90 and 71; 200 windows of 66,000, which fill the chip by themselves: 101 and 177.)
+// A row of a million counts kept one CU busy for 3.1 ms (its reads of 4 MB one after
 // another, then three radix passes over 524,288 entries), while the other 255 idled.
 //   k_wide_hist     histogram of the row over 1,728 bins that are exact below 128 and 1/64 of
 //                   an octave wide above; row sum and maximum
@@ -628,7 +631,7 @@ __global__ __launch_bounds__(kSortBlock, kNpl <= 20 ? 8 : 1) void k_sort_window_
 constexpr uint32_t kWideCmax = 1024;   // smallest C_max whose buffers hold the bins
 // Smallest row. 100 windows of 50,000 keys took 99 us with a block each (they fill the chip by
 // themselves) and 162 us this way.
-constexpr uint32_t kWideKeys = 65536;
+constexpr uint32_t kWideKeys = 73728, kWideKeysPerWindow = 1536;
 constexpr uint32_t kWideBins = 1728;
 constexpr uint32_t kWideSub = 1024;    // bins of a refinement: 10 bits
 constexpr uint32_t kWideThreads = 256;
@@ -2434,7 +2437,7 @@ extern "C" cr_status cr_admit(const uint32_t* counts, const cr_plan_set* plans, 
         else if (K <= 1024u * 20u) CR_SORT_REG(20);
         else CR_SORT_REG(32);
 #undef CR_SORT_REG
-    } else if (K >= kWideKeys && K <= 0xFFF00000u && cmax >= kWideCmax && plans->num_windows <= 65535u) {
+    } else if (K >= kWideKeys + (uint64_t)kWideKeysPerWindow * plans->num_windows && K <= 0xFFF00000u && cmax >= kWideCmax && plans->num_windows <= 65535u) {
         const uint32_t NW = plans->num_windows, tile = wide_tile(K, NW);
         const dim3 tiles((K + tile - 1u) / tile, NW), th(kWideThreads);
         uint32_t *ord = plans->order, *ocnt = plans->order_count;
