@@ -23,6 +23,7 @@
 // the key into lane 0, a single select between a lane and its left neighbour under a scalar
 // mask. From 64 slots it is a hash table in LDS that takes 64 records per step (below).
 #include "cr_common.h"
+#include "cr_replay_layout.h"
 
 #include <mutex>
 
@@ -30,13 +31,6 @@ namespace cr {
 namespace {
 
 constexpr int kReplayThreads = 256;
-
-struct WArg {
-    uint16_t W[CR_MAX_CANDS];
-    uint8_t grp[CR_MAX_CANDS];  // lists per wavefront: G > 1 for k_replay_grp<G>, else 1
-    uint32_t seg_min;  // shortest segment for this call's record count
-    uint32_t seg_per;  // records per segment and cache slot, at least
-};
 
 // The candidates one k_replay launch serves and the first wavefront of each: wavefront v takes
 // work item v - wv0[i] of candidate cand[i] for wv0[i] <= v < wv0[i + 1]. Each
@@ -63,47 +57,6 @@ __host__ __device__ __forceinline__ uint32_t seg_start(uint32_t i, uint32_t nseg
     return b < nb ? 64u * b : cnt;
 }
 
-// Segments the whole replay is cut into, a few rounds of wavefronts over the chip: a
-// wavefront's LRU chain is serial, so several per SIMD hide its latency, and beyond that
-// longer segments only save the backward rebuild of the initial state.
-constexpr uint64_t kSegTarget = 16384;
-
-// Shortest segments. A call with enough records to fill the chip (kSegFull) cuts nothing
-// shorter than kSegFloor records or kSegPerSlot W, so that the rebuild of the initial state
-// stays a small part. Smaller calls leave most of the chip idle, and their time is the chain
-// of one segment, so they are cut down to kSegShort records or kSegPerSlotShort W, between
-// the two in proportion, which keeps about 4,096 wavefronts. One list of 48 slots over 64
-// streams: 1e6 requests 61 -> 49 us with segments of 256 instead of 1,024; 4e6 requests 86 us
-// with 1,024 and 98 us with 488.
-constexpr uint64_t kSegFull = 4u << 20;
-constexpr uint32_t kSegFloor = 1024;
-constexpr uint32_t kSegShort = 256;
-constexpr uint32_t kSegPerSlot = 16;
-constexpr uint32_t kSegPerSlotShort = 4;
-
-// Records per segment: at least the call's shortest, seg_per W (the rebuild scans back to W
-// distinct keys) and the share that keeps the number of segments near kSegTarget. A candidate
-// whose wavefronts hold G lists (k_replay_grp) takes segments G times shorter, so that it
-// still has as many wavefronts.
-__host__ __device__ __forceinline__ uint32_t seg_len(uint32_t W, const WArg& wa, uint32_t G)
-{
-    uint32_t s = wa.seg_per * W;
-    s = s > wa.seg_min ? s : wa.seg_min;
-    s = s > 65536u ? 65536u : s;
-    if (G > 1u) s = s / G < kSegFloor ? kSegFloor : s / G;
-    return s;
-}
-
-// Lists per wavefront of a W-slot list in k_replay_grp (lane groups of 64 / G lanes), or 1
-// for the one-wavefront-per-list kernels. Only calls with one interval: the grouped kernel
-// keeps one set of statistics per segment. Two lists per wavefront (W <= 32) measured
-// slower than one on the 1e8-request sweep (10.2 against 7.2 ms for its W = 26 plans).
-__host__ __device__ __forceinline__ uint32_t grp_of(uint32_t W, uint32_t J)
-{
-    if (J != 1u || W > 16u) return 1u;
-    return W <= 8u ? 8u : 4u;
-}
-
 // Classes of k_replay: the largest W and the slots of the hash table. Class 0 replays by the
 // list in a register; the hash form, in the others, needs W >= 64. Table sizes by measurement, 4e7 requests x 8 candidates over 1,024
 // streams: W = 86 2.67 / 2.69 / 2.83 ms with 384 / 512 / 640 slots, W = 156 3.12 / 2.95 / 2.78
@@ -119,20 +72,6 @@ __host__ __device__ __forceinline__ uint32_t rep_class(uint32_t W)
     uint32_t cls = 0;
     while (cls + 1u < kClasses && W > (uint32_t)kMaxW[cls]) ++cls;
     return cls;
-}
-
-struct PartGeom {
-    uint64_t tile;
-    uint64_t ntiles;
-};
-
-inline PartGeom part_geom(uint64_t n, uint32_t P)
-{
-    const uint64_t target = 16384u / P > 0 ? 16384u / P : 1u;
-    uint64_t tile = (n + target - 1) / target;
-    tile = (tile + 1023) & ~1023ull;  // whole sub-tiles of the scatter
-    if (tile < 1024) tile = 1024;
-    return PartGeom{tile, n ? (n + tile - 1) / tile : 0};
 }
 
 // Per-tile destination counts; with aligned rows (kVec) every thread reads four
@@ -1558,47 +1497,6 @@ __global__ __launch_bounds__(kReplayThreads) void k_replay_grp(
     }
 }
 
-struct ReplayWs {
-    uint64_t* rec;
-    uint32_t* tcnt;
-    uint32_t* dtot;
-    uint32_t* grp_off;
-    uint32_t* item_off;
-    uint32_t* gwave_off;  // [P + 1] first k_replay_grp wavefront of each candidate
-    uint8_t* aborted;  // byte per work item: its rebuild ran out of budget
-    size_t bytes;
-};
-
-inline ReplayWs replay_layout(void* base, uint64_t n, uint32_t P, uint32_t R)
-{
-    const PartGeom g = part_geom(n, P);
-    auto up = [](uint64_t x) { return (x + 255) & ~255ull; };
-    uint8_t* b = reinterpret_cast<uint8_t*>(base);
-    uint64_t o = 0;
-    ReplayWs w{};
-    w.rec = reinterpret_cast<uint64_t*>(b + o);
-    o = up(o + (uint64_t)P * n * 8u);
-    w.tcnt = reinterpret_cast<uint32_t*>(b + o);
-    o = up(o + (uint64_t)P * R * g.ntiles * 4u);
-    w.dtot = reinterpret_cast<uint32_t*>(b + o);
-    o = up(o + (uint64_t)P * R * 4u);
-    w.grp_off = reinterpret_cast<uint32_t*>(b + o);
-    o = up(o + (uint64_t)P * (R + 1u) * 4u);
-    w.item_off = reinterpret_cast<uint32_t*>(b + o);
-    o = up(o + ((uint64_t)P * R + 1u) * 4u);
-    w.gwave_off = reinterpret_cast<uint32_t*>(b + o);
-    o = up(o + ((uint64_t)P + 1u) * 4u);
-    // The marks of cr_replay_lru take the place of the tile counts, which the scatter was the
-    // last to read: P R + P n / S items at most, S >= max(kSegShort, P n / kSegTarget), against
-    // 4 P R ntiles bytes with ntiles >= min(n / 1024, kSegTarget / P - 1); without requests,
-    // P R items in the 4 P R bytes of the destination totals.
-    w.aborted = reinterpret_cast<uint8_t*>(g.ntiles ? w.tcnt : w.dtot);
-    // a bit per P R + P n / kSegFloor items, which earlier layouts kept here: the size stays
-    o = up(o + (((uint64_t)P * R + (uint64_t)P * n / kSegFloor + 1u + 31u) / 32u) * 4u);
-    w.bytes = (size_t)o + 256u;
-    return w;
-}
-
 struct ReplayArgs {
     WArg wa;
     uint32_t classes;    // bit rep_class: some candidate's list is of that class
@@ -1619,14 +1517,7 @@ inline cr_status replay_args(uint64_t n, uint32_t J, uint32_t P, uint32_t R, con
         max_W > CR_MAX_W || !ws || n >= 0xFFFFFFFFull)
         return CR_EINVAL;
     ra->wa = WArg{};
-    const uint64_t recs = n * P;
-    const uint64_t share = (recs + kSegTarget - 1) / kSegTarget;
-    const uint32_t floor_ = recs >= kSegFull ? kSegFloor : (uint32_t)(recs * kSegFloor / kSegFull);
-    ra->wa.seg_min = share > 65536u ? 65536u : (uint32_t)share;
-    ra->wa.seg_min = ra->wa.seg_min > floor_ ? ra->wa.seg_min : floor_;
-    ra->wa.seg_min = ra->wa.seg_min > kSegShort ? ra->wa.seg_min : kSegShort;
-    ra->wa.seg_per = recs >= kSegFull ? kSegPerSlot : (uint32_t)(recs * kSegPerSlot / kSegFull);
-    ra->wa.seg_per = ra->wa.seg_per > kSegPerSlotShort ? ra->wa.seg_per : kSegPerSlotShort;
+    seg_rule(n, P, &ra->wa);
     ra->classes = 0;
     ra->wclasses = 0;
     ra->groups = 0;
@@ -1859,7 +1750,7 @@ extern "C" cr_status cr_replay_lru(const uint32_t* prefix_len, uint32_t num_keys
 #undef CR_REPLAY
     };
     // The list classes' launches and the grouped ones are independent of each other (other
-    // candidates; the marked-segment bitmap takes atomic ORs); the kSeq passes read what all
+    // candidates; every work item has a mark of its own); the kSeq passes read what all
     // of them marked, so they follow on the caller's stream after the join. A call under
     // stream capture keeps everything on the caller's stream.
     uint32_t nlaunch = __builtin_popcount(ra.wclasses) + __builtin_popcount(ra.groups);

@@ -102,3 +102,13 @@ def test_grouped_replay_carried_state(cut):
     np.testing.assert_array_equal(hb["stats"], orc_b["stats"])
     for c, cand in enumerate(b.candidates):
         np.testing.assert_array_equal(hb["lru"][c, :, :cand.W], orc_b["lru"][c])
+
+
+@pytest.mark.parametrize("n,P,R", [(20_000_000, 8, 2), (1_300_000, 64, 1)])
+def test_grouped_replay_of_long_streams_over_few_destinations(n, P, R):
+    # more segments than 4 P R tiles: their marks have to stay clear of the tables beside them
+    wl = wl_mod.small_random(214, num_keys=20_000, n=n, R=R, Ws=[8] * P, J=1)
+    say(f"[case] grouped lists, n={n} P={P} R={R}")
+    gp = Pipeline(wl)
+    gp.step()
+    compare_all(wl, gp, gp.host(), opipe.run(wl, threads=8))
