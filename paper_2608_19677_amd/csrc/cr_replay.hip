@@ -456,7 +456,8 @@ __global__ __launch_bounds__(64 * wide_waves<kOne>(), kOne ? 4 : 3) void k_part_
         // read one common representative (whichever write landed last); each lane then sets
         // its bit in the representative's peer mask and reads the mask. LDS operations of a
         // wavefront complete in order, so no barrier is needed, and the counter updates of
-        // chunk m precede those of chunk m + 1.
+        // chunk m precede those of chunk m + 1; the fences keep the compiler from answering a
+        // lane's read with the value the lane itself stored.
 #pragma unroll
         for (uint32_t m = 0; m < kWideChunks; m += 2) {
             uint32_t dd[2], jj[2];
@@ -480,9 +481,11 @@ __global__ __launch_bounds__(64 * wide_waves<kOne>(), kOne ? 4 : 3) void k_part_
             const uint32_t b0 = vv[0] ? dd[0] : R4, b1 = vv[1] ? dd[1] : R4;
             tag0[b0] = (uint8_t)lane;
             tag1[b1] = (uint8_t)lane;
+            wave_lds_fence();
             const uint32_t rep0 = tag0[b0], rep1 = tag1[b1];
             atomicOr(&pm0[rep0], 1ull << lane);
             atomicOr(&pm1[rep1], 1ull << lane);
+            wave_lds_fence();
             const uint64_t peers0 = pm0[rep0], peers1 = pm1[rep1];
             const uint32_t rk0 = mbcnt64(peers0), rk1 = mbcnt64(peers1);
             const uint32_t ld0 = (uint32_t)__builtin_ctzll(peers0), ld1 = (uint32_t)__builtin_ctzll(peers1);
@@ -499,6 +502,7 @@ __global__ __launch_bounds__(64 * wide_waves<kOne>(), kOne ? 4 : 3) void k_part_
                 mv[m] |= jj[0] << 16;
                 mv[m + 1] |= jj[1] << 16;
             }
+            wave_lds_fence();
         }
         __syncthreads();
         // destination runs in the sub-tile: each wavefront's slot base within its destination's
