@@ -1096,10 +1096,10 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_scatter(uint32_t Cmax, ui
         const uint32_t d = valid ? ((mx - kv[m].x) >> (11u * pass)) & (kWideDigits - 1u) : 0u;
         s_peer[wv][lane] = 0ull;
         if (valid) s_tag[wv][d] = (uint8_t)lane;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
         const uint32_t rep = valid ? s_tag[wv][d] : lane;
         if (valid) atomicOr(&s_peer[wv][rep], 1ull << lane);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
         const uint64_t peers = valid ? (uint64_t)s_peer[wv][rep] : 0ull;
         const uint32_t rk = (uint32_t)__popcll(peers & lanemask_lt());
         uint32_t old = 0;
@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_scatter(uint32_t Cmax, ui
         const uint32_t leader = valid ? (uint32_t)__builtin_ctzll(peers) : lane;
         old = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(leader << 2), (int)old);
         dr[m] = d | ((old + rk) << 16);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
     }
     __syncthreads();
     // first output position of every (digit, wavefront): digits before, tiles before, wavefronts before

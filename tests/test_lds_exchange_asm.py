@@ -12,8 +12,8 @@ import pytest
 
 from paper_2608_19677_amd import build as hip_build
 
-# source, kernel, instances, chunks of 64 requests per wavefront (unrolled: a store and a read each)
-KERNELS = [("cr_replay.hip", "k_part_scatter_wide", 2, 16)]
+# source, kernel, instances, chunks of 64 entries per wavefront (unrolled: a store and a read each)
+KERNELS = [("cr_replay.hip", "k_part_scatter_wide", 2, 16), ("cr_plan.hip", "k_wide_scatter", 1, 16)]
 
 
 @pytest.mark.parametrize("source,kernel,instances,chunks", KERNELS, ids=[k[1] for k in KERNELS])
