@@ -623,12 +623,12 @@ __global__ __launch_bounds__(kSortBlock, kNpl <= 20 ? 8 : 1) void k_sort_window_
 //   k_wide_digits / k_wide_offsets / k_wide_scatter  else, per 11 bits of (max - count): digit
 //                   counts per tile of 4,096 entries, their prefix over the tiles, and the
 //                   stable scatter (passes past the range exit)
-// Scratch: the window's two buffers in the workspace and, before anything is known to be kept,
-// its rows of order and order_count. Every launch is a few microseconds of latency: cr_admit of 1,920
+// Scratch: the window's two buffers in the workspace (its rows of order and order_count are
+// written where entries are kept and nowhere else). Every launch is a few microseconds of latency: cr_admit of 1,920
 // from 128,824 keys 326 -> 74 us, of 524,288 from 1,000,000 3,290 -> 365 us, 24 windows of
 // 128,824 244 -> 155 us.
 // ---------------------------------------------------------------------------------------
-constexpr uint32_t kWideCmax = 1024;   // smallest C_max whose buffers hold the bins
+constexpr uint32_t kWideCmax = 1024;   // smallest C_max whose buffers hold the scratch
 // Smallest row. 100 windows of 50,000 keys took 99 us with a block each (they fill the chip by
 // themselves) and 162 us this way.
 constexpr uint32_t kWideKeys = 73728, kWideKeysPerWindow = 1536;
@@ -639,7 +639,7 @@ constexpr uint32_t kWideSmall = 4096;  // largest C_max sorted by one block
 constexpr uint32_t kWideTile = 4096;   // entries per tile of a radix pass
 constexpr uint32_t kWideDigits = 2048; // 11 bits
 
-// Per window, at the start of its second buffer.
+// Per window, in its second buffer.
 struct WideHead {
     uint32_t mx, t, take, M;  // largest count, threshold, entries equal to it that are kept, entries kept
     uint32_t low[32];         // the last refinement's bins
@@ -662,22 +662,34 @@ __device__ __forceinline__ uint32_t wide_bin(uint32_t c)
     return 64u + (e - 6u) * 64u + ((c >> (e - 6u)) & 63u);
 }
 
+// A window's two buffers (2 C_max words each): the bins and the second refinement's from the
+// first's start, then, from the second buffer's start or past those bins, the head, the tiles'
+// counts and the first refinement's bins. Compaction may fill the first buffer with entries: it
+// needs the head and the tiles only; the radix passes' counters then lie where the tiles were.
+constexpr uint32_t kWideTiles = 132;  // tiles of a row (at most 129: wide_tile)
+constexpr uint32_t kWideHeadWords = sizeof(WideHead) / 4u;
+static_assert(kWideBins + kWideSub + kWideHeadWords + 2u * kWideTiles + kWideSub <= 4u * kWideCmax &&
+                  (kWideBins + kWideSub) % 2u == 0 && kWideHeadWords % 2u == 0,
+              "the smallest buffers hold the scratch, tiles and entries aligned");
+
 struct WideWin {
-    uint32_t* bins;           // [kWideBins], in the first buffer until it takes the entries
+    uint32_t* bins;           // [kWideBins]
+    uint32_t *sub1, *sub2;    // [kWideSub] each
     WideHead* head;
-    uint2* tiles;             // per tile {above, equal}, after the head
-    uint32_t *sub1, *sub2;    // [kWideSub] each, in order and order_count
+    uint2* tiles;             // [kWideTiles] {above, equal}
+    uint32_t *ord, *ocnt;     // the window's rows of order and order_count
     uint2* b0;
-    uint32_t* counters;       // [tile][kWideDigits], then the totals: the second buffer again
+    uint32_t* counters;       // [tile][kWideDigits], then the totals
 };
 
 __device__ __forceinline__ WideWin wide_win(uint2* buf, uint32_t* order, uint32_t* order_count, uint32_t Cmax, uint32_t w)
 {
     uint2* b0 = buf + (uint64_t)w * 2u * Cmax;
-    uint2* b1 = b0 + Cmax;
-    return WideWin{reinterpret_cast<uint32_t*>(b0), reinterpret_cast<WideHead*>(b1),
-                   b1 + (sizeof(WideHead) + 7u) / 8u, order + (uint64_t)w * Cmax, order_count + (uint64_t)w * Cmax, b0,
-                   reinterpret_cast<uint32_t*>(b1 + (sizeof(WideHead) + 7u) / 8u)};
+    uint32_t* words = reinterpret_cast<uint32_t*>(b0);
+    uint32_t* head = words + (2u * Cmax > kWideBins + kWideSub ? 2u * Cmax : kWideBins + kWideSub);
+    uint32_t* tiles = head + kWideHeadWords;
+    return WideWin{words, tiles + 2u * kWideTiles, words + kWideBins, reinterpret_cast<WideHead*>(head),
+                   reinterpret_cast<uint2*>(tiles), order + (uint64_t)w * Cmax, order_count + (uint64_t)w * Cmax, b0, tiles};
 }
 
 // From the top of `nbins` bins down: the bin in which the need-th entry lies, and how many of
@@ -933,8 +945,8 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_compact(const uint32_t* _
         const uint32_t pos = at + (uint32_t)__popcll(ms & lanemask_lt());
         if (sel && pos < M) {
             if (soa) {
-                order[(uint64_t)w * Cmax + pos] = b;
-                order_count[(uint64_t)w * Cmax + pos] = c;
+                ww.ord[pos] = b;
+                ww.ocnt[pos] = c;
             } else {
                 ww.b0[pos] = make_uint2(c, b);
             }
@@ -1009,15 +1021,15 @@ __global__ __launch_bounds__(kSortBlock) void k_wide_sort(uint32_t Cmax, uint32_
         dst = tmp;
     }
     for (uint32_t e = tid; e < M; e += kSortBlock) {
-        ww.sub1[e] = src[e].y;  // the window's rows of order and order_count
-        ww.sub2[e] = src[e].x;
+        ww.ord[e] = src[e].y;
+        ww.ocnt[e] = src[e].x;
     }
 }
 
 // One radix pass: entries of the pass's source, by index.
 __device__ __forceinline__ uint2 wide_entry(const WideWin& ww, bool from_b0, uint32_t e)
 {
-    return from_b0 ? ww.b0[e] : make_uint2(ww.sub2[e], ww.sub1[e]);
+    return from_b0 ? ww.b0[e] : make_uint2(ww.ocnt[e], ww.ord[e]);
 }
 
 __global__ __launch_bounds__(kWideThreads) void k_wide_digits(uint32_t Cmax, uint32_t pass, uint32_t* __restrict__ order,
@@ -1034,7 +1046,7 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_digits(uint32_t Cmax, uin
     __syncthreads();
     const uint32_t e1 = M - e0 < kWideTile ? M : e0 + kWideTile;
     for (uint32_t e = e0 + tid; e < e1; e += kWideThreads)
-        atomicAdd(&s_h[((mx - (from_b0 ? ww.b0[e].x : ww.sub2[e])) >> (11u * pass)) & (kWideDigits - 1u)], 1u);
+        atomicAdd(&s_h[((mx - (from_b0 ? ww.b0[e].x : ww.ocnt[e])) >> (11u * pass)) & (kWideDigits - 1u)], 1u);
     __syncthreads();
     uint32_t* __restrict__ out = ww.counters + (uint64_t)blockIdx.x * kWideDigits;
     for (uint32_t d = tid; d < kWideDigits; d += kWideThreads) out[d] = s_h[d];
@@ -1141,8 +1153,8 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_scatter(uint32_t Cmax, ui
         const uint32_t at = s_cnt[wv][dr[m] & 0xFFFFu] + (dr[m] >> 16);
         if (at >= M) continue;
         if (from_b0) {
-            ww.sub1[at] = kv[m].y;
-            ww.sub2[at] = kv[m].x;
+            ww.ord[at] = kv[m].y;
+            ww.ocnt[at] = kv[m].x;
         } else {
             ww.b0[at] = kv[m];
         }

@@ -107,3 +107,30 @@ def test_window_order_of_wide_rows(K, R, W, NW, kind):
         np.testing.assert_array_equal(ps.order_count[w, :m].cpu().numpy().view(np.uint32), rows[w][keys])
         assert int(ps.cold[w]) == int(rows[w].astype(np.uint64).sum() - rows[w][keys].astype(np.uint64).sum())
     assert int(err) == 0
+
+
+@pytest.mark.parametrize("R,W", [(64, 16), (43, 32), (32, 64), (64, 64), (50, 100)])
+def test_wide_rows_leave_unused_entries_alone(R, W):
+    # entries of order and order_count past n_order are the caller's; rows of few nonzero keys, of
+    # counts wide enough for every refinement (kept whole rows), and an empty one
+    K, NW = 80_009, 3
+    rng = np.random.default_rng(R)
+    rows = np.zeros((NW, K), np.uint32)
+    rows[0, rng.choice(K, 700, replace=False)] = rng.integers(1, 1 << 32, 700)
+    rows[1] = rng.integers(1, 1 << 32, K)
+    say(f"[case] unused entries, Cmax={R * W}")
+    ps = B.PlanSet([(w, W, B.CR_WINDOW_SUM, 1, 1, B.CR_PLAN_AFFINITY, 0) for w in range(NW)], 1, R, W, K, NW, "cuda")
+    ps.order.fill_(0x5A5A5A5A)
+    ps.order_count.fill_(0x3C3C3C3C)
+    ws = torch.empty(B.cr_admit_workspace_bytes(NW, R, W), dtype=torch.uint8, device="cuda")
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    B.cr_admit(torch.from_numpy(rows.view(np.int32)).cuda(), ps.c, ws, err)
+    assert int(err) == 0
+    for w, m in enumerate((700, R * W, 0)):
+        keys = np.nonzero(rows[w])[0]
+        keys = keys[np.lexsort((keys, -rows[w][keys].astype(np.int64)))][:m]
+        got, cnt = ps.order[w].cpu().numpy(), ps.order_count[w].cpu().numpy()
+        assert int(ps.n_order[w]) == m
+        np.testing.assert_array_equal(got[:m].view(np.uint32), keys)
+        np.testing.assert_array_equal(cnt[:m].view(np.uint32), rows[w][keys])
+        assert np.all(got[m:] == 0x5A5A5A5A) and np.all(cnt[m:] == 0x3C3C3C3C)
