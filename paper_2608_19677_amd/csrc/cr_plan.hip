@@ -1774,7 +1774,8 @@ __global__ __launch_bounds__(64) void k_lpt_small(uint32_t KW, uint32_t R, uint3
 //
 // The tail of the order is long runs of one count x. Placing them is popping the smallest of
 // the pairs {(L_i + j x, i), j >= 0} J times, and as long as no load leaves the power of two
-// that the smallest load lies in, every such sum is exact (all are multiples of its last bit).
+// that the smallest load lies in, every such sum is exact (all are multiples of its last bit,
+// the counts too while the loads are below 2^53; from there on no epochs are taken).
 // With L_0 the smallest load, write L_i = L_0 + e_i x + f_i, 0 <= f_i < x: in epoch e the loads
 // in [L_0 + e x, L_0 + (e + 1) x) are charged, once each, in the order of (f_i, i) among the
 // destinations with e_i <= e. So one sort by (f, i) serves up to kLptEpochs epochs (each a
@@ -1912,7 +1913,7 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
             // epochs before a load may leave the power of two of v0
             const double top = __longlong_as_double((long long)(((((uint64_t)__double_as_longlong(v0)) >> 52) + 1ull) << 52));
             const double fit = (top - v0) / x - 2.0;
-            const uint32_t emax = fit >= (double)kLptEpochs ? kLptEpochs : (fit >= 2.0 ? (uint32_t)fit : 0u);
+            const uint32_t emax = v0 >= 9007199254740992.0 ? 0u : (fit >= (double)kLptEpochs ? kLptEpochs : (fit >= 2.0 ? (uint32_t)fit : 0u));
             const uint64_t last = (uint64_t)t + (uint64_t)(lane + 1u) * R - 1u;
             const uint32_t m = (uint32_t)__popcll(ballot(last < A && ocnt[last < A ? (uint32_t)last : t] == c0));
             if (emax >= 2u && m >= kLptMinRounds) {

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from oracle import pipeline as opipe
 from paper_2608_19677_amd import binding as B
 from paper_2608_19677_amd import workload as wl_mod
@@ -134,3 +135,23 @@ def test_wide_rows_leave_unused_entries_alone(R, W):
         np.testing.assert_array_equal(got[:m].view(np.uint32), keys)
         np.testing.assert_array_equal(cnt[:m].view(np.uint32), rows[w][keys])
         assert np.all(got[m:] == 0x5A5A5A5A) and np.all(cnt[m:] == 0x3C3C3C3C)
+
+
+@pytest.mark.parametrize("R", [64, 65, 300])
+def test_lpt_loads_beyond_the_integers_of_a_double(R):
+    # equal counts on loads of 2^53 and more: every charge rounds, so no two may be added as one
+    K = int(R * 2**53 / (2**32 - 1) * 1.01) // 64 * 64 + 3
+    W = 5 * 1024 // R
+    say(f"[case] loads past 2^53, R={R} K={K}")
+    counts = torch.full((1, K), -1, dtype=torch.int32, device="cuda")
+    ps = B.PlanSet([(0, W, B.CR_WINDOW_SUM, 1, 1, B.CR_PLAN_FULL, 0)], 1, R, W, K, 1, "cuda")
+    ws = torch.empty(B.cr_admit_workspace_bytes(1, R, W), dtype=torch.uint8, device="cuda")
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    B.cr_admit(counts, ps.c, ws, err)
+    B.cr_place_lpt(counts, ps.c)
+    A = R * W
+    cold = (K - A) * (2**32 - 1)
+    members, _, load = oracle.place_lpt(np.arange(A, dtype=np.uint32), np.ones(A, np.uint32), np.full(A, 0xFFFFFFFF, np.uint32), R, cold)
+    assert int(err) == 0 and int(ps.num_admitted[0]) == A and int(ps.cold[0]) == cold and load.min() >= 2.0**53
+    np.testing.assert_array_equal(ps.members[0, :A].cpu().numpy().view(np.uint16), members)
+    np.testing.assert_array_equal(ps.load[0].cpu().numpy().view(np.uint64), load.view(np.uint64))
