@@ -473,6 +473,13 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_group(
 // between its member and itself. The lookups of the next batches (key, key-index entry, route
 // word: three dependent gathers) are in flight while a batch is decided.
 //
+// The fewer the destinations, the more of a batch's requests meet and the more passes it takes.
+// Up to kLiveFew destinations the masks are therefore ballots, and a pass makes no LDS round
+// trip. 200 intervals of 10,000 requests, hardly anything admitted, 2 / 3 / 4 destinations: 394 us
+// by a serial walk, 430 / 431 / 390 with the masks in LDS, 291 / 299 / 278 with ballots; 5
+// destinations 396 by the walk, 362 in LDS; most requests of admitted keys, 2 destinations: 395,
+// 211 and 166.
+//
 // The requests of a key of k > 1 members depend on each other one by one (each takes the least
 // loaded), so a batch that holds one is walked in order, with a member choice as one minimum
 // over the lanes: with R <= 64 lane r holds destination r's load and a request's members are a
@@ -493,6 +500,16 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
     return rdlane(v, 63u);
 }
 
+constexpr uint32_t kLiveFew = 4;
+
+// c[d] for d < kLiveFew
+__device__ __forceinline__ uint32_t pick_few(const uint32_t (&c)[kLiveFew], uint32_t d)
+{
+    const uint32_t even = d & 2u ? c[2] : c[0], odd = d & 2u ? c[3] : c[1];
+    return d & 1u ? odd : even;
+}
+
+template <bool kFew>  // R <= kLiveFew
 __global__ __launch_bounds__(64) void k_route_live(
     const uint32_t* __restrict__ keys, uint64_t n, uint64_t first_index, uint32_t smix,
     const uint64_t* __restrict__ off, const uint32_t* __restrict__ gmap, uint32_t K, uint32_t R, uint32_t cands,
@@ -551,30 +568,63 @@ __global__ __launch_bounds__(64) void k_route_live(
         uint32_t out = 0;
         if (multi == 0) {
             const uint32_t l1 = s_live[d1], l2 = s_live[d2];
-            out = l2 < l1 ? d2 : d1;
-            if (in) atomicOr(&s_mask[out], 1ull << lane);
-            wave_lds_fence();
-            for (;;) {
-                const uint32_t n1 = mbcnt_mask(s_mask[d1]), n2 = mbcnt_mask(s_mask[d2]);
+            if (kFew) {
+                // second: the lanes that choose their second draw
+                const uint64_t all = ballot(in);
+                uint64_t first[kLiveFew], other[kLiveFew], second = ballot(l2 < l1) & all;
+#pragma unroll
+                for (uint32_t r = 0; r < kLiveFew; ++r) {
+                    first[r] = ballot(d1 == r) & all;
+                    other[r] = ballot(d2 == r) & all;
+                }
+                // l1 - l2, cut where the 63 earlier lanes cannot matter
+                const int32_t lead = l1 > l2 ? (int32_t)(l1 - l2 < 64u ? l1 - l2 : 64u) : -(int32_t)(l2 - l1 < 64u ? l2 - l1 : 64u);
+                uint32_t sent[kLiveFew];  // of the batch
+                for (;;) {
+                    uint32_t before[kLiveFew];  // of the lanes before this one
+#pragma unroll
+                    for (uint32_t r = 0; r < kLiveFew; ++r) {
+                        const uint64_t m = (second & other[r]) | (first[r] & ~second);
+                        sent[r] = (uint32_t)__popcll(m);
+                        before[r] = mbcnt64(m);
+                    }
+                    const uint64_t now = ballot((int32_t)(pick_few(before, d2) - pick_few(before, d1)) < lead) & all;
+                    if (now == second) break;
+                    second = now;
+                }
+                out = __builtin_amdgcn_inverse_ballot_w64(second) ? d2 : d1;
+                uint32_t mine = 0;  // lane r: the batch's requests sent to destination r
+#pragma unroll
+                for (uint32_t r = 0; r < kLiveFew; ++r) mine = lane == r ? sent[r] : mine;
                 wave_lds_fence();
-                const uint32_t q = l2 + n2 < l1 + n1 ? d2 : d1;
-                const bool change = in && q != out;
-                if (ballot(change) == 0ull) break;
-                if (change) {
-                    atomicXor(&s_mask[out], 1ull << lane);
-                    atomicXor(&s_mask[q], 1ull << lane);
-                    out = q;
+                if (lane < R) s_live[lane] += mine;
+                wave_lds_fence();
+            } else {
+                out = l2 < l1 ? d2 : d1;
+                if (in) atomicOr(&s_mask[out], 1ull << lane);
+                wave_lds_fence();
+                for (;;) {
+                    const uint32_t n1 = mbcnt_mask(s_mask[d1]), n2 = mbcnt_mask(s_mask[d2]);
+                    wave_lds_fence();
+                    const uint32_t q = l2 + n2 < l1 + n1 ? d2 : d1;
+                    const bool change = in && q != out;
+                    if (ballot(change) == 0ull) break;
+                    if (change) {
+                        atomicXor(&s_mask[out], 1ull << lane);
+                        atomicXor(&s_mask[q], 1ull << lane);
+                        out = q;
+                    }
+                    wave_lds_fence();
+                }
+                // the batch's counts, by the last lane of every destination
+                const uint64_t m = in ? (uint64_t)s_mask[out] : 0ull;
+                wave_lds_fence();
+                if (in) {
+                    if ((m >> lane) == 1ull) s_live[out] += (uint32_t)__popcll(m);
+                    s_mask[out] = 0ull;
                 }
                 wave_lds_fence();
             }
-            // the batch's counts, by the last lane of every destination
-            const uint64_t m = in ? (uint64_t)s_mask[out] : 0ull;
-            wave_lds_fence();
-            if (in) {
-                if ((m >> lane) == 1ull) s_live[out] += (uint32_t)__popcll(m);
-                s_mask[out] = 0ull;
-            }
-            wave_lds_fence();
         } else {
             const uint32_t nb = i1 - base < 64u ? (uint32_t)(i1 - base) : 64u;
             const bool is = (multi >> lane) & 1ull;
@@ -669,10 +719,14 @@ extern "C" cr_status cr_route_live(const uint32_t* keys, uint64_t n, uint64_t fi
     if (blocks > 0x7FFFFFF0ull) return CR_EINVAL;
     const uint32_t cmax = plans->R * plans->max_W;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_route_live, dim3((uint32_t)blocks), dim3(64), (size_t)plans->R * 12u, as_stream(stream), keys, n,
-                       first_index, seed_mix(seed), off, gmap, plans->num_keys, plans->R, plans->cands,
-                       plans->num_plans / plans->cands, (plans->num_keys + 63u) / 64u, plans->key_index, plans->route,
-                       plans->member_off, cmax, plans->members, dest, err);
+#define CR_LIVE(FEW)                                                                                                \
+    hipLaunchKernelGGL(k_route_live<FEW>, dim3((uint32_t)blocks), dim3(64), (size_t)plans->R * 12u, as_stream(stream), \
+                       keys, n, first_index, seed_mix(seed), off, gmap, plans->num_keys, plans->R, plans->cands,      \
+                       plans->num_plans / plans->cands, (plans->num_keys + 63u) / 64u, plans->key_index, plans->route, \
+                       plans->member_off, cmax, plans->members, dest, err)
+    if (plans->R <= kLiveFew) CR_LIVE(true);
+    else CR_LIVE(false);
+#undef CR_LIVE
     return hipGetLastError() == hipSuccess ? CR_OK : CR_EHIP;
 }
 

@@ -31,3 +31,15 @@ def test_live_members(case):
     gp = Pipeline(wl, dispatch="live")
     gp.step()
     compare_all(wl, gp, gp.host(), opipe.run(wl, dispatch="live"))
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("W,n,hot", [(1, 64 * 90 + 3, 0), (40, 20_001, 0), (6, 9_000, 2)])
+def test_live_few_destinations(R, W, n, hot):
+    # both sides of the line between masks as ballots and masks in LDS: hardly anything admitted
+    # (many passes per batch), most of it, and batches with replicated keys between the others
+    wl = wl_mod.small_random(60 + R, num_keys=1200, n=n, R=R, Ws=[W], J=5, hot=hot, hot_share=0.02 * hot, qs=[(1, 8 if hot else 1)])
+    say(f"[case] live, R={R} W={W}")
+    gp = Pipeline(wl, dispatch="live")
+    gp.step()
+    compare_all(wl, gp, gp.host(), opipe.run(wl, dispatch="live"))
