@@ -1,5 +1,6 @@
 """GPU parity of interval counting for key spaces beyond one block's LDS: one to 32 ranges and
-past them, intervals that are one part, several parts or empty, streams that start off a
+past them, intervals that are one part, several parts or empty, most requests in one of many
+intervals, intervals across the bounds by which items are numbered, streams that start off a
 16-byte boundary, out-of-range keys. Reference: numpy.bincount per interval."""
 import numpy as np
 import pytest
@@ -16,6 +17,7 @@ CASES = [
     (40_900, [10_000, 0, 1, 70_001], 0, False), (41_000, [131_072, 131_073, 5], 1, False), (81_801, [400_003], 2, True),
     (128_824, [1] * 30 + [600_000] + [0] * 5 + [17], 3, False), (1_000_000, [200_000, 300_001], 1, True),
     (1_300_000, [50_000, 1000], 0, True),  # more than 32 ranges: one atomic per request
+    (50_000, [3] * 500 + [1_000_003] + [7] * 500, 1, False), (45_001, [100_000] * 9, 2, False), (45_001, [131_072] * 3 + [0] * 70 + [1], 0, False),
     (50_000, [37] * 3000, 0, False), (20_000, [300_000, 5], 3, True), (300, [100] * 400, 1, False),
 ]
 
