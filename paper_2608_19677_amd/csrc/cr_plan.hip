@@ -1782,11 +1782,20 @@ __global__ __launch_bounds__(64) void k_lpt_small(uint32_t KW, uint32_t R, uint3
 // batch of its own otherwise): the epochs' sizes are prefix lengths of the sorted state, a
 // job's place in its epoch is a count of active destinations before it (ballots), and the
 // new state is that sort order followed by the destinations still ahead.
-// One plan of 524,288 jobs over 1,024 destinations (611 batches, 403 of them of one count, bound
-// by their barriers and LDS round trips): 4,000 -> 2,480 us; 92 plans over 257 destinations
-// 709 -> 384 us. Route words are written afterwards by k_route_words, in parallel.
+// Which jobs start such a run is a bit per job beside the ring, made at its refills, so that
+// a batch pays one scalar compare for it; and where a batch's counts change is looked up only when its
+// charged pairs are out of order: a batch is bound by its barriers and by what 16 wavefronts
+// read from one CU's LDS (every read more was about 1 %).
+// One plan of 524,288 jobs over 1,024 destinations (611 batches, 403 of them of one count): 3,980 us
+// by batches alone, 2,020 us; 24 plans over 257 destinations 436 -> 231 us. Without long runs
+// (99,328 distinct counts, 1,024 destinations) 1,133 -> 936 us, by the sort's DPP steps.
+// Route words are written afterwards by k_route_words, in parallel.
 constexpr uint32_t kLptEpochs = 64;
-constexpr uint32_t kLptMinRounds = 2;  // rounds of R a run must cover for it (1 and 4 measured slower)
+// Rounds of R that a run must cover for it, in blocks up to 256 threads and above. An epoch run
+// costs about 8 us there (sort, three rounds of loads) against 1.5 to 2.5 us for a batch: with
+// 2, 4 and 6 rounds 188, 202 and 212 us (128 destinations, 16,384 jobs, mostly short runs),
+// 965, 908 and 896 us (65 destinations, 33,280 jobs, all loads within one count); above, 2 is best.
+constexpr uint32_t kLptRoundsSmall = 4, kLptRounds = 2;
 constexpr uint32_t kLptRuns = 3;       // sorted runs merged at once (2 and 4 measured slower)
 constexpr int kLptRunsFrom = 512;      // block size from which that beats the sort (small blocks: 98 against 86 us)
 
@@ -1805,56 +1814,86 @@ struct LptBlockLds {
     uint32_t l0r[N / 64];
     uint32_t wfail[N / 64];  // per-wavefront first position that fails the batch rule
     uint32_t wuns[N / 64];   // per-wavefront: 1 some charged pairs are out of order, 2 of one count
-    unsigned long long wbrk[N / 64];  // per-wavefront: positions whose next job has another count
-    uint32_t en[kLptEpochs + 2];      // destinations active in an epoch
+    unsigned long long run[2 * N / 64];  // ring: the jobs that start a run of one count long enough for epochs
+    uint32_t en[kLptEpochs + 2];         // destinations active in an epoch
 };
 
-// Number of pairs among (v[lo .. lo+len)) smaller than (x, rx); the list is sorted.
+// Number of pairs among (v[lo .. lo+len)) smaller than (x, rx); the list is sorted, and its
+// place and length are uniform, so that every lane takes the same steps.
 __device__ __forceinline__ uint32_t lower_bound_pair(const double* __restrict__ v, const uint32_t* __restrict__ r,
                                                      uint32_t lo, uint32_t len, double x, uint32_t rx)
 {
-    uint32_t n = len, b = lo;
-    while (n > 0) {
-        const uint32_t h = n >> 1;
-        const uint32_t m = b + h;
-        const double y = v[m];
-        if (y < x || (y == x && r[m] < rx)) {  // the index is read on ties only
-            b = m + 1;
-            n -= h + 1;
-        } else {
-            n = h;
-        }
+    uint32_t b = lo;
+    for (uint32_t n = len; n > 0;) {
+        const uint32_t h = (n + 1u) >> 1;
+        b += lt_pair(v[b + h - 1u], r[b + h - 1u], x, rx) ? h : 0u;
+        n -= h;
     }
     return b - lo;
 }
 
-// Bitonic sort of the block's N pairs, one per thread; tv and tr are scratch.
+// Bitonic sort of the block's N pairs, one per thread; tv and tr are scratch. A lane's partner in
+// its wavefront comes by DPP for 1, 2 and 8 lanes' distance, else by ds_bpermute.
+template <uint32_t J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v, uint32_t at)
+{
+    if (J == 1u) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+    if (J == 2u) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+    if (J == 8u) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(at ^ (J << 2)), (int)v);
+}
+
+// `flip`: the lane keeps the larger pair of the two.
+__device__ __forceinline__ void sort_keep(double& v, uint32_t& r, double pv, uint32_t pr, bool flip)
+{
+    const bool pless = lt_pair(pv, pr, v, r) != 0;
+    if (pless != flip) {
+        v = pv;
+        r = pr;
+    }
+}
+
+template <uint32_t J>
+__device__ __forceinline__ void wave_sort_step(double& v, uint32_t& r, uint32_t dir, uint32_t at)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = lane_xor<J>((uint32_t)b, at), hi = lane_xor<J>((uint32_t)(b >> 32), at);
+    sort_keep(v, r, __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32))), lane_xor<J>(r, at), (dir & J) != 0u);
+}
+
+template <int N>
+__device__ __forceinline__ void block_sort_round(double& v, uint32_t& r, double* tv, uint32_t* tr, uint32_t kk)
+{
+    const uint32_t i = threadIdx.x, at = (i & 63u) << 2;
+    uint32_t dir = (i & kk) ? ~i : i;  // bit j: the step of distance j keeps the larger pair here
+    asm volatile("" : "+v"(dir));      // (the steps' lane masks are made where they are used: all at once, they spill)
+#pragma unroll 1
+    for (uint32_t j = kk >> 1; j >= 64u; j >>= 1) {
+        tv[i] = v;
+        tr[i] = r;
+        __syncthreads();
+        const double pv = tv[i ^ j];
+        const uint32_t pr = tr[i ^ j];
+        __syncthreads();
+        sort_keep(v, r, pv, pr, (dir & j) != 0u);
+    }
+    if (kk > 32u) wave_sort_step<32>(v, r, dir, at);
+    if (kk > 16u) wave_sort_step<16>(v, r, dir, at);
+    if (kk > 8u) wave_sort_step<8>(v, r, dir, at);
+    if (kk > 4u) wave_sort_step<4>(v, r, dir, at);
+    if (kk > 2u) wave_sort_step<2>(v, r, dir, at);
+    wave_sort_step<1>(v, r, dir, at);
+}
+
 template <int N>
 __device__ __forceinline__ void block_sort_pairs(double& v, uint32_t& r, double* tv, uint32_t* tr)
 {
-    const uint32_t i = threadIdx.x;
-    for (uint32_t kk = 2; kk <= N; kk <<= 1) {
-        for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-            double pv;
-            uint32_t pr;
-            if (j >= 64) {
-                tv[i] = v;
-                tr[i] = r;
-                __syncthreads();
-                pv = tv[i ^ j];
-                pr = tr[i ^ j];
-                __syncthreads();
-            } else {
-                pv = __shfl_xor(v, (int)j, 64);
-                pr = __shfl_xor(r, (int)j, 64);
-            }
-            const bool up = (i & kk) == 0, lower = (i & j) == 0;
-            const bool pless = lt_pair(pv, pr, v, r) != 0;
-            if (pless == (lower == up)) {
-                v = pv;
-                r = pr;
-            }
-        }
+    if (N <= 256) {
+#pragma unroll
+        for (uint32_t kk = 2; kk <= N; kk <<= 1) block_sort_round<N>(v, r, tv, tr, kk);
+    } else {
+#pragma unroll 1
+        for (uint32_t kk = 2; kk <= N; kk <<= 1) block_sort_round<N>(v, r, tv, tr, kk);
     }
 }
 
@@ -1883,113 +1922,127 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
     uint32_t r = i < R ? i : 0xFFFFFFFFu;
     sh.v[0][i] = v;
     sh.r[0][i] = r;
-    // job a: (count, member offset, k); k = 0 marks a >= A
-    auto job = [&](uint32_t a, uint32_t& c, uint32_t& o, uint32_t& k) {
-        const uint32_t aa = a < A ? a : 0u;
-        c = ocnt[aa];
-        o = moff[aa];
-        k = a < A ? moff[aa + 1] - o : 0u;
+    const uint32_t run_len = (N <= 256 ? kLptRoundsSmall : kLptRounds) * R;  // shortest run placed by epochs
+    struct Job {
+        uint32_t c, o, k, z;  // count, member offset, k (0 past A), count at the end of a run
     };
-    uint32_t pc, po, pk;  // job base + 2N + i, loaded one refill ahead
-    {
-        uint32_t c, o, k;
-        job(i, c, o, k);
-        sh.jc[i] = c, sh.jo[i] = o, sh.jk[i] = (uint16_t)k;
-        job(N + i, c, o, k);
-        sh.jc[N + i] = c, sh.jo[N + i] = o, sh.jk[N + i] = (uint16_t)k;
-        job(2 * N + i, pc, po, pk);
-    }
+    auto job = [&](uint32_t a) {
+        const uint32_t aa = a < A ? a : 0u;
+        Job q;
+        q.c = ocnt[aa];
+        q.o = moff[aa];
+        q.k = a < A ? moff[aa + 1] - q.o : 0u;
+        q.z = ocnt[a + run_len <= A ? a + run_len - 1u : aa];
+        return q;
+    };
+    auto put = [&](uint32_t a, const Job& q) {
+        const uint32_t slot = a & (2u * N - 1u);
+        sh.jc[slot] = q.c, sh.jo[slot] = q.o, sh.jk[slot] = (uint16_t)q.k;
+        const uint64_t starts = ballot(q.k == 1u && a + run_len <= A && q.z == q.c);
+        if (lane == 0) sh.run[slot >> 6] = starts;
+    };
+    const Job q0 = job(i), q1 = job(N + i);
+    Job pre = job(2 * N + i);  // job base + 2N + i, loaded one refill ahead
+    put(i, q0);
+    put(N + i, q1);
     static_assert(kLptEpochs == 64 && kLptEpochs * NWV * 4u <= sizeof(sh.cv), "epochs by lane; counts in cv");
     uint32_t cur = 0, base = 0, t = 0;
+    uint32_t next_run = 0;  // no job in t .. next_run - 1 starts a run to be placed by epochs
     __syncthreads();
     while (t < A) {
         const uint32_t rj = (t + i) & (2u * N - 1u), r0 = t & (2u * N - 1u);
         const uint32_t c = sh.jc[rj], o = sh.jo[rj], k = sh.jk[rj];
         const uint32_t k0 = sh.jk[r0];
-        if (k0 == 1 && t + R <= A && sh.jc[(t + R - 1u) & (2u * N - 1u)] == sh.jc[r0]) {
-            // a run of at least R jobs of one count (which then all have the same k)
-            const uint32_t c0 = sh.jc[r0], o0 = sh.jo[r0];
-            const double x = (double)c0, v0 = sh.v[cur][0];
-            // epochs before a load may leave the power of two of v0
-            const double top = __longlong_as_double((long long)(((((uint64_t)__double_as_longlong(v0)) >> 52) + 1ull) << 52));
-            const double fit = (top - v0) / x - 2.0;
-            const uint32_t emax = v0 >= 9007199254740992.0 ? 0u : (fit >= (double)kLptEpochs ? kLptEpochs : (fit >= 2.0 ? (uint32_t)fit : 0u));
-            const uint64_t last = (uint64_t)t + (uint64_t)(lane + 1u) * R - 1u;
-            const uint32_t m = (uint32_t)__popcll(ballot(last < A && ocnt[last < A ? (uint32_t)last : t] == c0));
-            if (emax >= 2u && m >= kLptMinRounds) {
-                // the run's jobs, up to 64 R of them: m R, and those of the next R
-                const uint64_t more = (uint64_t)t + (uint64_t)m * R + i;
-                const uint64_t same = ballot(m < 64u && i < R && more < A && ocnt[more < A ? (uint32_t)more : t] == c0);
-                uint32_t e = emax + 1u;
-                double f = 0.0;
-                if (i < R && v < v0 + (double)(emax + 1u) * x) {
-                    const double d = v - v0;
-                    double q = floor(d / x);
-                    f = d - q * x;
-                    if (f < 0.0) q -= 1.0, f += x;
-                    else if (f >= x) q += 1.0, f -= x;
-                    e = (uint32_t)q;
+        if (t >= next_run) {
+            // the next job in the ring that starts such a run
+            const uint32_t w0 = (t >> 6) + lane;
+            uint64_t starts = w0 < (base >> 6) + 2u * NWV ? sh.run[w0 & (2u * NWV - 1u)] : 0ull;
+            if (lane == 0) starts &= ~0ull << (t & 63u);
+            const uint64_t any = ballot(starts != 0ull);
+            const uint32_t u = any ? first_lane(any) : 0u;
+            next_run = any ? ((t >> 6) + u) * 64u + (uint32_t)__builtin_ctzll(rdlane64(starts, u)) : base + 2u * N;
+            if (t == next_run) {
+                const uint32_t c0 = sh.jc[r0], o0 = sh.jo[r0];
+                const double x = (double)c0, v0 = sh.v[cur][0];
+                // epochs before a load may leave the power of two of v0
+                const double top = __longlong_as_double((long long)(((((uint64_t)__double_as_longlong(v0)) >> 52) + 1ull) << 52));
+                const double fit = (top - v0) / x - 2.0;
+                const uint32_t emax = v0 >= 9007199254740992.0 ? 0u : (fit >= (double)kLptEpochs ? kLptEpochs : (fit >= 2.0 ? (uint32_t)fit : 0u));
+                if (emax >= 2u) {
+                    const uint64_t last = (uint64_t)t + (uint64_t)(lane + 1u) * R - 1u;
+                    const uint32_t m = (uint32_t)__popcll(ballot(last < A && ocnt[last < A ? (uint32_t)last : t] == c0));
+                    // the run's jobs, up to 64 R of them: m R, and those of the next R
+                    const uint64_t more = (uint64_t)t + (uint64_t)m * R + i;
+                    const uint64_t same = ballot(m < 64u && i < R && more < A && ocnt[more < A ? (uint32_t)more : t] == c0);
+                    uint32_t e = emax + 1u;
+                    double f = 0.0;
+                    if (i < R && v < v0 + (double)(emax + 1u) * x) {
+                        const double d = v - v0;
+                        double q = floor(d / x);
+                        f = d - q * x;
+                        if (f < 0.0) q -= 1.0, f += x;
+                        else if (f >= x) q += 1.0, f -= x;
+                        e = (uint32_t)q;
+                    }
+                    sh.cr[i] = e;  // nondecreasing in i
+                    if (lane == 0) sh.wfail[wv] = (uint32_t)__popcll(same);
+                    __syncthreads();
+                    const uint32_t en = i + 1u < (uint32_t)N ? sh.cr[i + 1u] : emax + 1u;
+                    for (uint32_t u = e; u < en && u <= emax; ++u) sh.en[u] = i + 1u;
+                    const uint32_t J = m * R + rdlane(wave_incl_scan_u32(lane < NWV ? sh.wfail[lane] : 0u), 63u);
+                    __syncthreads();
+                    // lane u: destinations active in epoch u and jobs before it; the epochs J covers
+                    // whole (E of them, at least one) and what it takes of the next
+                    const uint32_t na = lane < emax ? sh.en[lane] : 0u;
+                    const uint32_t incl = wave_incl_scan_u32(na);
+                    const uint32_t first = incl - na;
+                    const uint32_t E = (uint32_t)__popcll(ballot(lane + 1u < emax && incl <= J));
+                    const uint32_t whole = rdlane(incl, E - 1u), nE = sh.en[E];
+                    const uint32_t left = J - whole < nE ? J - whole : 0u;
+                    const uint32_t nP = sh.en[E + 1u];
+                    double sf = i < nP ? f : INF;
+                    uint32_t sr = i < nP ? (r << 7) | e : 0xFFFFFFFFu;
+                    // the ring starts again around the next job: its loads run under the sort
+                    t += whole + left;
+                    base = t & ~(uint32_t)(N - 1);
+                    const Job q0 = job(base + i), q1 = job(base + N + i);
+                    pre = job(base + 2 * N + i);
+                    block_sort_pairs<N>(sf, sr, sh.v[cur ^ 1u], sh.r[cur ^ 1u]);
+                    const uint32_t se = sr & 127u;
+                    const bool in = i < nP;
+                    uint32_t* __restrict__ wc = reinterpret_cast<uint32_t*>(sh.cv);  // [epoch][wavefront]
+                    uint32_t mine = 0;
+                    for (uint32_t u = 0; u <= E; ++u) {
+                        const uint32_t n = (uint32_t)__popcll(ballot(in && se <= u));
+                        mine = lane == u ? n : mine;
+                    }
+                    wc[lane * NWV + wv] = mine;
+                    __syncthreads();
+                    uint32_t at = 0;  // lane u: epoch u's active destinations in earlier wavefronts
+                    for (uint32_t u = 0; u < wv; ++u) at += wc[lane * NWV + u];
+                    uint32_t place = 0;
+                    for (uint32_t u = 0; u <= E; ++u) {
+                        const bool on = in && se <= u;
+                        const uint64_t om = ballot(on);
+                        place = rdlane(at, u) + __builtin_amdgcn_mbcnt_hi((uint32_t)(om >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)om, 0u));
+                        if (on && (u < E || place < left)) mem[o0 + rdlane(first, u) + place] = (uint16_t)(sr >> 7);
+                    }
+                    if (in) {
+                        // epoch E's uncharged ones, then epoch E + 1's
+                        const bool stay = se <= E && place >= left;
+                        const uint32_t pos = stay ? place - left : nE - left + i - (place > left ? place - left : 0u);
+                        sh.v[cur][pos] = (v0 + (double)(stay ? E : E + 1u) * x) + sf;
+                        sh.r[cur][pos] = sr >> 7;
+                    }
+                    put(base + i, q0);
+                    put(base + N + i, q1);
+                    __syncthreads();
+                    v = sh.v[cur][i];
+                    r = sh.r[cur][i];
+                    next_run = t;
+                    continue;
                 }
-                sh.cr[i] = e;  // nondecreasing in i
-                if (lane == 0) sh.wfail[wv] = (uint32_t)__popcll(same);
-                __syncthreads();
-                const uint32_t en = i + 1u < (uint32_t)N ? sh.cr[i + 1u] : emax + 1u;
-                for (uint32_t u = e; u < en && u <= emax; ++u) sh.en[u] = i + 1u;
-                const uint32_t J = m * R + rdlane(wave_incl_scan_u32(lane < NWV ? sh.wfail[lane] : 0u), 63u);
-                __syncthreads();
-                // lane u: destinations active in epoch u and jobs before it; the epochs J covers
-                // whole (E of them, at least one) and what it takes of the next
-                const uint32_t na = lane < emax ? sh.en[lane] : 0u;
-                const uint32_t incl = wave_incl_scan_u32(na);
-                const uint32_t first = incl - na;
-                const uint32_t E = (uint32_t)__popcll(ballot(lane + 1u < emax && incl <= J));
-                const uint32_t whole = rdlane(incl, E - 1u), nE = sh.en[E];
-                const uint32_t left = J - whole < nE ? J - whole : 0u;
-                const uint32_t nP = sh.en[E + 1u];
-                double sf = i < nP ? f : INF;
-                uint32_t sr = i < nP ? (r << 7) | e : 0xFFFFFFFFu;
-                block_sort_pairs<N>(sf, sr, sh.v[cur ^ 1u], sh.r[cur ^ 1u]);
-                const uint32_t se = sr & 127u;
-                const bool in = i < nP;
-                uint32_t* __restrict__ wc = reinterpret_cast<uint32_t*>(sh.cv);  // [epoch][wavefront]
-                uint32_t mine = 0;
-                for (uint32_t u = 0; u <= E; ++u) {
-                    const uint32_t n = (uint32_t)__popcll(ballot(in && se <= u));
-                    mine = lane == u ? n : mine;
-                }
-                wc[lane * NWV + wv] = mine;
-                __syncthreads();
-                uint32_t at = 0;  // lane u: epoch u's active destinations in earlier wavefronts
-                for (uint32_t u = 0; u < wv; ++u) at += wc[lane * NWV + u];
-                uint32_t place = 0;
-                for (uint32_t u = 0; u <= E; ++u) {
-                    const bool on = in && se <= u;
-                    const uint64_t om = ballot(on);
-                    place = rdlane(at, u) + __builtin_amdgcn_mbcnt_hi((uint32_t)(om >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)om, 0u));
-                    if (on && (u < E || place < left)) mem[o0 + rdlane(first, u) + place] = (uint16_t)(sr >> 7);
-                }
-                if (in) {
-                    // epoch E's uncharged ones, then epoch E + 1's
-                    const bool stay = se <= E && place >= left;
-                    const uint32_t pos = stay ? place - left : nE - left + i - (place > left ? place - left : 0u);
-                    sh.v[cur][pos] = (v0 + (double)(stay ? E : E + 1u) * x) + sf;
-                    sh.r[cur][pos] = sr >> 7;
-                }
-                t += whole + left;
-                // the ring starts again around t
-                base = t & ~(uint32_t)(N - 1);
-#pragma unroll
-                for (uint32_t h = 0; h < 2; ++h) {
-                    const uint32_t ja = base + h * N + i, slot = ja & (2u * N - 1u);
-                    uint32_t cc, oo, kk;
-                    job(ja, cc, oo, kk);
-                    sh.jc[slot] = cc, sh.jo[slot] = oo, sh.jk[slot] = (uint16_t)kk;
-                }
-                job(base + 2 * N + i, pc, po, pk);
-                __syncthreads();
-                v = sh.v[cur][i];
-                r = sh.r[cur][i];
-                continue;
+                next_run = t + R;
             }
         }
         double a;
@@ -2027,6 +2080,7 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
             for (uint32_t u = 0; u < NWV; ++u) M = min(M, sh.wfail[u]);
             if (i < M) mem[o] = (uint16_t)r;
         }
+        M = (uint32_t)__builtin_amdgcn_readfirstlane((int)M);
         // charged pairs (positions < M) and whether they are still in (L, r) order
         const bool charged = i < M;
         const double wv_ = charged ? a : v;
@@ -2037,54 +2091,54 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
             nr = sh.l0r[wv + 1];
         }
         const bool out_of_order = i + 1 < M && !lt_pair(wv_, r, nx, nr);
-        const bool brk = k0 == 1 && i + 1 < M && c != sh.jc[(t + i + 1u) & (2u * N - 1u)];
-        const uint64_t uns = ballot(out_of_order), bad = ballot(out_of_order && !brk), brks = ballot(brk);
-        if (lane == 0) {
-            sh.wuns[wv] = (uns != 0 ? 1u : 0u) | (bad != 0 ? 2u : 0u);
-            sh.wbrk[wv] = brks;
-        }
+        const uint64_t uns = ballot(out_of_order);
+        uint32_t flags = uns != 0 ? 1u : 0u;
+        if (N >= kLptRunsFrom && uns) flags |= ballot(out_of_order && c == sh.jc[(t + i + 1u) & (2u * N - 1u)]) ? 2u : 0u;
+        if (lane == 0) sh.wuns[wv] = flags;
         if (charged) {
             sh.cv[i] = a;
             sh.cr[i] = r;
         }
         __syncthreads();
-        const uint32_t flags = lane < NWV ? sh.wuns[lane] : 0u;
-        const uint64_t wbrk = lane < NWV ? sh.wbrk[lane] : 0ull;
-        const uint32_t any_uns = (ballot((flags & 1u) != 0u) ? 1u : 0u) | (ballot((flags & 2u) != 0u) ? 2u : 0u);
-        const uint32_t nbrk = rdlane(wave_incl_scan_u32((uint32_t)__popcll(wbrk)), 63u);
+        uint32_t any_uns = 0;
+        for (uint32_t u = 0; u < NWV; ++u) any_uns |= sh.wuns[u];
+        any_uns = (uint32_t)__builtin_amdgcn_readfirstlane((int)any_uns);
         const uint32_t nxt = cur ^ 1u;
-        if (any_uns == 0 || (N >= kLptRunsFrom && any_uns == 1u && nbrk < kLptRuns)) {
+        uint32_t nruns = any_uns ? kLptRuns + 1u : 1u;  // sorted runs of the charged list
+        uint32_t rs[kLptRuns + 1];                      // and their starts
+        if (N >= kLptRunsFrom && any_uns == 1u && k0 == 1) {
+            // a run ends where the count changes: in at most two of 64 pieces of the batch, else
+            // there are too many
+            const uint32_t s = (M + 63u) / 64u, at = lane * s, to = at + s < M ? at + s : M - 1u;
+            const uint64_t has = ballot(at + 1u < M && sh.jc[(t + at) & (2u * N - 1u)] != sh.jc[(t + to) & (2u * N - 1u)]);
+            if (__popcll(has) < kLptRuns) {
+                static_assert(kLptRuns == 3 && N <= 1024, "two pieces of up to 16 jobs by lane");
+                const uint32_t piece = lane < 16u ? first_lane(has) : first_lane(has & (has - 1ull));
+                const uint32_t e = piece * s + (lane & 15u);
+                const bool in = lane < 16u * (uint32_t)__popcll(has) && (lane & 15u) < s && e + 1u < M;
+                const uint64_t ends = ballot(in && sh.jc[(t + e) & (2u * N - 1u)] != sh.jc[(t + e + 1u) & (2u * N - 1u)]);
+                nruns = 1u + (uint32_t)__popcll(ends);
+                rs[1] = ends ? rdlane(e, first_lane(ends)) + 1u : M;
+                rs[2] = ends & (ends - 1ull) ? rdlane(e, first_lane(ends & (ends - 1ull))) + 1u : M;
+            }
+        }
+        if (nruns <= kLptRuns) {
             // merge path: the charged list cv[0..M), one sorted run or one per count, and the
             // unchanged sorted positions M..R-1
-            uint32_t rs[kLptRuns + 1];  // the runs' starts
-            uint32_t nr_ = 1;
-            rs[0] = 0;
-            if (any_uns) {
-#pragma unroll
-                for (uint32_t q = 1; q < kLptRuns; ++q) rs[q] = M;
-                for (uint64_t waves = ballot(wbrk != 0ull); waves; waves &= waves - 1ull) {
-                    const uint32_t u = first_lane(waves);
-                    for (uint64_t w = rdlane64(wbrk, u); w; w &= w - 1ull) {
-                        const uint32_t at = u * 64u + (uint32_t)__builtin_ctzll(w) + 1u;
-#pragma unroll
-                        for (uint32_t q = 1; q < kLptRuns; ++q)
-                            if (q == nr_) rs[q] = at;
-                        ++nr_;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (uint32_t q = 1; q < kLptRuns; ++q) rs[q] = M;
-            }
-            rs[kLptRuns] = M;
             if (i < R) {
                 const double y = charged ? a : v;
                 uint32_t pos = charged ? lower_bound_pair(sh.v[cur], sh.r[cur], M, R - M, y, r) : i - M;
+                if (nruns == 1u) {
+                    pos += charged ? i : lower_bound_pair(sh.cv, sh.cr, 0, M, y, r);
+                } else {
+                    rs[0] = 0;
+                    rs[kLptRuns] = M;
 #pragma unroll
-                for (uint32_t q = 0; q < kLptRuns; ++q) {
-                    if (rs[q] >= rs[q + 1]) continue;
-                    const bool own = charged && i >= rs[q] && i < rs[q + 1];
-                    pos += own ? i - rs[q] : lower_bound_pair(sh.cv, sh.cr, rs[q], rs[q + 1] - rs[q], y, r);
+                    for (uint32_t q = 0; q < kLptRuns; ++q) {
+                        if (rs[q] >= rs[q + 1]) continue;
+                        const bool own = charged && i >= rs[q] && i < rs[q + 1];
+                        pos += own ? i - rs[q] : lower_bound_pair(sh.cv, sh.cr, rs[q], rs[q + 1] - rs[q], y, r);
+                    }
                 }
                 sh.v[nxt][pos] = y;
                 sh.r[nxt][pos] = r;
@@ -2105,10 +2159,9 @@ __global__ __launch_bounds__(N) void k_lpt_block(uint32_t R, uint32_t Cmax, cons
         cur = nxt;
         t += k0 > 1 ? 1u : (M ? M : 1u);  // M = 0 only for a job with k = 0, which admission never makes
         if (t >= base + N) {  // the ring's older half is consumed: refill it one half ahead
-            const uint32_t slot = (base + i) & (2u * N - 1u);
-            sh.jc[slot] = pc, sh.jo[slot] = po, sh.jk[slot] = (uint16_t)pk;
+            put(base + 2 * N + i, pre);
             base += N;
-            job(base + 2 * N + i, pc, po, pk);
+            pre = job(base + 2 * N + i);
         }
         __syncthreads();
     }

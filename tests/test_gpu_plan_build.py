@@ -155,3 +155,39 @@ def test_lpt_loads_beyond_the_integers_of_a_double(R):
     assert int(err) == 0 and int(ps.num_admitted[0]) == A and int(ps.cold[0]) == cold and load.min() >= 2.0**53
     np.testing.assert_array_equal(ps.members[0, :A].cpu().numpy().view(np.uint16), members)
     np.testing.assert_array_equal(ps.load[0].cpu().numpy().view(np.uint64), load.view(np.uint64))
+
+
+@pytest.mark.parametrize("R", [65, 128, 129, 256, 257, 512, 513, 1024])
+@pytest.mark.parametrize("kind", ["distinct", "steps", "pairs", "ties"])
+def test_lpt_batches_of_few_and_many_counts(R, kind):
+    # batches of one to many counts, in order or not (merged by runs, or sorted), runs of one
+    # count around the lengths from which they are placed by epochs, k > 1 in front
+    rng = np.random.default_rng(R)
+    W = 12
+    A = R * W
+    if kind == "distinct":
+        c = 50_000 + np.arange(A)[::-1] * rng.integers(1, 4)
+    elif kind == "steps":    # runs of 1 to 7 R jobs, steps small and large
+        c = np.repeat(np.cumsum(rng.integers(1, 900, 64))[::-1] + 40_000, rng.integers(1, 7 * R, 64))[:A]
+    elif kind == "pairs":    # two or three counts per batch
+        c = np.repeat(np.cumsum(rng.integers(1, 300, A))[::-1] + 5000, rng.integers(R // 3 + 1, R, A))[:A]
+    else:                    # loads that meet
+        c = np.sort(rng.choice([1, 2, 4, 8, 64, 3000], A, p=[0.3, 0.2, 0.2, 0.2, 0.09, 0.01]))[::-1]
+    K = A + 50
+    row = np.zeros(K, np.uint32)
+    row[: len(c)] = c
+    row[len(c):] = 1
+    say(f"[case] lpt batches {kind} R={R}")
+    counts = torch.from_numpy(row.view(np.int32)).cuda()[None].contiguous()
+    ps = B.PlanSet([(0, W, B.CR_WINDOW_SUM, 1, 1, B.CR_PLAN_FULL, 0)], 1, R, W, K, 1, "cuda")
+    ws = torch.empty(B.cr_admit_workspace_bytes(1, R, W), dtype=torch.uint8, device="cuda")
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    B.cr_admit(counts, ps.c, ws, err)
+    B.cr_place_lpt(counts, ps.c)
+    assert int(err) == 0
+    a = int(ps.num_admitted[0])
+    off = ps.member_off[0, : a + 1].cpu().numpy()
+    keys = ps.order[0, :a].cpu().numpy().astype(np.uint32)
+    members, _, load = oracle.place_lpt(keys, np.diff(off).astype(np.uint32), row, R, int(ps.cold[0]))
+    np.testing.assert_array_equal(ps.members[0, : off[-1]].cpu().numpy().view(np.uint16), members)
+    np.testing.assert_array_equal(ps.load[0].cpu().numpy().view(np.uint64), load.view(np.uint64))
