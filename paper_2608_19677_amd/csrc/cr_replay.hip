@@ -359,7 +359,11 @@ __device__ __forceinline__ T at_bytes(const T* p, uint32_t off, uint32_t k)
 template <bool kOne>
 __host__ __device__ constexpr uint32_t wide_waves() { return kOne ? 8u : 4u; }
 
-constexpr uint64_t kWideMinBlocks = 256;
+// Blocks of eight wavefronts from which they are used (for one interval): fewer leave CUs idle that
+// blocks of four would take. 2e6 requests, 1,024 destinations 41 us with eight and 46 with four;
+// 1e6, 65 destinations 32 and 30.
+constexpr uint64_t kWideMinBlocks = 128;
+static_assert(wide_waves<true>() == 8, "sub-tiles of 8,192");
 
 template <bool kOne>
 __host__ __device__ constexpr uint32_t wide_stage_bytes() { return wide_waves<kOne>() * 1024u * (kOne ? 8u : 10u); }
@@ -1604,11 +1608,12 @@ extern "C" cr_status cr_replay_partition(const uint32_t* keys, const uint16_t* s
     if (!off || !err || (n > 0 && (!keys || !suffix || !dest))) return CR_EINVAL;
     const ReplayWs w = replay_layout(ws_base(ws), n, P, R);
     PartGeom g = part_geom(n, P);
-    // R > 64: whole sub-tiles of the wide scatter (a tile of 1,024 occupies one wavefront of a
-    // block: 4,000,037 x 4 candidates, 257 destinations 210 -> 81 us), where the chip
-    // then still holds a block per CU (below that, smaller tiles spread the work over more CUs)
-    const uint64_t sub = 1024u * (J == 1 ? wide_waves<true>() : wide_waves<false>());
-    if (R > 64 && P * ((n + sub - 1) / sub) >= kWideMinBlocks) {
+    // R > 64: whole sub-tiles of the wide scatter, however few (a tile of 1,024 occupies one
+    // wavefront of a block, whose phases are as long as a full sub-tile's: 4,000,037 x 4 candidates, 257
+    // destinations 210 -> 81 us; 1e6 x 1, 65 destinations 57 -> 31 us; 1e5 x 1 31 -> 29 us)
+    const bool one = J == 1 && P * ((n + 8191u) / 8192u) >= kWideMinBlocks;
+    if (R > 64) {
+        const uint64_t sub = 1024u * (one ? wide_waves<true>() : wide_waves<false>());
         g.tile = (g.tile + sub - 1) / sub * sub;
         g.ntiles = (n + g.tile - 1) / g.tile;
     }
@@ -1645,7 +1650,7 @@ extern "C" cr_status cr_replay_partition(const uint32_t* keys, const uint16_t* s
                            st, keys, suffix, dest, n, off, J, P, R, g.tile, g.ntiles, w.tcnt, w.grp_off,       \
                            w.rec);                                                                                  \
     } while (0)
-        if (J == 1) CR_WIDE(true);
+        if (one) CR_WIDE(true);
         else CR_WIDE(false);
 #undef CR_WIDE
     }

@@ -1,6 +1,6 @@
 """GPU parity of the partition at the edges of its sub-tiles and rows. More than 64
-destinations: sub-tiles of 8,192 requests with one interval and of 4,096 with several, 1,024
-per wavefront; request counts around whole sub-tiles and wavefronts, padded and full
+destinations: sub-tiles of 8,192 requests with one interval and 128 of them or more, else of
+4,096, 1,024 per wavefront; request counts around whole sub-tiles and wavefronts, padded and full
 destination rows, skewed and uniform destinations, few and many blocks. Up to 64: counter rows
 of an odd number of 16-byte pieces, under the staged records."""
 import numpy as np
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("R", [65, 257, 1023, 1024])
-@pytest.mark.parametrize("n,J,P", [(1, 1, 2), (8192 * 3, 1, 3), (8192 * 5 + 1025, 1, 64), (8192 * 4 + 63, 1, 64), (4096 * 2, 3, 2),
+@pytest.mark.parametrize("n,J,P", [(1, 1, 2), (8192 * 3, 1, 3), (8192 * 5 + 1025, 1, 64), (8192 * 4 + 63, 1, 64), (4096 * 7 + 1030, 1, 4), (4096 * 2, 3, 2),
                                    (4096 * 4 + 1023, 7, 64), (4096 * 5 + 1, 30, 64)])
 def test_wide_partition_parity(R, n, J, P):
     wl = wl_mod.small_random(R + n % 89, num_keys=1500, n=n, R=R, Ws=[4 + 3 * (c % 9) for c in range(P)], J=J)
