@@ -631,7 +631,9 @@ __global__ __launch_bounds__(kSortBlock, kNpl <= 20 ? 8 : 1) void k_sort_window_
 constexpr uint32_t kWideCmax = 1024;   // smallest C_max whose buffers hold the scratch
 // Smallest row. 100 windows of 50,000 keys took 99 us with a block each (they fill the chip by
 // themselves) and 162 us this way.
-constexpr uint32_t kWideKeys = 73728, kWideKeysPerWindow = 1536;
+// From 113 windows on a block each fills the chip whatever the rows (1e6 Zipf keys: 100 windows 1,225
+// us by one block each and 1,140 by many, 150 windows 1,250 and 1,685).
+constexpr uint32_t kWideKeys = 73728, kWideKeysPerWindow = 1536, kWideWindows = 112;
 constexpr uint32_t kWideBins = 1728;
 constexpr uint32_t kWideSub = 1024;    // bins of a refinement: 10 bits
 constexpr uint32_t kWideThreads = 256;
@@ -2504,7 +2506,8 @@ extern "C" cr_status cr_admit(const uint32_t* counts, const cr_plan_set* plans, 
         else if (K <= 1024u * 20u) CR_SORT_REG(20);
         else CR_SORT_REG(32);
 #undef CR_SORT_REG
-    } else if (K >= kWideKeys + (uint64_t)kWideKeysPerWindow * plans->num_windows && K <= 0xFFF00000u && cmax >= kWideCmax && plans->num_windows <= 65535u) {
+    } else if (K >= kWideKeys + (uint64_t)kWideKeysPerWindow * plans->num_windows && K <= 0xFFF00000u && cmax >= kWideCmax &&
+               plans->num_windows <= kWideWindows) {
         const uint32_t NW = plans->num_windows, tile = wide_tile(K, NW);
         const dim3 tiles((K + tile - 1u) / tile, NW), th(kWideThreads);
         uint32_t *ord = plans->order, *ocnt = plans->order_count;
