@@ -63,15 +63,20 @@ def test_lpt_runs_of_equal_counts(case):
     compare_all(wl, gp, gp.host(), opipe.run(wl))
 
 
-# The window order of rows sorted by many blocks (K >= 65,536, budgets from 1,024 slots): thresholds
-# inside the exact bins and inside refined ones, ties cut by key, rows with fewer nonzero keys
-# than slots, odd row lengths, budgets sorted by one block and by 1 to 3 radix passes.
+# The window order of long rows. By one block per window: below 73,728 + 1,536 keys per window,
+# and for more than 112 windows. By many blocks (budgets from 1,024 slots): thresholds inside the
+# exact bins and inside refined ones, ties cut by key, rows with fewer nonzero keys than slots and
+# empty ones, odd row lengths, budgets sorted by one block and, above 4,096 slots, by 1 to 3 radix
+# passes, of one window and of several.
 WIDE = [
     # K, R, W, windows, kind
     (65_535, 64, 16, 3, "zipf"), (65_537, 32, 64, 5, "zipf"), (128_824, 30, 64, 2, "big"), (70_000, 30, 64, 4, "flat"),
     (66_666, 64, 64, 2, "few"), (65_536, 128, 64, 2, "zipf"), (100_003, 64, 300, 40, "big"), (90_000, 100, 100, 1, "huge"),
     (70_000, 200, 200, 2, "flat"), (262_147, 1024, 128, 1, "zipf"), (66_001, 33, 125, 2, "huge"), (80_001, 64, 65, 1, "one"),
     (200_000, 7, 100, 2, "big"),
+    (75_263, 32, 64, 1, "zipf"), (75_264, 32, 64, 1, "zipf"), (76_801, 32, 32, 2, "flat"), (80_003, 64, 64, 4, "flat"), (81_411, 200, 200, 5, "flat"),
+    (80_001, 64, 64, 3, "few"), (80_002, 128, 64, 3, "few"), (245_761, 64, 16, 112, "few"), (247_301, 64, 16, 113, "few"),
+    (83_003, 64, 300, 3, "mid"), (84_001, 50, 100, 3, "huge"), (90_001, 65, 64, 10, "big"), (79_001, 80, 100, 3, "one"),
 ]
 
 
@@ -84,6 +89,8 @@ def test_window_order_of_wide_rows(K, R, W, NW, kind):
         rows = rng.integers(2000, 90_000, (NW, K))
     elif kind == "huge":     # up to 2^32 - 1: all three
         rows = rng.integers(1, 1 << 32, (NW, K))
+    elif kind == "mid":      # counts of 11 bits
+        rows = rng.integers(1, 2000, (NW, K))
     elif kind == "flat":     # ties everywhere
         rows = rng.integers(5, 8, (NW, K))
     elif kind == "few":      # fewer nonzero keys than slots, an empty row
