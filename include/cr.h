@@ -320,12 +320,13 @@ cr_status cr_replay_partition(const uint32_t* keys, const uint16_t* suffix, cons
 /* Second phase of cr_replay: replays the partitioned workspace (same n, J, P, R, W)
  * through the per-destination LRU caches and accumulates stats. Each segment rebuilds the
  * cache state it starts from by scanning its stream backwards for W distinct keys, at most
- * 64 segment lengths; a segment whose scan runs out before that (a stretch with fewer than
+ * 64 max(S, 1,024) records for segments of S records; a segment whose scan runs out before that (a stretch with fewer than
  * W distinct keys) is left to a second launch, in which one wavefront per run of such
  * segments replays the segment before the run (without counting it) and then the run, in
- * order. Each request is thus replayed at most twice and scanned at most 65 times (the scan
- * of a stretch of known keys is a fraction of its replay), whatever the key mix; the results
- * do not depend on which launch counts them.
+ * order. Each request is thus replayed at most twice and scanned at most 65 times (in calls of
+ * fewer than 4,194,304 request-candidate pairs, whose segments can be as short as 256 records,
+ * 64 * 1,024 / S + 1 times; the scan of a stretch of known keys is a fraction of its replay),
+ * whatever the key mix; the results do not depend on which launch counts them.
  * The launches of the first pass (one per class of list sizes and one per grouped form)
  * are independent of each other. When there are two or more and `stream`
  * is not capturing, they run on two side streams of the device, forked from `stream`
