@@ -7,15 +7,15 @@
 //          (no zeroing pass, no global atomics);
 //   tiled  few long intervals: rows are zeroed, blocks count tiles of requests into
 //          LDS-private bins and merge nonzero bins with one atomic each;
-//   ranges key spaces beyond LDS, up to 32 ranges that fit: a block per (range, interval,
-//          part of a long interval) counts its range's keys in LDS;
+//   ranges key spaces beyond LDS, up to 32 ranges that fit: a block per (range, part of an
+//          interval) counts its range's keys in LDS;
 //   global larger key spaces: rows are zeroed and each request adds one atomic.
-// A device-scope atomic per request costs about 0.12 ns of the whole chip, and far more where
+// A device-scope atomic per request costs about 0.1 ns of the whole chip, and far more where
 // a Zipf head puts millions of them on one address. Against one per request: 4e6 requests over
-// 24 intervals of 128,824 keys 527 -> 45 us, 2e7 over 5 of 200,000 keys 7,420 -> 134 us, 5e6
-// over 10 of 1,000,000 keys 470 -> 113 us; against 16-bit bins of the whole key space per tile
-// of 64,512 requests: 5e7 over 100 intervals of 50,000 keys 189 -> 148 us (its hot keys' LDS
-// conflicts now bound it), 1e6 over 200 of 45,000 92 -> 29 us.
+// 24 intervals of 128,824 keys (Zipf 0.9) 236 -> 42 us, 2e7 over 5 of 200,000 (Zipf 1.0) 7,675 ->
+// 143, 5e6 over 10 of 1,000,000 (0.9) 470 -> 116; against 16-bit bins of the whole key space per
+// tile of 64,512 requests: 5e7 over 100 intervals of 50,000 (1.2) 186 -> 145 us (its hot keys' LDS
+// conflicts now bound it), 1e6 over 200 of 45,000 (1.0) 90 -> 28.
 #include "cr_common.h"
 
 namespace cr {

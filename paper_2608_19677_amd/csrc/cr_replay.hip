@@ -353,9 +353,9 @@ __device__ __forceinline__ T at_bytes(const T* p, uint32_t off, uint32_t k)
 // staged later. The phases of a sub-tile are chains of LDS and memory round trips that only
 // other wavefronts can cover, and a destination's run in a sub-tile (4 or 8 records at R = 1,024)
 // is what a line of HBM gets at once: with one interval, eight wavefronts stage 8,192 records in
-// 80 KB, and two blocks share a CU (4 wavefronts per SIMD). 1e8 requests x
-// 64 candidates over 1,024 destinations: 46.1 -> 38.3 ms (four wavefronts, 74 KB with 8-byte
-// records, 32-bit counters and scratch of its own: 46.1; four, three blocks of 44 KB: 43.9).
+// 80 KB, and two blocks share a CU (4 wavefronts per SIMD). The whole partition of 1e8 requests
+// x 64 candidates over 1,024 destinations takes 40.6 ms, 47.4 with four wavefronts (74 KB with
+// 8-byte records, 32-bit counters and scratch of its own).
 template <bool kOne>
 __host__ __device__ constexpr uint32_t wide_waves() { return kOne ? 8u : 4u; }
 
@@ -745,8 +745,8 @@ struct StreamStats {
 // the first segment of a stream has nothing to rebuild), rebuilds the predecessor's state
 // as that segment did, replays it without counting, and then replays the run in order,
 // counting it and writing the final state if the run ends the stream. Each marked record
-// is thus replayed once more, and every record is scanned at most kRebuildBudget + 1 times,
-// whatever the keys. The kSeq launch rebuilds without a budget: a run's predecessor is an
+// is thus replayed once more, and every record is scanned at most kRebuildBudget + 1 times
+// (by segments of S < kSegFloor records, kRebuildBudget kSegFloor / S + 1 times), whatever the keys. The kSeq launch rebuilds without a budget: a run's predecessor is an
 // unmarked segment, whose rebuild ended within its budget. A scan that meets known keys only
 // takes 256 records a step, about a tenth of the time their replay takes, and a marked run is
 // one serial chain, so the budget is wide: 2,000 keys over 30 streams of 133,000 requests took
@@ -785,11 +785,13 @@ __device__ __forceinline__ bool item_marked(const uint8_t* __restrict__ aborted,
 //   - the step's last access of every key becomes its position, the old position's bit is
 //     cleared, and T moves to the W-th bit.
 // The cost of a step hardly depends on W, where a list in registers paid a compare and a move
-// per 64 slots for every record. Measured (the cr_replay_lru call, 4e7 requests x 8 candidates
-// over 1,024 streams; list in registers before): W = 64 3.83 -> 2.35 ms, 86 6.64 -> 2.39,
-// 156 7.64 -> 2.50, 283 10.5 -> 2.74, 512 14.3 -> 3.17. Bound by instruction issue up to W of
-// about 200, and by the latency of the dependent LDS round trips where the tables leave few
-// wavefronts per CU.
+// per 64 slots for every record. Measured (the cr_replay_lru call, 4e7 Zipf 0.9 requests of 1e6
+// keys x 8 candidates over 1,024 streams, four in five routed by key; list in registers before):
+// W = 64 3.26 -> 2.31 ms, 86 5.58 -> 2.43, 156 6.89 -> 2.52, 283 9.98 -> 2.92, 512 16.7 -> 4.22.
+// Bound by instruction issue where many wavefronts fit a SIMD and by the latency of the
+// dependent LDS round trips where the tables leave few: counters of 8e8 records give, at W = 86,
+// 156, 283 and 512, 5.6, 4.1, 3.2 and 2.1 wavefronts per SIMD, VALU busy 0.59, 0.56, 0.49 and 0.37 of
+// the time and wavefronts waiting 0.39 to 0.52 of theirs; the list of W < 64 keeps the VALU busy 0.80.
 // Entries past T stay in the table (their keys may come back to the same slot); when the
 // table or the 64 bitmap words run full, the live entries are re-inserted into an empty table
 // at positions that leave the words before them free (refresh).
