@@ -124,15 +124,15 @@ __global__ __launch_bounds__(kCountThreads) void k_count_ranges(const uint32_t* 
     const uint32_t tid = threadIdx.x, bd = blockDim.x, lane = lane_id();
     const uint32_t b0 = blockIdx.x * per, nb = K - b0 < per ? K - b0 : per;  // b0 < K
     bool bad = false;
-    const uint64_t before = parts_before(n, inv), items = J + before;
+    const uint64_t before = rdlane64(parts_before(n, inv), 0u), items = J + before;
     for (uint64_t y = blockIdx.y; y < items; y += gridDim.y) {
         // the last interval whose first item is at most y, among y - before .. y; its ends with it
         uint32_t j = y > before ? (uint32_t)(y - before) : 0u, jhi = y < J ? (uint32_t)y + 1u : J;
+        uint32_t stride = jhi - j < 64u ? 1u : (jhi - j + 62u) / 63u;
+        uint64_t q = (uint64_t)j + lane * stride, o = off[q < J ? q : J];
+        for (uint32_t b = tid; b < nb; b += bd) hist[b] = 0u;  // (while the bounds come)
         uint64_t s, e;
         for (;;) {
-            const uint32_t stride = jhi - j < 64u ? 1u : (jhi - j + 62u) / 63u;
-            const uint64_t q = (uint64_t)j + lane * stride;
-            uint64_t o = off[q < J ? q : J];
             o = o < n ? o : n;
             const uint32_t le = (uint32_t)__popcll(ballot(q < jhi && q + parts_before(o, inv) <= y));
             const uint32_t at = le ? le - 1u : 0u;
@@ -141,19 +141,23 @@ __global__ __launch_bounds__(kCountThreads) void k_count_ranges(const uint32_t* 
             j += at * stride;
             if (stride == 1u) break;
             jhi = jhi - j < stride ? jhi : j + stride;
+            stride = jhi - j < 64u ? 1u : (jhi - j + 62u) / 63u;
+            q = (uint64_t)j + lane * stride;
+            o = off[q < J ? q : J];
         }
         s = s < e ? s : e;
-        const uint64_t len = e - s, first = parts_before(s, inv), part = y - j - first;
+        // (what comes from doubles is read back into scalar registers)
+        const uint64_t len = e - s, first = rdlane64(parts_before(s, inv), 0u), part = y - j - first;
         uint64_t parts = 1;
         if (len > part_len) {
-            const uint64_t slots = parts_before(e, inv) - first + 1u, want = (len + part_len - 1u) / part_len;
-            parts = want < slots ? want : slots;
+            const uint64_t slots = parts_before(e, inv) - first + 1u, want = parts_before(len - 1u, inv) + 1u;
+            parts = rdlane64(want < slots ? want : slots, 0u);
         }
         if (part >= parts) continue;
-        const uint64_t per_part = parts == 1u ? len : (len + parts - 1u) / parts;
+        // (in doubles: every wavefront of the block would run the 64-bit division; at least len / parts)
+        const uint64_t per_part = parts == 1u ? len : rdlane64((uint64_t)((double)len / (double)parts), 0u) + 1u;
         const uint64_t ps = s + part * per_part < e ? s + part * per_part : e;
         const uint64_t pe = ps + per_part < e ? ps + per_part : e;
-        for (uint32_t b = tid; b < nb; b += bd) hist[b] = 0u;
         __syncthreads();
         count_range<kBinsRange>(keys, ps, pe, K, hist, nullptr, bad, b0, nb);
         __syncthreads();
